@@ -139,7 +139,11 @@ void nwm_plan_destroy(nwm_plan *plan);
  *     (l_i = tokens of source sentence i; S_raw = 0 when l_i = 0);
  *   rho[i][j]   = min(l_i, l'_j) / max(l_i, l'_j)  (1 when both are 0);
  *   S = sigmoid(w0 * S_raw + w1 * rho + b).
- * The contraction runs on MFMA with `prec` operands and FP32 accumulation.
+ * The contraction takes `prec` operands (T rounded to BF16 or kept in FP32,
+ * Y exact) and accumulates in FP32: on MFMA over dense tiles, or, where the
+ * target sentences' words are few against the tiles' vocabulary, as sums over
+ * each target sentence's words (BF16: on MFMA; FP32: the same additions in the
+ * same order, identical results).
  * Outputs (device, FP32, row-major n_b x m_b blocks, pair b at element
  * offset sum_{c<b} n_c m_c): S [S_elems]; S_raw [S_elems] or NULL.
  * ws: device workspace of ws_bytes, contents need not persist. */
@@ -274,14 +278,17 @@ nwm_status nwm_union_kept(const nwm_plan *plan, const int32_t *kept_fwd, const i
  *                                 fill runs whole workgroups of four waves)
  *   NWM_PARAM_MERGE_WAVES_PER_CU  dictionary-merge waves per compute unit
  *                                 (0 = as many as the LDS allows; default 0)
- *   NWM_PARAM_SCORE_XCD_MAP       1 = contraction tiles of one pair on one XCD
- *                                 (shared L2), 0 = dispatch order; default 1
+ *   NWM_PARAM_SCORE_XCD_MAP       1 = dense contraction tiles of one pair on
+ *                                 one XCD (shared L2), 0 = dispatch order;
+ *                                 default 1
  *   NWM_PARAM_DP_HOT_PERCENT      DP strips of pairs whose dependency chain is
  *                                 at least this percent of the longest one run
  *                                 at raised wave priority (0 = never; default 50)
- *   NWM_PARAM_SCORE_COMPACT       1 = the contraction of each 64 x 64 tile runs
- *                                 over the words of its 64 target sentences
- *                                 only (the other words have a zero Y factor);
+ *   NWM_PARAM_SCORE_COMPACT       1 = the contraction runs over the words of
+ *                                 the target sentences only (the other words
+ *                                 have a zero Y factor): each sentence's own,
+ *                                 or those of a 64 x 64 tile's 64 sentences,
+ *                                 whichever the plan finds cheaper;
  *                                 0 = over the whole vocabulary.  Default 1.
  *                                 The FP32 sums are taken in another order, so
  *                                 S may differ in the last bits.
@@ -291,8 +298,8 @@ nwm_status nwm_union_kept(const nwm_plan *plan, const int32_t *kept_fwd, const i
  *                                 pair taller than one strip publishes nothing,
  *                                 so the strips below it give up (exercises the
  *                                 failure report of nwm_align_check); default 0
- *   NWM_PARAM_SCORE_KGROUP        K width of one round of the compacted
- *                                 contraction: 1 = one 32-word chunk per round,
+ *   NWM_PARAM_SCORE_KGROUP        K width of one round of the contraction over a
+ *                                 tile's vocabulary: 1 = one 32-word chunk per round,
  *                                 2 = two chunks (64 words) scattered before one
  *                                 barrier; the same sums in the same order, so
  *                                 the results are identical.  Default 1.

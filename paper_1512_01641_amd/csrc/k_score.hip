@@ -21,6 +21,7 @@
 // rounded once to the operand type.
 #include "nwm_internal.h"
 #include "libnwmine.h"
+#include "nwm_score.h"
 
 #include <type_traits>
 
@@ -274,29 +275,6 @@ struct ScoreLds {
   static constexpr int BYTES = OPS > RED ? OPS : RED;
 };
 
-// Features and logistic score of one cell (Sec. 4): S_raw = dot / l (0 for an
-// empty source sentence), rho = min(l, l') / max(l, l') (1 when both
-// sentences are empty), z = w0 S_raw + w1 rho + b, S = 1 / (1 + exp(-z)).
-// rl, rlt are the reciprocals of l, l' (inf for 0), so rho = min(l / l',
-// l' / l) = min(l rlt, l' rl); positive floats order as their bit patterns,
-// so that minimum is an integer one.  An exponent past the FP32 range gives
-// exp = inf and S = 0 (1 / inf), exp = 0 gives S = 1.  CHECKED = false drops
-// the tests for empty sentences (every length of the tile is positive).
-template <bool CHECKED>
-static __device__ __forceinline__ float logistic_cell(float dot, float l, float rl, float lt, float rlt,
-                                                      const nwm_scorer &sc, float &sraw) {
-  const float LOG2E = 1.4426950408889634f;
-  float sr = dot * rl;
-  float rho = __uint_as_float(min(__float_as_uint(l * rlt), __float_as_uint(lt * rl)));
-  if (CHECKED) {
-    sr = l > 0.0f ? sr : 0.0f;
-    rho = (l > 0.0f || lt > 0.0f) ? rho : 1.0f;
-  }
-  sraw = sr;
-  const float z = __builtin_fmaf(sc.w0, sr, __builtin_fmaf(sc.w1, rho, sc.b));
-  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-z * LOG2E));
-}
-
 // Epilogue of a tile: accumulators -> LDS (transpose) -> per row the
 // logistic scorer and coalesced stores of S (and S_raw).
 static __device__ __forceinline__ void score_epilogue(const f32x4 (&acc)[4][4], float *red, const PlanDev &P,
@@ -411,6 +389,32 @@ static __device__ __forceinline__ void score_epilogue_regs(const f32x4 (&acc)[4]
   }
 }
 
+// The record of contraction tile gt: its pair by binary search of the pairs'
+// first tiles in lane order.
+static __device__ __forceinline__ GtMeta locate_tile(const PlanDev &P, int gt) {
+  int lo = 0, hi = P.B;   // lane_gt[lo] <= gt < lane_gt[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (P.lane_gt[mid] <= gt) lo = mid;
+    else hi = mid;
+  }
+  GtMeta g;
+  const int k = gt - P.lane_gt[lo], nct = P.lane_ct[lo + 1] - P.lane_ct[lo];
+  g.pair = P.lane_pair[lo];
+  g.rt = P.lane_rt[lo] + k / nct;
+  g.ct = P.lane_ct[lo] + k % nct;
+  g.m = P.m[g.pair];
+  g.row0 = P.rt_row0[g.rt];
+  g.rows = P.rt_rows[g.rt];
+  g.col0 = P.ct_col0[g.ct];
+  g.cols = P.ct_cols[g.ct];
+  g.s_first = P.sfirst[g.pair] + g.row0;
+  g.t_first = P.tfirst[g.pair] + g.col0;
+  g.s_off = P.s_off[g.pair];
+  g.pad = 0;
+  return g;
+}
+
 template <bool BF16>
 __global__ __launch_bounds__(64) void k_score(PlanDev P, const int64_t *__restrict__ src_off,
                                               const int64_t *__restrict__ tgt_off, const uint2 *__restrict__ a_list,
@@ -433,13 +437,11 @@ __global__ __launch_bounds__(64) void k_score(PlanDev P, const int64_t *__restri
   const int gl = xcd_map ? (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
   if (gl >= G) return;
   const int gt = g0 + gl;
-  const int rt = P.gt_rt[gt], ct = P.gt_ct[gt];
-  const int pair = P.rt_pair[rt];
-  const int row0 = P.rt_row0[rt], rows = P.rt_rows[rt];
-  const int col0 = P.ct_col0[ct], cols = P.ct_cols[ct];
-  const int64_t s_first = P.sfirst[pair] + row0;
-  const int64_t t_first = P.tfirst[pair] + col0;
-  const int m = P.m[pair];
+  const GtMeta g = locate_tile(P, gt);
+  const int rt = g.rt, ct = g.ct, pair = g.pair;
+  const int row0 = g.row0, rows = g.rows, col0 = g.col0, cols = g.cols;
+  const int64_t s_first = g.s_first, t_first = g.t_first;
+  const int m = g.m;
   const int nch = P.nch;
   const int lane = threadIdx.x;
   // where idle lanes write: one padding element (row 0, column KC) shared
@@ -674,9 +676,7 @@ __global__ __launch_bounds__(64) void k_score_c(PlanDev P, const int64_t *__rest
   const int gl = xcd_map ? (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
   if (gl >= G) return;
   const int gt = g0 + gl;
-  // the tile's metadata in one record; everything else it needs is at most
-  // two dependent loads away
-  const GtMeta g = P.gt_meta[gt];
+  const GtMeta g = locate_tile(P, gt);
   const int rt = g.rt, ct = g.ct;
   const int nch = P.nch;
   const int lane = threadIdx.x;

@@ -28,6 +28,14 @@ hipError_t launch_expand_a(const PlanDev &, const int64_t *, const int32_t *, co
 bool expand_a_fits(int max_sent_tokens, int max_deg, int nch);
 hipError_t launch_pack_dict(const int32_t *, const int32_t *, const float *, int, int, uint2 *, hipStream_t);
 hipError_t build_set_attrs(int nch, int V);
+hipError_t launch_merge_tiles(const PlanDev &, const int64_t *, const int32_t *, const uint2 *, int, uint2 *,
+                              int32_t *, int, int, hipStream_t);
+hipError_t launch_tgt_lists(const PlanDev &, const int64_t *, const int32_t *, uint16_t *, uint2 *, float *, int, int,
+                            hipStream_t);
+hipError_t launch_score_s(const PlanDev &, bool, int, int, const int64_t *, const int64_t *, const uint2 *,
+                          const int32_t *, const uint16_t *, const uint2 *, const float *, nwm_scorer, float *,
+                          float *, int, int, hipStream_t);
+hipError_t sparse_set_attrs();
 hipError_t launch_score(const PlanDev &, bool, const int64_t *, const int64_t *, const uint2 *, const int32_t *,
                         const uint32_t *, const int32_t *, nwm_scorer, float *, float *, int, int, int, const uint2 *,
                         const int32_t *, const int2 *, const int64_t *, const int64_t *, int, int, hipStream_t);
@@ -156,13 +164,19 @@ struct nwm_plan {
   // pairs); nwm_mine prepares and scores them first and runs their DP on a
   // stream of its own while the main stream prepares, scores and aligns the
   // others
-  int n_gt_long = 0, n_items_long = 0, n_pairs_long = 0, n_rt_long = 0, n_ct_long = 0;
-  int64_t n_sent_long = 0;
+  int n_items_long = 0, n_pairs_long = 0;
   // the first of the long pairs (chain >= TOP_CHAIN_PERCENT of the longest):
   // their contraction tiles, DP items and pairs lead the long pairs' ranges
-  int n_gt_top = 0, n_items_top = 0, n_pairs_top = 0, n_rt_top = 0, n_ct_top = 0;
+  int n_items_top = 0, n_pairs_top = 0;
   int n_tasks_top = 0, n_tasks_long = 0;   // the same ranges in tasks
-  int64_t n_sent_top = 0;
+  // the batch in three parts, the top pairs, the other long pairs, the rest:
+  // where each starts in every order the score path works through (a fourth
+  // entry ends the last), and its SROWS x TN tiles (all, and per column of
+  // them: the row tiles)
+  struct Part {
+    int rt, ct, gt, gs;
+    int64_t sent, tiles, rows;
+  } part[4] = {};
   hipStream_t lane_stream = nullptr;   // the top pairs' DP
   hipEvent_t ev_top = nullptr, ev_top_done = nullptr;
   hipStream_t exp_stream = nullptr;    // the other pairs' source-side expansion
@@ -237,6 +251,43 @@ struct Mark {
 };
 
 bool finite(float x) { return std::isfinite(x); }
+
+// Whether part k's contraction sums each target sentence's words (k_score_s)
+// instead of multiplying dense tiles over the column tile's vocabulary
+// (k_score_c).  Measured (us of expansion + contraction, dense / sparse):
+// - entries of a merged row (mean tokens x dictionary entries), 500 uneven
+//   pairs of median 80, V = 16384: FP32 518 / 205 at 90, 800 / 545 and 1033 /
+//   677 at 180, 1585 / 1589 at 360 (a table of 16 rows no longer fits LDS
+//   and is built for fewer rows at a time); BF16 211 / 174 at 90, 463 / 459
+//   and 520 / 545 at 180;
+// - column tiles per 16 rows, 20 M cells of square pairs, V = 4096, BF16: 691
+//   / 767 at 40 sentences a side, 405 / 412 at 64, 247 / 238 at 128, 180 / 159
+//   at 256 (the table is not used often enough); FP32 gains at every size,
+//   583 / 531 at 64.
+// The target sentences' length does not matter (1000 tokens: BF16 942 / 693).
+bool sparse(const nwm_plan *p, int k) {
+  const int64_t entries = p->src_tokens * p->max_deg;
+  if (!p->param[NWM_PARAM_SCORE_COMPACT]) return false;
+  if (p->tgt_tokens >= ((int64_t)1 << 29)) return false;   // list offsets of a run of sentences stay 32-bit
+  if (p->prec == NWM_BF16) return entries <= 128 * p->n_src && p->part[k].tiles >= 2 * p->part[k].rows;
+  return entries <= 256 * p->n_src;
+}
+
+// The parts [a, b) in runs of one kind: f(first part, end, sparse).  Empty
+// parts go with any kind.
+template <typename F>
+hipError_t each_kind(const nwm_plan *p, int a, int b, F &&f) {
+  hipError_t e = hipSuccess;
+  for (int i = a; i < b && e == hipSuccess;) {
+    while (i < b && p->part[i].tiles == 0) ++i;
+    if (i == b) break;
+    int j = i + 1;
+    while (j < b && (p->part[j].tiles == 0 || sparse(p, j) == sparse(p, i))) ++j;
+    e = f(i, j, sparse(p, i));
+    i = j;
+  }
+  return e;
+}
 
 
 }  // namespace
@@ -320,7 +371,9 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
   const int nch = (p->V + KC - 1) / KC;
   // ---- host metadata ---------------------------------------------------------
   std::vector<int64_t> sfirst(B + 1, 0), tfirst(B + 1, 0), s_off(B + 1, 0), p_off(B + 1, 0), tb_off(B + 1, 0);
-  std::vector<int32_t> rt_pair, rt_row0, rt_rows, ct_pair, ct_col0, ct_cols, gt_rt, gt_ct;
+  std::vector<int32_t> rt_pair, rt_row0, rt_rows, ct_pair, ct_col0, ct_cols;
+  std::vector<int32_t> lane_gt(B + 1, 0), lane_rt(B + 1, 0), lane_ct(B + 1, 0);
+  std::vector<GtMeta> gs_meta;
   for (int b = 0; b < B; ++b) {
     const int64_t nb = p->n[b], mb = p->m[b];
     sfirst[b + 1] = sfirst[b] + nb;
@@ -354,12 +407,28 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
   const size_t n_long_pairs = lane_pairs.size();
   for (int b = 0; b < B; ++b)
     if (!is_long[b]) lane_pairs.push_back(b);
+  // column tiles per workgroup of the sparse contraction: long runs share one
+  // table of merged rows, shorter ones give the chip enough workgroups
+  int64_t wave_tiles = 0;
+  for (int b = 0; b < B; ++b) {
+    const int64_t r = ((int64_t)p->n[b] + SROWS - 1) / SROWS, c = ((int64_t)p->m[b] + TN - 1) / TN;
+    nwm_plan::Part &x = p->part[is_top[b] ? 0 : is_long[b] ? 1 : 2];
+    x.tiles += r * c;
+    x.rows += c > 0 ? r : 0;
+    wave_tiles += r * c;
+  }
+  const int run = (int)std::min<int64_t>(SCOLS, std::max<int64_t>(8, wave_tiles / 1024));
+  int64_t n_gt = 0;
   std::vector<int64_t> sent_ids;
   sent_ids.reserve((size_t)sfirst[B]);
-  p->n_rt_long = p->n_ct_long = p->n_gt_long = 0;
-  p->n_sent_long = 0;
-  p->n_gt_top = p->n_rt_top = p->n_ct_top = 0;
-  p->n_sent_top = 0;
+  auto mark = [&](int k) {   // part k starts here
+    p->part[k].rt = (int)rt_pair.size();
+    p->part[k].ct = (int)ct_pair.size();
+    p->part[k].gt = (int)n_gt;
+    p->part[k].gs = (int)gs_meta.size();
+    p->part[k].sent = (int64_t)sent_ids.size();
+  };
+  mark(1);   // (moved on while there are top pairs)
   for (int pass = 0; pass < 2; ++pass) {
     const size_t q0 = pass == 0 ? 0 : n_long_pairs, q1 = pass == 0 ? n_long_pairs : lane_pairs.size();
     for (size_t q = q0; q < q1; ++q) {
@@ -378,24 +447,30 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
         ct_cols.push_back((int)std::min<int64_t>(TN, mb - c));
       }
       const int nrt = (int)rt_pair.size() - rt0, nct = (int)ct_pair.size() - ct0;
-      for (int ri = 0; ri < nrt; ++ri)
-        for (int ci = 0; ci < nct; ++ci) {
-          gt_rt.push_back(rt0 + ri);
-          gt_ct.push_back(ct0 + ci);
-        }
-      if (is_top[b]) {
-        p->n_gt_top = (int)gt_rt.size();
-        p->n_rt_top = (int)rt_pair.size();
-        p->n_ct_top = (int)ct_pair.size();
-        p->n_sent_top = (int64_t)sent_ids.size();
+      lane_gt[q] = (int32_t)n_gt;
+      lane_rt[q] = rt0;
+      lane_ct[q] = ct0;
+      n_gt += (int64_t)nrt * nct;
+      if (nct > 0) {
+        const int chunks = (nct + run - 1) / run, tiles = (nct + chunks - 1) / chunks;
+        for (int r = 0; r < nb; r += SROWS)
+          for (int c = 0; c < mb; c += tiles * TN) {
+            GtMeta x{};
+            x.pair = b;
+            x.m = (int32_t)mb;
+            x.row0 = r;
+            x.rows = (int)std::min<int64_t>(SROWS, nb - r);
+            x.col0 = c;
+            x.cols = (int)std::min<int64_t>(tiles * TN, mb - c);
+            x.s_first = sfirst[b] + r;
+            x.t_first = tfirst[b] + c;
+            x.s_off = s_off[b];
+            gs_meta.push_back(x);
+          }
       }
+      if (is_top[b]) mark(1);
     }
-    if (pass == 0) {
-      p->n_rt_long = (int)rt_pair.size();
-      p->n_ct_long = (int)ct_pair.size();
-      p->n_gt_long = (int)gt_rt.size();
-      p->n_sent_long = (int64_t)sent_ids.size();
-    }
+    mark(pass == 0 ? 2 : 3);
   }
   p->n_src = sfirst[B];
   p->n_tgt = tfirst[B];
@@ -404,22 +479,9 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
     rt_meta[k] = TileMeta{sfirst[rt_pair[k]] + rt_row0[k], rt_rows[k], rt_pair[k]};
   for (size_t k = 0; k < ct_pair.size(); ++k)
     ct_meta[k] = TileMeta{tfirst[ct_pair[k]] + ct_col0[k], ct_cols[k], ct_pair[k]};
-  std::vector<GtMeta> gt_meta(gt_rt.size());
-  for (size_t g = 0; g < gt_rt.size(); ++g) {
-    GtMeta &x = gt_meta[g];
-    x.rt = gt_rt[g];
-    x.ct = gt_ct[g];
-    x.pair = rt_pair[x.rt];
-    x.m = p->m[x.pair];
-    x.row0 = rt_row0[x.rt];
-    x.rows = rt_rows[x.rt];
-    x.col0 = ct_col0[x.ct];
-    x.cols = ct_cols[x.ct];
-    x.s_first = sfirst[x.pair] + x.row0;
-    x.t_first = tfirst[x.pair] + x.col0;
-    x.s_off = s_off[x.pair];
-    x.pad = 0;
-  }
+  lane_gt[B] = (int32_t)n_gt;
+  lane_rt[B] = (int32_t)rt_pair.size();
+  lane_ct[B] = (int32_t)ct_pair.size();
   // pair order of the DP, the walk and the keep: long pairs first (longest
   // chain first), then the others by cells, largest first
   std::vector<int32_t> order(B);
@@ -545,8 +607,9 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
   size_t i_rn = add(rt_rows.data(), 4 * rt_rows.size());
   size_t i_cp = add(ct_pair.data(), 4 * ct_pair.size()), i_cc = add(ct_col0.data(), 4 * ct_col0.size());
   size_t i_cn = add(ct_cols.data(), 4 * ct_cols.size());
-  size_t i_gr = add(gt_rt.data(), 4 * gt_rt.size()), i_gc = add(gt_ct.data(), 4 * gt_ct.size());
-  size_t i_gm = add(gt_meta.data(), sizeof(GtMeta) * gt_meta.size());
+  size_t i_lp = add(lane_pairs.data(), 4 * lane_pairs.size()), i_lg = add(lane_gt.data(), 4 * lane_gt.size());
+  size_t i_lr = add(lane_rt.data(), 4 * lane_rt.size()), i_lc = add(lane_ct.data(), 4 * lane_ct.size());
+  size_t i_gs = add(gs_meta.data(), sizeof(GtMeta) * gs_meta.size());
   size_t i_rm = add(rt_meta.data(), sizeof(TileMeta) * rt_meta.size());
   size_t i_cm = add(ct_meta.data(), sizeof(TileMeta) * ct_meta.size());
   size_t i_do = add(order.data(), 4 * order.size());
@@ -592,10 +655,13 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
   D.ct_pair = (const int32_t *)at(i_cp);
   D.ct_col0 = (const int32_t *)at(i_cc);
   D.ct_cols = (const int32_t *)at(i_cn);
-  D.n_gt = (int)gt_rt.size();
-  D.gt_rt = (const int32_t *)at(i_gr);
-  D.gt_ct = (const int32_t *)at(i_gc);
-  D.gt_meta = (const GtMeta *)at(i_gm);
+  D.n_gt = (int)n_gt;
+  D.lane_pair = (const int32_t *)at(i_lp);
+  D.lane_gt = (const int32_t *)at(i_lg);
+  D.lane_rt = (const int32_t *)at(i_lr);
+  D.lane_ct = (const int32_t *)at(i_lc);
+  D.n_gs = (int)gs_meta.size();
+  D.gs_meta = (const GtMeta *)at(i_gs);
   D.rt_meta = (const TileMeta *)at(i_rm);
   D.ct_meta = (const TileMeta *)at(i_cm);
   D.dp_order = (const int32_t *)at(i_do);
@@ -630,6 +696,10 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
   W.a_base = carve(8 * (size_t)D.n_rt);
   W.b_base = carve(8 * (size_t)D.n_ct);
   W.p_voc = carve(4 * (size_t)B * (size_t)nch);
+  // (a 16-byte load may read past the last list)
+  W.t_list = carve(2 * ((size_t)p->tgt_tokens + 8 * (size_t)p->n_tgt + 8) + 64);
+  W.t_rec = carve(8 * (size_t)p->n_tgt);
+  W.t_len = carve(4 * (size_t)p->n_tgt);
   W.bwd = carve(16 * ((size_t)B + (size_t)D.n_rt));
   // published rows, + 2 entries (cleared in 16-byte units)
   W.bnd = carve(8 * ((size_t)bnd_off[B] + 2));
@@ -642,7 +712,8 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
   p->sizes.ws_bytes = W.total;
   // ---- kernel attributes (dynamic LDS above the default) ---------------------------
   if (merge_set_attrs(p->max_entries) != hipSuccess || score_set_attrs(nch) != hipSuccess ||
-      build_set_attrs(nch, p->V) != hipSuccess || fill_set_attrs(0) != hipSuccess) {
+      build_set_attrs(nch, p->V) != hipSuccess || sparse_set_attrs() != hipSuccess ||
+      fill_set_attrs(0) != hipSuccess) {
     (void)hipFree(p->dmeta);
     delete p;
     return NWM_EDEVICE;
@@ -718,50 +789,59 @@ static uint32_t *pair_vocab(nwm_plan *p, void *ws) {
                                                           : nullptr;
 }
 
-// The source-side expansion of part of the batch on `st`: merged dictionary
-// rows of source sentences sent_ids[k0, k0 + ns), then (once `tgt_done` has
-// been reached, when given: the column tiles of the same pairs are built) the
-// lists of row tiles [r0, r0 + nr), which hold exactly those sentences.
-static hipError_t expand_src(nwm_plan *p, const nwm_batch *batch, const nwm_dict *dict, void *ws, int64_t k0,
-                             int64_t ns, int r0, int nr, hipEvent_t tgt_done, hipStream_t st) {
+// The source-side expansion of parts [a, b) on `st`: merged dictionary rows,
+// then for the dense contraction (once `tgt_done` has been reached, when
+// given: the column tiles of the same pairs are built) the lists of their row
+// tiles.
+static hipError_t expand_src(nwm_plan *p, const nwm_batch *batch, const nwm_dict *dict, void *ws, int a, int b,
+                             hipEvent_t tgt_done, hipStream_t st) {
   char *w = static_cast<char *>(ws);
   uint2 *merged = (uint2 *)(w + p->ws.a_merged);
   int32_t *cnt = (int32_t *)(w + p->ws.a_cnt);
+  const uint2 *dpk = (const uint2 *)(w + p->ws.d_pack);
   const bool bf16 = p->prec == NWM_BF16;
   // list entries of the dense contraction are LDS byte offsets inside the
   // operand tiles
   const int pitch = bf16 ? PITCH_BF16 : PITCH_F32;
   const int esize = bf16 ? 2 : 4;
-  if (fused_a(p)) {
-    // no dependency on the target side; the wait keeps the contract that the
-    // contraction queued after this on `st` finds both sides built
-    Mark mx(p, K_EXPAND_A, st);
-    hipError_t e = launch_expand_a(p->dev, batch->src_off, batch->src_tok, (const uint2 *)(w + p->ws.d_pack), p->V,
-                                   p->max_entries, (uint2 *)(w + p->ws.a_list), (int32_t *)(w + p->ws.a_choff),
-                                   pitch, esize, p->param[NWM_PARAM_SCORE_COMPACT], (int64_t *)(w + p->ws.a_base),
-                                   r0, nr, st);
-    mx.done();
-    if (e == hipSuccess && tgt_done) e = hipStreamWaitEvent(st, tgt_done, 0);
-    return e;
-  }
-  Mark mk(p, K_MERGE, st);
-  hipError_t e = launch_merge_src(ns, p->dev.sent_ids, k0, batch->src_off, batch->src_tok, dict->row_off, dict->col,
-                                  dict->val, p->V, p->max_deg, p->max_entries, merged, cnt,
-                                  p->param[NWM_PARAM_MERGE_WAVES_PER_CU], st);
-  mk.done();
-  if (e == hipSuccess && tgt_done) e = hipStreamWaitEvent(st, tgt_done, 0);
-  Mark ma(p, K_BUILD_A, st);
-  if (e == hipSuccess)
-    e = launch_build_a(p->dev, batch->src_off, merged, cnt, (uint2 *)(w + p->ws.a_list),
-                       (int32_t *)(w + p->ws.a_choff), pitch, esize, p->param[NWM_PARAM_SCORE_COMPACT],
-                       (int64_t *)(w + p->ws.a_base), pair_vocab(p, ws), r0, nr, st);
-  ma.done();
+  bool waited = tgt_done == nullptr;
+  hipError_t e = each_kind(p, a, b, [&](int i, int j, bool sp) {
+    const int r0 = p->part[i].rt, nr = p->part[j].rt - r0;
+    const int64_t k0 = p->part[i].sent, ns = p->part[j].sent - k0;
+    if (fused_a(p)) {   // needs nothing of the target side
+      Mark mx(p, K_EXPAND_A, st);
+      const hipError_t x =
+          sp ? launch_merge_tiles(p->dev, batch->src_off, batch->src_tok, dpk, p->max_entries, merged, cnt, r0, nr, st)
+             : launch_expand_a(p->dev, batch->src_off, batch->src_tok, dpk, p->V, p->max_entries,
+                               (uint2 *)(w + p->ws.a_list), (int32_t *)(w + p->ws.a_choff), pitch, esize,
+                               p->param[NWM_PARAM_SCORE_COMPACT], (int64_t *)(w + p->ws.a_base), r0, nr, st);
+      mx.done();
+      return x;
+    }
+    Mark mk(p, K_MERGE, st);
+    hipError_t x = launch_merge_src(ns, p->dev.sent_ids, k0, batch->src_off, batch->src_tok, dict->row_off, dict->col,
+                                    dict->val, p->V, p->max_deg, p->max_entries, merged, cnt,
+                                    p->param[NWM_PARAM_MERGE_WAVES_PER_CU], st);
+    mk.done();
+    if (sp) return x;
+    if (x == hipSuccess && !waited) x = hipStreamWaitEvent(st, tgt_done, 0);
+    waited = true;
+    Mark ma(p, K_BUILD_A, st);
+    if (x == hipSuccess)
+      x = launch_build_a(p->dev, batch->src_off, merged, cnt, (uint2 *)(w + p->ws.a_list),
+                         (int32_t *)(w + p->ws.a_choff), pitch, esize, p->param[NWM_PARAM_SCORE_COMPACT],
+                         (int64_t *)(w + p->ws.a_base), pair_vocab(p, ws), r0, nr, st);
+    ma.done();
+    return x;
+  });
+  // the contraction queued after this on `st` finds both sides built
+  if (e == hipSuccess && !waited) e = hipStreamWaitEvent(st, tgt_done, 0);
   return e;
 }
 
-// The lists of column tiles [c0, c0 + nc) on `st`; `first` clears the pair
+// The target lists of parts [a, b) on `st`; `first` clears the pair
 // vocabularies beforehand (once per pass over the batch).
-static hipError_t expand_tgt(nwm_plan *p, const nwm_batch *batch, void *ws, int c0, int nc, bool first,
+static hipError_t expand_tgt(nwm_plan *p, const nwm_batch *batch, void *ws, int a, int b, bool first,
                              hipStream_t st) {
   char *w = static_cast<char *>(ws);
   const bool bf16 = p->prec == NWM_BF16;
@@ -770,10 +850,16 @@ static hipError_t expand_tgt(nwm_plan *p, const nwm_batch *batch, void *ws, int 
   hipError_t e = hipSuccess;
   if (first && voc) e = launch_clear_u32(voc, (int64_t)p->B * p->dev.nch, st);
   if (e == hipSuccess)
-    e = launch_build_b(p->dev, batch->tgt_off, batch->tgt_tok, (uint32_t *)(w + p->ws.b_list),
-                       (int32_t *)(w + p->ws.b_choff), bf16 ? PITCH_BF16 : PITCH_F32, bf16 ? 2 : 4,
-                       p->param[NWM_PARAM_SCORE_COMPACT], (uint2 *)(w + p->ws.b_mt), (int32_t *)(w + p->ws.b_kcn),
-                       (int2 *)(w + p->ws.b_rng), (int64_t *)(w + p->ws.b_base), voc, c0, nc, st);
+    e = each_kind(p, a, b, [&](int i, int j, bool sp) {
+      const int c0 = p->part[i].ct, nc = p->part[j].ct - c0;
+      if (sp)
+        return launch_tgt_lists(p->dev, batch->tgt_off, batch->tgt_tok, (uint16_t *)(w + p->ws.t_list),
+                                (uint2 *)(w + p->ws.t_rec), (float *)(w + p->ws.t_len), c0, nc, st);
+      return launch_build_b(p->dev, batch->tgt_off, batch->tgt_tok, (uint32_t *)(w + p->ws.b_list),
+                            (int32_t *)(w + p->ws.b_choff), bf16 ? PITCH_BF16 : PITCH_F32, bf16 ? 2 : 4,
+                            p->param[NWM_PARAM_SCORE_COMPACT], (uint2 *)(w + p->ws.b_mt), (int32_t *)(w + p->ws.b_kcn),
+                            (int2 *)(w + p->ws.b_rng), (int64_t *)(w + p->ws.b_base), voc, c0, nc, st);
+    });
   mk.done();
   return e;
 }
@@ -796,23 +882,33 @@ static hipError_t expand_lists(nwm_plan *p, const nwm_batch *batch, const nwm_di
   hipError_t e = pack_dict(p, dict, ws, st);
   if (e == hipSuccess) e = hipEventRecord(p->ev_fork, st);
   if (e == hipSuccess) e = hipStreamWaitEvent(p->aux_stream, p->ev_fork, 0);
-  if (e == hipSuccess) e = expand_tgt(p, batch, ws, 0, p->dev.n_ct, true, p->aux_stream);
+  if (e == hipSuccess) e = expand_tgt(p, batch, ws, 0, 3, true, p->aux_stream);
   if (e == hipSuccess) e = hipEventRecord(p->ev_join, p->aux_stream);
-  if (e == hipSuccess) e = expand_src(p, batch, dict, ws, 0, p->n_src, 0, p->dev.n_rt, p->ev_join, st);
+  if (e == hipSuccess) e = expand_src(p, batch, dict, ws, 0, 3, p->ev_join, st);
   return e;
 }
 
+// The contraction of parts [a, b).
 static hipError_t score_tiles(nwm_plan *p, const nwm_batch *batch, nwm_scorer sc, float *S, float *S_raw, void *ws,
-                              int g0, int G, hipStream_t st) {
+                              int a, int b, hipStream_t st) {
   char *w = static_cast<char *>(ws);
   Mark mk(p, K_SCORE, st);
-  hipError_t e = launch_score(p->dev, p->prec == NWM_BF16, batch->src_off, batch->tgt_off, (uint2 *)(w + p->ws.a_list),
-                              (int32_t *)(w + p->ws.a_choff), (uint32_t *)(w + p->ws.b_list),
-                              (int32_t *)(w + p->ws.b_choff), sc, S, S_raw, p->param[NWM_PARAM_SCORE_XCD_MAP],
-                              p->param[NWM_PARAM_SCORE_COMPACT], p->param[NWM_PARAM_SCORE_KGROUP],
-                              (uint2 *)(w + p->ws.b_mt),
-                              (int32_t *)(w + p->ws.b_kcn), (int2 *)(w + p->ws.b_rng), (int64_t *)(w + p->ws.a_base),
-                              (int64_t *)(w + p->ws.b_base), g0, G, st);
+  const hipError_t e = each_kind(p, a, b, [&](int i, int j, bool sp) {
+    if (sp) {
+      int64_t tiles = 0, rows = 0;
+      for (int k = i; k < j; ++k) tiles += p->part[k].tiles, rows += p->part[k].rows;
+      return launch_score_s(p->dev, p->prec == NWM_BF16, p->max_entries, (int)(tiles / std::max<int64_t>(rows, 1)),
+                            batch->src_off, batch->tgt_off, (uint2 *)(w + p->ws.a_merged),
+                            (int32_t *)(w + p->ws.a_cnt), (uint16_t *)(w + p->ws.t_list), (uint2 *)(w + p->ws.t_rec),
+                            (float *)(w + p->ws.t_len), sc, S, S_raw, p->part[i].gs, p->part[j].gs - p->part[i].gs, st);
+    }
+    return launch_score(p->dev, p->prec == NWM_BF16, batch->src_off, batch->tgt_off, (uint2 *)(w + p->ws.a_list),
+                        (int32_t *)(w + p->ws.a_choff), (uint32_t *)(w + p->ws.b_list),
+                        (int32_t *)(w + p->ws.b_choff), sc, S, S_raw, p->param[NWM_PARAM_SCORE_XCD_MAP],
+                        p->param[NWM_PARAM_SCORE_COMPACT], p->param[NWM_PARAM_SCORE_KGROUP], (uint2 *)(w + p->ws.b_mt),
+                        (int32_t *)(w + p->ws.b_kcn), (int2 *)(w + p->ws.b_rng), (int64_t *)(w + p->ws.a_base),
+                        (int64_t *)(w + p->ws.b_base), p->part[i].gt, p->part[j].gt - p->part[i].gt, st);
+  });
   mk.done();
   return e;
 }
@@ -843,7 +939,7 @@ nwm_status nwm_score_pairs(nwm_plan *p, const nwm_batch *batch, const nwm_dict *
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = ensure_streams(p);
   if (e == hipSuccess) e = expand_lists(p, batch, dict, ws, st);
-  if (e == hipSuccess) e = score_tiles(p, batch, sc, S, S_raw, ws, 0, p->dev.n_gt, st);
+  if (e == hipSuccess) e = score_tiles(p, batch, sc, S, S_raw, ws, 0, 3, st);
   return dev_err(e);
 }
 
@@ -1058,9 +1154,7 @@ static nwm_status mine_path(nwm_plan *p, const nwm_batch *batch, const nwm_dict 
   const int stg = p->param[NWM_PARAM_FILL_STAGING];
   const PlanDev &D = p->dev;
   const bool scored = p->sizes.S_elems > 0;
-  const int gl = p->n_gt_long, il = p->n_items_long, ol = p->n_pairs_long;
-  const int rl = p->n_rt_long, cl = p->n_ct_long, rtop = p->n_rt_top, ctop = p->n_ct_top;
-  const int64_t kl = p->n_sent_long, ktop = p->n_sent_top;
+  const int il = p->n_items_long, ol = p->n_pairs_long;
   hipError_t e = ensure_streams(p);
   hipStream_t aux = p->aux_stream, lane = p->lane_stream, xs = p->exp_stream;
   if (e == hipSuccess && scored) e = pack_dict(p, dict, ws, st);
@@ -1071,11 +1165,11 @@ static nwm_status mine_path(nwm_plan *p, const nwm_batch *batch, const nwm_dict 
   if (e == hipSuccess) e = hipStreamWaitEvent(aux, p->ev_fork, 0);
   if (e == hipSuccess) e = hipStreamWaitEvent(xs, p->ev_fork, 0);
   if (scored) {
-    if (e == hipSuccess) e = expand_tgt(p, batch, ws, 0, ctop, true, aux);
+    if (e == hipSuccess) e = expand_tgt(p, batch, ws, 0, 1, true, aux);
     if (e == hipSuccess) e = hipEventRecord(p->ev_b_top, aux);
-    if (e == hipSuccess) e = expand_tgt(p, batch, ws, ctop, cl - ctop, false, aux);
+    if (e == hipSuccess) e = expand_tgt(p, batch, ws, 1, 2, false, aux);
     if (e == hipSuccess) e = hipEventRecord(p->ev_b_long, aux);
-    if (e == hipSuccess) e = expand_tgt(p, batch, ws, cl, D.n_ct - cl, false, aux);
+    if (e == hipSuccess) e = expand_tgt(p, batch, ws, 2, 3, false, aux);
   }
   if (e == hipSuccess) e = hipEventRecord(p->ev_b_rest, aux);
   // the other pairs' source-side expansion on the second side stream, issued
@@ -1085,12 +1179,12 @@ static nwm_status mine_path(nwm_plan *p, const nwm_batch *batch, const nwm_dict 
   // behind it)
   auto rest_src = [&]() {
     if (e == hipSuccess && scored)
-      e = expand_src(p, batch, dict, ws, kl, p->n_src - kl, rl, D.n_rt - rl, p->ev_b_rest, xs);
+      e = expand_src(p, batch, dict, ws, 2, 3, p->ev_b_rest, xs);
     if (e == hipSuccess) e = hipEventRecord(p->ev_a_rest, xs);
   };
-  const int gtop = p->n_gt_top, itop = p->n_items_top, otop = p->n_pairs_top;
+  const int itop = p->n_items_top, otop = p->n_pairs_top;
   const int ttop = p->n_tasks_top, tl = p->n_tasks_long;
-  const bool rest_after_top = ol > 0 && gtop > 0;
+  const bool rest_after_top = ol > 0 && p->part[0].tiles > 0;
   if (!rest_after_top) rest_src();
   if (e == hipSuccess) e = launch_nw_reset(D, gap, score, bnd, p->n_bnd, ctl, st);
   if (ol > 0) {
@@ -1101,13 +1195,13 @@ static nwm_status mine_path(nwm_plan *p, const nwm_batch *batch, const nwm_dict 
     // streams in all, one hardware queue each), while the main stream goes
     // on with the rest
     if (scored) {
-      if (e == hipSuccess) e = expand_src(p, batch, dict, ws, 0, ktop, 0, rtop, p->ev_b_top, st);
-      if (e == hipSuccess) e = score_tiles(p, batch, sc, S, S_raw, ws, 0, gtop, st);
+      if (e == hipSuccess) e = expand_src(p, batch, dict, ws, 0, 1, p->ev_b_top, st);
+      if (e == hipSuccess) e = score_tiles(p, batch, sc, S, S_raw, ws, 0, 1, st);
     }
     if (e == hipSuccess) e = hipEventRecord(p->ev_top, st);
     if (scored) {
-      if (e == hipSuccess) e = expand_src(p, batch, dict, ws, ktop, kl - ktop, rtop, rl - rtop, p->ev_b_long, st);
-      if (e == hipSuccess) e = score_tiles(p, batch, sc, S, S_raw, ws, gtop, gl - gtop, st);
+      if (e == hipSuccess) e = expand_src(p, batch, dict, ws, 1, 2, p->ev_b_long, st);
+      if (e == hipSuccess) e = score_tiles(p, batch, sc, S, S_raw, ws, 1, 2, st);
     }
     if (e == hipSuccess) e = hipEventRecord(p->ev_long, st);
     if (otop > 0) {
@@ -1136,7 +1230,7 @@ static nwm_status mine_path(nwm_plan *p, const nwm_batch *batch, const nwm_dict 
   }
   if (e == hipSuccess) e = hipStreamWaitEvent(st, p->ev_a_rest, 0);
   if (e == hipSuccess) e = hipStreamWaitEvent(st, p->ev_b_rest, 0);
-  if (e == hipSuccess && scored) e = score_tiles(p, batch, sc, S, S_raw, ws, gl, D.n_gt - gl, st);
+  if (e == hipSuccess && scored) e = score_tiles(p, batch, sc, S, S_raw, ws, 2, 3, st);
   if (e == hipSuccess)
     e = launch_nw_fill_items(D, S, gap, score, tbc, bnd, p->n_bnd, ctl, ctl + 1, il, D.n_items - il, tl,
                              D.n_tasks - tl, wpc, spin, hold, stg, st);

@@ -31,6 +31,12 @@ constexpr int CREG_B = 2;
 constexpr int LIST_SLACK_A = 64 * (CREG_A > REG_A ? CREG_A : REG_A);
 constexpr int LIST_SLACK_B = 64 * (CREG_B > REG_B ? CREG_B : REG_B);
 
+// ---- sparse contraction ------------------------------------------------------
+// Source sentences per workgroup tile, and the most column tiles (of TN
+// target sentences) one workgroup walks.
+constexpr int SROWS = 16;
+constexpr int SCOLS = 32;
+
 // ---- dictionary-row merge ---------------------------------------------------
 constexpr int MERGE_SLOTS = 1024;     // bound on tokens x max_deg per source sentence
 constexpr int MAX_V = 32768;          // vocabulary bound (LDS tables of V / 32 words per tile)
@@ -68,7 +74,8 @@ constexpr int DIR_DIAG = 0, DIR_UP = 1, DIR_LEFT = 2;
 // (row) one uint4 = four 32-bit words of 16 steps x 2 bits (first step in the
 // high bits).  ceil((m + 63) / 64) blocks per strip, 1 KiB per block.
 
-// Everything the contraction needs about one tile, in one 64-byte record.
+// Everything a contraction needs about one tile, in one 64-byte record (rt
+// and ct: the dense contraction's row and column tile).
 struct GtMeta {
   int32_t rt, ct, pair, m;
   int32_t row0, rows, col0, cols;
@@ -102,10 +109,14 @@ struct PlanDev {
   const int32_t *rt_pair, *rt_row0, *rt_rows;
   const int32_t *ct_pair, *ct_col0, *ct_cols;
   const TileMeta *rt_meta, *ct_meta;
-  // contraction tiles: (row tile, column tile)
+  // contraction tiles: the pairs in lane order (long pairs first), pair
+  // lane_pair[q]'s row tiles from lane_rt[q], column tiles from lane_ct[q] and
+  // (row tile, column tile) products, row-major, from lane_gt[q]
   int n_gt;
-  const int32_t *gt_rt, *gt_ct;
-  const GtMeta *gt_meta;
+  const int32_t *lane_pair, *lane_gt, *lane_rt, *lane_ct;   // [B + 1]
+  // tiles of the sparse contraction: SROWS source sentences x column tiles
+  int n_gs;
+  const GtMeta *gs_meta;
   // DP order (longest first) and DP work items (pair, strip) in queue order
   const int32_t *dp_order;
   const int64_t *sent_ids;   // [sum n] source sentences, long pairs' first
@@ -132,6 +143,10 @@ struct WsLayout {
   size_t a_base;     // int64 [n_rt] first A-list entry of each row tile
   size_t b_base;     // int64 [n_ct] first B-list entry of each column tile
   size_t p_voc;      // uint32 [B * ceil(V / 32)] target vocabulary of each pair (compacted contraction)
+  // the sparse contraction's target side
+  size_t t_list;     // uint16 word lists (in granules of 8, see k_sparse.hip)
+  size_t t_rec;      // uint2 [sum m] per column tile, most words first: {list, word quads and sentence}
+  size_t t_len;      // float [sum m] tokens of each target sentence
   size_t bwd;        // float [B * 4] per-pair partials + float [n_blocks * 4]
   size_t bnd;        // uint64 (value, epoch) boundary rows between strips
   size_t ctl;        // int32 [2]: DP queue head, error flag

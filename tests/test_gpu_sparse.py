@@ -1,0 +1,92 @@
+"""The sparse contraction (sums of the merged rows' entries over each target
+sentence's words) at the sizes where it can go wrong: list lengths around the
+sorting network, granule and block sizes, partial row tiles, column tiles and
+runs of column tiles, a vocabulary larger than the LDS table, empty sentences,
+repeated words; against the whole-vocabulary contraction bit for bit with FP32
+operands (both add the same FP32 terms in ascending word order, each partial
+sum rounded) and against the FP64 oracle."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+from synth import corpus
+from . import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(n, m, V, s_len, t_len, words=None, seed=0):
+    """Pairs of n x m sentences with the given token counts (cycled over the
+    sentences), words drawn from [0, words)."""
+    rng = np.random.default_rng([21, seed])
+    b = corpus.make_batch(2, sizes=([1] * len(n), [1] * len(n)), V=V)
+    words = V if words is None else words
+    s = np.resize(np.asarray(s_len), int(np.sum(n)))
+    t = np.resize(np.asarray(t_len), int(np.sum(m)))
+    return dataclasses.replace(
+        b, n=np.asarray(n, np.int32), m=np.asarray(m, np.int32),
+        src_off=np.concatenate([[0], np.cumsum(s)]).astype(np.int64),
+        src_tok=rng.integers(0, words, int(s.sum())).astype(np.int32),
+        tgt_off=np.concatenate([[0], np.cumsum(t)]).astype(np.int64),
+        tgt_tok=rng.integers(0, words, int(t.sum())).astype(np.int32),
+        gold_off=np.zeros(len(n) + 1, np.int64), gold=np.zeros((0, 2), np.int32))
+
+
+LENGTHS = [0, 1, 2, 7, 8, 9, 31, 32, 33, 40, 63, 64, 65, 100, 200]
+CASES = {
+    # every list length next to every other, most words present, V not a multiple of 32
+    "lengths": lambda: _batch([17, 33], [131, 260], 1000, [0, 1, 16, 40, 48], LENGTHS),
+    # few words: lists full of repeats
+    "repeats": lambda: _batch([16, 1], [130, 200], 257, [48, 3, 0], LENGTHS, words=40),
+    # the vocabulary of 16 rows exceeds the table: fewer rows at a time
+    "table": lambda: _batch([40], [140], 32768, [48], [20, 45]),
+    # several runs of column tiles, one column in the last
+    "runs": lambda: _batch([15], [4097], 4096, [5, 30], [12, 40, 1]),
+    # one row, two column tiles
+    "row": lambda: _batch([1], [128], 33, [4], [3, 64]),
+}
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_sparse_contraction(case, prec):
+    b = CASES[case]()
+    two = H.run_gpu(b, prec=prec, params={"expand_fused": 0}, timing=True)
+    if prec == 1 and case == "table":   # more entries a row than BF16 sums pay for: mean 48 x 4
+        assert two["launches"]["build_a"] > 0
+    else:
+        assert two["launches"]["merge"] > 0 and two["launches"]["build_a"] == 0   # the sparse route ran
+    one = H.run_gpu(b, prec=prec)
+    dense = H.run_gpu(b, prec=prec, params={"score_compact": 0})
+    np.testing.assert_array_equal(one["S"].view(np.uint32), two["S"].view(np.uint32))
+    np.testing.assert_array_equal(one["S_raw"].view(np.uint32), two["S_raw"].view(np.uint32))
+    ora = oracle.score(b)
+    if prec == 0:
+        np.testing.assert_array_equal(one["S_raw"].view(np.uint32), dense["S_raw"].view(np.uint32))
+        np.testing.assert_array_equal(one["S"].view(np.uint32), dense["S"].view(np.uint32))
+        assert H.s_rel_err(one["S"], ora["S64"]).max() <= 1e-5
+    else:
+        assert np.abs(one["S"].astype(np.float64) - ora["S64"]).max() <= 2e-2
+    quiet = H.run_gpu(b, prec=prec, want_raw=False)   # the variant that writes no S_raw
+    np.testing.assert_array_equal(quiet["S"].view(np.uint32), one["S"].view(np.uint32))
+
+
+def test_parts_of_one_batch_by_different_contractions():
+    # a long pair (summed) among short ones (BF16 operands: dense tiles): one
+    # workspace holds both kinds of lists; S equals the whole-vocabulary run's
+    # within the BF16 bar, and a graph replay writes the same bits
+    import torch
+    import paper_1512_01641_amd as nw
+    b = _batch([700] + [20, 40, 64] * 5, [900] + [25, 64, 33] * 5, 2048, [5, 22, 40], [5, 22, 40])
+    ora = oracle.score(b)
+    one = H.run_gpu(b, prec=1, params={"expand_fused": 0}, timing=True)
+    assert one["launches"]["build_a"] > 0
+    assert np.abs(one["S"].astype(np.float64) - ora["S64"]).max() <= 2e-2
+    mn = nw.Miner(nw.Context(0), nw.DeviceBatch.from_host(b), nw.DeviceDict.from_host(b), nw.NWM_BF16)
+    for _ in range(3):
+        mn.S.zero_()
+        mn.mine(b.scorer, b.gap, b.threshold, graph=True)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(mn.S[:mn.plan.S_elems].cpu().numpy().view(np.uint32), one["S"].view(np.uint32))
