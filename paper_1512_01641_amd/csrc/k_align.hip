@@ -2,43 +2,50 @@
 // document pair (Sec. 5.1, Figs. 1-2, eq. (1)) and the threshold filter
 // (Sec. 4).
 //
-// k_nw_fill   persistent work-queue kernel, four waves per workgroup.  A
-//             strip is 64 rows of one pair's DP lattice; a task is four
-//             strips, one per wave: four consecutive strips of one pair (fewer
-//             at its end) or strips of one-strip pairs, in queue order
-//             (longest chains first).  Lane r owns row r of the strip and at
-//             step t computes column j = t - r + 1, so each step is one
+// k_nw_fill   persistent work-queue kernel, four strip waves and two row waves
+//             per workgroup.  A strip is 64 rows of one pair's DP lattice; a
+//             task is four strips, one per strip wave: consecutive strips of
+//             one pair (fewer at its end) or strips of several pairs, in queue
+//             order (longest chains first).  Lane r owns row r of the strip
+//             and at step t computes column j = t - r + 1, so each step is one
 //             anti-diagonal of the strip, computed by all lanes at once
 //             (Sec. 5.1, Fig. 2).  Per cell, in FP32 without contraction:
 //                up = H[i-1][j] + g, left = H[i][j-1] + g, diag = H[i-1][j-1] + S
 //                first maximum of (up, left, diag) with '>' (UP > LEFT > DIAG)
 //             The value from the row above moves one lane per step by a DPP
-//             wave shift.  The strip's top boundary (the previous strip's last
-//             row) enters lane 0 through a 64-lane register window shifted one
-//             lane per step; the strip's own last row leaves through a second
-//             shifted window every 16 steps.  Between the strips of one task
-//             the row passes through an LDS ring with a count of columns put
-//             and taken (about 80 steps behind); the last strip of a task
-//             publishes it as tagged 64-bit agent-coherent stores (no
-//             counters, no cache flushes) for the first strip of the next
-//             task, which runs on another workgroup about 150 steps behind
-//             (bounded re-read).  A wave that gives up waiting (its poll
-//             limit) sets the error flag, marks its own last row failed (tag
-//             TAG_FAIL in memory, count -1 in LDS, so the strips below give up
-//             at once instead of waiting out their own limits) and, in a
-//             pair's last strip, writes NaN as the score; the walk then leaves
-//             the pair empty.  S is staged through an LDS ring of two 64-step
-//             groups per wave (16 KiB each: 64 rows x 256 bytes), filled a
-//             group ahead by 16-byte LDS-direct buffer loads (no register
-//             holds S); each lane reads the four steps of one 16-byte chunk
-//             of its own row with one ds_read_b128, placed so that the lanes
-//             of a quarter-wave hit different banks.  Each lane packs its
-//             2-bit directions, 16 steps per word, and every 64 steps the
-//             wave writes one coalesced 1 KiB block.  H never reaches HBM.
+//             wave shift.  The row above the strip comes from an LDS row ring,
+//             16 columns at a time, the same values in every lane (lane 0 uses
+//             them); the strip's own last row leaves lane 63 into the next row
+//             ring every 16 steps, with a count of columns put and taken.  So a
+//             strip trails the one above it by 80 steps.  What does not come
+//             from or go to a strip of the same task is the row waves' work:
+//             one fills row rings with a pair's first row (j g) or with a row
+//             another workgroup publishes, the other publishes the task's last
+//             row, as tagged 64-bit agent-coherent stores (no counters, no
+//             cache flushes).  A wave that gives up waiting (its poll limit)
+//             sets the error flag, marks its own last row failed (tag TAG_FAIL
+//             in memory, count -1 in LDS, so the strips below give up at once
+//             instead of waiting out their own limits) and, in a pair's last
+//             strip, writes NaN as the score; the walk then leaves the pair
+//             empty.  S is staged through an LDS ring of two 64-step groups
+//             per strip (16 KiB each: 64 rows x 256 bytes), filled a group
+//             ahead by 16-byte LDS-direct buffer loads (no register holds S);
+//             each lane reads the four steps of one 16-byte piece of its own
+//             row with one ds_read_b128, placed so that the lanes of a
+//             quarter-wave hit different banks.  Each lane collects its
+//             directions in two bit planes, and every 64 steps the wave writes
+//             one coalesced 1 KiB block.  H never reaches HBM.
+//             What bounds it is a strip wave's issue: one wave per SIMD, about
+//             225 instructions per 16 steps (150 of them the cells') at about
+//             4.7 clocks.  Measured: one strip of 64 x 20000 566 us (774 with
+//             the row above shifted through a register window, directions
+//             packed by selects and S waits spread over the chunk), 256 x
+//             20000 674 us (981), 2000 x 2000 180 us (260), 64 pairs of 5000 x
+//             5000 1.63 ms (1.66: S from HBM, 3.9 TB/s).
 // k_nw_reset  clears the published-row region and the queue; scores of
 //             empty pairs.
 // k_nw_walk   traceback from (n, m): one wave per pair holds one 64-step
-//             block of its strip (one 16-byte word per lane) and reads it with
+//             block of its strip (both planes of a row per lane) and reads it with
 //             uniform-index readlane, with the previous block prefetched.
 //             Aligned pairs are written right-aligned (ascending) into the
 //             path area.
@@ -47,12 +54,14 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace nwm {
 
-constexpr int GROUP = 64;             // steps per S staging group (four chunks of 16)
-constexpr int GROUP_FLOATS = 64 * GROUP;   // ring floats per group (64 rows x 256 bytes)
-constexpr int RING_GROUPS = 2;        // groups in the S ring: one in flight while one is read
+constexpr int CHUNK = 16;             // steps per chunk
+constexpr int GROUP = 64;             // steps per S staging group (four chunks)
+constexpr int GROUP_BYTES = 64 * GROUP * 4;   // LDS bytes per group (64 rows x 256 bytes)
+constexpr int RING_GROUPS = 2;        // groups in a strip's S ring: one in flight while one is read
 constexpr int SPIN_LIMIT = 1 << 22;   // default polls before a wave gives up (error flag)
 constexpr uint32_t TAG_FAIL = 2u;     // tag of a boundary value whose producer gave up
 
@@ -63,6 +72,11 @@ static __device__ __forceinline__ float dpp_shr1(float old, float src) {
 static __device__ __forceinline__ float dpp_shl1(float old, float src) {
   // lane l <- src of lane l+1; lane 63 keeps `old`
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(src), 0x130, 0xF, 0xF, false));
+}
+
+static __device__ __forceinline__ float dpp_next(float src) {
+  // lane l <- src of lane l+1 (lane 63: 0)
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(src), 0x130, 0xF, 0xF, true));
 }
 
 static __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -88,30 +102,29 @@ static __device__ __forceinline__ T *uniform_ptr(T *p) {
 // from memory into one ring slot of 16 KiB by 16 LDS-direct 16-byte buffer
 // loads; load k brings rows 4k .. 4k + 3 into the slot's k-th KiB.  Within
 // that KiB, lane l of the load writes bytes 16 l .. 16 l + 15, so the lane
-// that loads 16-byte chunk c (steps 4c .. 4c + 3) of row 4k + rho is the
+// that loads 16-byte piece c (steps 4c .. 4c + 3) of row 4k + rho is the
 // one that puts it where the reader wants it:
 //    lane = 16 rho + ((c + 4 (k & 3) + rho) & 15).
-// Every lane of the reader (lane = row) then reads chunk c of its own row
+// Every lane of the reader (lane = row) then reads piece c of its own row
 // with one ds_read_b128, and the 16 lanes of each quarter-wave (rows
 // 16p + j) fall on 16 different 16-byte bank groups ((c + j) & 15).  The 16
-// lanes of a load that share rho read one row's 256 contiguous bytes.  No
-// register holds S.
+// lanes of a load that share rho read one row's 256 contiguous bytes (rows
+// start at any multiple of 4 bytes: shorter pieces of a row, 64 bytes per 16
+// steps, touch twice the cache lines; a batch of 64 pairs of 5000 x 5000
+// took 1.88 ms with them).  No register holds S in flight.
 //
 // Lane l of load k reads strip bytes 4 (r (m - 1) + GROUP q) + 16 c for its
-// row r = 4k + rho and chunk c: base_{k & 3} + (k >> 2) 64 (m - 1) + 256 q,
+// row r = 4k + rho and piece c: base_{k & 3} + (k >> 2) 64 (m - 1) + 256 q,
 // with the group offset in the VGPR offset so that the range check covers it.
 // A cell outside the strip's m columns (the first steps of a row, the steps
 // after its last column) reads another cell of the strip, or 0 past the
-// strip's end through the buffer range check: a value that only the masked
-// steps see, and those leave H unchanged there.  Rows at or beyond `rows`
-// (the last strip of a pair) lie past the end.  Groups past the strip's
-// last step are loaded from an offset past the range (no memory access), so
-// every group issues the same 16 loads.
+// strip's end through the buffer range check: a value that no cell of the
+// lattice sees.  Rows at or beyond `rows` (the last strip of a pair) lie past
+// the end.
 struct StripSrc {
   __amdgpu_buffer_rsrc_t rs;
-  uint32_t base[4];        // bytes, this lane's (row, chunk) in loads 0..3
+  uint32_t base[4];        // bytes, this lane's (row, piece) in loads 0..3
   uint32_t step;           // bytes from load k to load k + 4: 64 (m - 1)
-  int n_groups;            // groups holding steps of the strip
 };
 
 typedef __attribute__((address_space(3))) void lds_void;
@@ -121,8 +134,7 @@ constexpr int CPOL_SC1 = 16;          // cache-policy bit of an agent-coherent a
 constexpr int PUB_NONE = 0x40000000;  // buffer offset past any boundary row: the store is dropped
 
 // The strip's last row: one tagged 64-bit agent-coherent store per lane into
-// the boundary row `rs` (slot j at byte 8 j).  Every lane issues the store, so
-// each chunk issues the same memory operations; a lane with nothing to
+// the boundary row `rs` (slot j at byte 8 j).  A lane with nothing to
 // publish stores at PUB_NONE, past the buffer's range, and the range check
 // drops it without a memory access.
 static __device__ __forceinline__ void publish(__amdgpu_buffer_rsrc_t rs, bool pub, int j, uint64_t v) {
@@ -130,10 +142,8 @@ static __device__ __forceinline__ void publish(__amdgpu_buffer_rsrc_t rs, bool p
   __builtin_amdgcn_raw_buffer_store_b64(d, rs, pub ? 8 * j : PUB_NONE, 0, CPOL_SC1);
 }
 
-constexpr uint32_t S_NONE = 0x40000000u;   // buffer offset past any strip (S stays below 1 GiB per strip)
-
 // The lane's byte base for load j < 4 (see StripSrc): row rho of the load
-// and chunk c, inverting lane = 16 rho + ((c + 4 j + rho) & 15).
+// and piece c, inverting lane = 16 rho + ((c + 4 j + rho) & 15).
 static __device__ __forceinline__ uint32_t s_lane_base(int lane, int j, int m) {
   const int rho = lane >> 4;
   const int c = ((lane & 15) - 4 * j - rho) & 15;
@@ -141,112 +151,212 @@ static __device__ __forceinline__ uint32_t s_lane_base(int lane, int j, int m) {
 }
 
 #define NWM_S_LOAD(A)                               \
-  "buffer_load_dwordx4 " A ", %9, 0 offen lds\n\t"  \
+  "buffer_load_dwordx4 " A ", %8, 0 offen lds\n\t"  \
   "s_add_u32 m0, m0, 1024\n\t"                      \
-  "v_add_u32 " A ", %10, " A "\n\t"
-#define NWM_S_LOAD4 NWM_S_LOAD("%1") NWM_S_LOAD("%2") NWM_S_LOAD("%3") NWM_S_LOAD("%4")
+  "v_add_u32 " A ", %9, " A "\n\t"
+#define NWM_S_LOAD4 NWM_S_LOAD("%0") NWM_S_LOAD("%1") NWM_S_LOAD("%2") NWM_S_LOAD("%3")
 
-// The 16 loads of group q into ring slot `slot`, in one asm statement so that
-// the compiler neither reorders them with other memory accesses nor adds
-// waits for them: every read of the ring waits for them with an explicit
-// vmcnt (below).  M0 (the LDS address of a load) is saved, stepped by 1 KiB
-// per load and restored; a VALU instruction separates each M0 write from the
+// The 16 loads of the group at byte offset goff = 256 q into the ring slot at
+// `slot`, in one asm statement so that the compiler neither reorders them with
+// other memory accesses nor adds waits for them: every read of the ring waits
+// for them with an explicit vmcnt (below).  M0 (the LDS address of a load)
+// steps by 1 KiB per load; a VALU instruction separates each M0 write from the
 // load that uses it.
-static __device__ __forceinline__ void load_group(float *ring, const StripSrc &src, int q, int slot) {
-  const uint32_t la = (uint32_t)uniform((int)(uint32_t)(uintptr_t)(lds_void *)(ring + slot * GROUP_FLOATS));
-  const uint32_t goff = (uint32_t)uniform(q < src.n_groups ? (int)(GROUP * 4 * q) : (int)S_NONE);
-  uint32_t save, a0, a1, a2, a3;
+static __device__ __forceinline__ void load_group(uint32_t slot, const StripSrc &src, uint32_t goff) {
+  uint32_t a0, a1, a2, a3;
   asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %5\n\t"
-      "v_add_u32 %1, %8, %6\n\t"
-      "v_add_u32 %2, %8, %7\n\t"
-      "v_add_u32 %3, %8, %11\n\t"
-      "v_add_u32 %4, %8, %12\n\t"
+      "s_mov_b32 m0, %4\n\t"
+      "v_add_u32 %0, %7, %5\n\t"
+      "v_add_u32 %1, %7, %6\n\t"
+      "v_add_u32 %2, %7, %10\n\t"
+      "v_add_u32 %3, %7, %11\n\t"
       NWM_S_LOAD4 NWM_S_LOAD4 NWM_S_LOAD4 NWM_S_LOAD4
-      "s_mov_b32 m0, %0"
-      : "=&s"(save), "=&v"(a0), "=&v"(a1), "=&v"(a2), "=&v"(a3)
-      : "s"(la), "v"(src.base[0]), "v"(src.base[1]), "s"(goff), "s"(src.rs), "s"(src.step), "v"(src.base[2]),
+      : "=&v"(a0), "=&v"(a1), "=&v"(a2), "=&v"(a3)
+      : "s"(slot), "v"(src.base[0]), "v"(src.base[1]), "s"(goff), "s"(src.rs), "s"(src.step), "v"(src.base[2]),
         "v"(src.base[3])
-      : "memory", "scc");
+      : "memory", "scc", "m0");
 }
 #undef NWM_S_LOAD4
 #undef NWM_S_LOAD
 
-// One 16-byte agent-coherent (sc1) LDS-direct load per active lane: lane l
-// writes bytes 16 l .. 16 l + 15 of buf.  Written as asm for the same reason
-// as the S loads: the compiler's own tracking of an LDS-direct load makes
-// every later LDS read (the ring included) wait for all loads in flight,
-// which would cancel the two-group prefetch.  Its readers wait with an
-// explicit vmcnt.  One wait state separates the M0 write from the load.
-static __device__ __forceinline__ void load_window_lds(uint64_t *buf, const uint64_t *src) {
-  const uint32_t la = (uint32_t)uniform((int)(uint32_t)(uintptr_t)(lds_void *)buf);
-  uint32_t save;
+struct StripState {
+  float H, diag, pw, col;
+};
+
+// Directions, one bit per step and plane, first step in the high bits: into U
+// goes 1 where the cell's maximum is the value from above, into L where it is
+// the value from the left (UP wins where both are, DIAG is neither).
+template <bool MAX3>
+static __device__ __forceinline__ float cell(float up, float left, float dg, uint32_t &U, uint32_t &L) {
+  if constexpr (MAX3) {
+    const float best = __builtin_fmaxf(__builtin_fmaxf(up, left), dg);
+    U = (U << 1) | (up == best ? 1u : 0u);
+    L = (L << 1) | (left == best ? 1u : 0u);
+    return best;
+  } else {
+    const bool c1 = left > up;
+    const float b1 = c1 ? left : up;
+    const bool c2 = dg > b1;
+    U = (U << 1) | (!c1 && !c2 ? 1u : 0u);
+    L = (L << 1) | (c1 && !c2 ? 1u : 0u);
+    return c2 ? dg : b1;
+  }
+}
+
+// Eight steps with a gap of -0 (see run8_chain).  In the first 64 of a strip (EARLY: their first, a multiple of
+// 8; else -1) H is updated only in the lanes 0 .. t whose first column has come
+// at step t, so a lane keeps H[i][0] until then.  A lane that is past its last
+// column goes on with values no lattice cell sees: a lane's cell of column j
+// uses the lane above at columns j - 1 and j only, and what leaves the strip
+// (its last row, the score) is taken at the step of its column.  row: the row
+// above the strip at the columns of lane 0; hs receives H after every step.
+template <int EARLY>
+static __device__ __forceinline__ void run8(StripState &st, const float4 *sv, const float4 *row, float g, uint32_t &U,
+                                            uint32_t &L, float *hs) {
+  float H = st.H, diag = st.diag;
+  uint64_t begun = EARLY >= 0 ? (2ull << (EARLY & 63)) - 1ull : 0ull;   // lanes at column 1 or past it
+  asm volatile("" : "+s"(begun));   // (constants here would be kept in scalar registers over the whole kernel)
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    const float4 v4 = sv[u >> 2], b4 = row[u >> 2];
+    const float s = (u & 3) == 0 ? v4.x : (u & 3) == 1 ? v4.y : (u & 3) == 2 ? v4.z : v4.w;
+    const float above = (u & 3) == 0 ? b4.x : (u & 3) == 1 ? b4.y : (u & 3) == 2 ? b4.z : b4.w;
+    const float x = dpp_shr1(above, H);   // H[i-1][j]: lane r-1, or the row above the strip for lane 0
+    const float best = cell<false>(x + g, H + g, diag + s, U, L);
+    if constexpr (EARLY >= 0) {
+      H = __builtin_amdgcn_inverse_ballot_w64(begun) ? best : H;
+      begun = (begun << 1) | 1ull;
+    } else {
+      H = best;
+    }
+    diag = x;
+    hs[u] = H;
+  }
+  st.H = H;
+  st.diag = diag;
+}
+
+// The same eight steps (gap not -0) as one block, in the order a lone wave
+// needs.  A chain of strips runs one wave per SIMD, where every vector
+// instruction costs about 4.7 clocks whatever it is: nine per step (a lane
+// shift, three adds, one max3, and compare + add-with-carry per direction
+// plane; two-bit codes packed by selects took 16).  The chain of a step (lane
+// shift, add, max3) has other instructions behind each of its own, which cover
+// their latency and the two wait states that a lane shift needs after the
+// write of its source and an add-with-carry after the write of its carry; the
+// directions of a step are taken in the steps after it.  Left to itself the
+// compiler moves the directions of all steps behind the chain, 50 clocks a
+// step against 42.
+//
+// The new H is max(up, left, diag) in one instruction: the first maximum with
+// '>' bit for bit whenever no operand is NaN or -0.  A finite S and a gap that
+// is not -0 never produce either (H starts at +0 or i*gap != 0, and a sum is
+// -0 only when both terms are); a gap of -0 takes the compare chain.
+#define NWM_CMP(a, H) "v_cmp_eq_f32_e32 vcc, %[" a "], " H "\n\t"
+#define NWM_ADDC(P) "v_addc_co_u32_e32 %[" P "], vcc, %[" P "], %[" P "], vcc\n\t"
+// step k from H, x of the step before (Hp, Xp), temporaries u and l number u;
+// A: the step before that one's L; B, C, D: the step before's
+#define NWM_STEP(k, Hp, Xp, u, A, B, C, D)                                     \
+  "v_add_f32 %[h" k "], " Xp ", %[s" k "]\n\t" A B                             \
+  "v_mov_b32_dpp %[b" k "], " Hp " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t"  \
+  "v_add_f32 %[l" u "], %[g], " Hp "\n\t"                                      \
+  "v_add_f32 %[u" u "], %[g], %[b" k "]\n\t" C D                               \
+  "v_max3_f32 %[h" k "], %[u" u "], %[l" u "], %[h" k "]\n\t"
+#define NWM_FIRST(k, Hp, Xp, u) NWM_STEP(k, Hp, Xp, u, "s_nop 0\n\t", "", "", "")
+#define NWM_NEXT(k, p, u, v, A)                                                                              \
+  NWM_STEP(k, "%[h" p "]", "%[b" p "]", u, A, NWM_CMP("u" v, "%[h" p "]"), NWM_ADDC("U"),                    \
+           NWM_CMP("l" v, "%[h" p "]"))
+#define NWM_LAST                                                                           \
+  NWM_ADDC("L") NWM_CMP("u1", "%[h7]") "v_cmp_eq_f32_e64 %[m], %[l1], %[h7]\n\ts_nop 0\n\t" \
+  NWM_ADDC("U") "v_addc_co_u32_e64 %[L], %[m], %[L], %[L], %[m]"
+// lanes past lane t keep H
+#define NWM_KEEP(k, Hp, T) "s_bfm_b64 %[m], " T "+%[t], 0\n\tv_cndmask_b32_e64 %[h" k "], " Hp ", %[h" k "], %[m]\n\t"
+template <int EARLY>
+static __device__ __forceinline__ void run8_chain(StripState &st, const float4 *sv, const float4 *row, float g,
+                                                  uint32_t &U, uint32_t &L, float *hs) {
+  float x[8] = {row[0].x, row[0].y, row[0].z, row[0].w, row[1].x, row[1].y, row[1].z, row[1].w};
+  float u0, u1, l0, l1;
+  uint64_t m;
+#define NWM_OPERANDS                                                                                                  \
+  : [h0] "=&v"(hs[0]), [h1] "=&v"(hs[1]), [h2] "=&v"(hs[2]), [h3] "=&v"(hs[3]), [h4] "=&v"(hs[4]), [h5] "=&v"(hs[5]), \
+    [h6] "=&v"(hs[6]), [h7] "=&v"(hs[7]), [b0] "+v"(x[0]), [b1] "+v"(x[1]), [b2] "+v"(x[2]), [b3] "+v"(x[3]),          \
+    [b4] "+v"(x[4]), [b5] "+v"(x[5]), [b6] "+v"(x[6]), [b7] "+v"(x[7]), [U] "+v"(U), [L] "+v"(L), [u0] "=&v"(u0),      \
+    [u1] "=&v"(u1), [l0] "=&v"(l0), [l1] "=&v"(l1), [m] "=&s"(m)                                                      \
+  : [s0] "v"(sv[0].x), [s1] "v"(sv[0].y), [s2] "v"(sv[0].z), [s3] "v"(sv[0].w), [s4] "v"(sv[1].x), [s5] "v"(sv[1].y), \
+    [s6] "v"(sv[1].z), [s7] "v"(sv[1].w), [H] "v"(st.H), [X] "v"(st.diag), [g] "s"(g), [t] "n"(EARLY)                 \
+  : "vcc"
+  if constexpr (EARLY < 0) {
+    asm volatile(NWM_FIRST("0", "%[H]", "%[X]", "0")
+                 NWM_NEXT("1", "0", "1", "0", "") NWM_NEXT("2", "1", "0", "1", NWM_ADDC("L"))
+                 NWM_NEXT("3", "2", "1", "0", NWM_ADDC("L")) NWM_NEXT("4", "3", "0", "1", NWM_ADDC("L"))
+                 NWM_NEXT("5", "4", "1", "0", NWM_ADDC("L")) NWM_NEXT("6", "5", "0", "1", NWM_ADDC("L"))
+                 NWM_NEXT("7", "6", "1", "0", NWM_ADDC("L")) NWM_LAST NWM_OPERANDS);
+  } else {
+    asm volatile(NWM_FIRST("0", "%[H]", "%[X]", "0") NWM_KEEP("0", "%[H]", "1")
+                 NWM_NEXT("1", "0", "1", "0", "") NWM_KEEP("1", "%[h0]", "2")
+                 NWM_NEXT("2", "1", "0", "1", NWM_ADDC("L")) NWM_KEEP("2", "%[h1]", "3")
+                 NWM_NEXT("3", "2", "1", "0", NWM_ADDC("L")) NWM_KEEP("3", "%[h2]", "4")
+                 NWM_NEXT("4", "3", "0", "1", NWM_ADDC("L")) NWM_KEEP("4", "%[h3]", "5")
+                 NWM_NEXT("5", "4", "1", "0", NWM_ADDC("L")) NWM_KEEP("5", "%[h4]", "6")
+                 NWM_NEXT("6", "5", "0", "1", NWM_ADDC("L")) NWM_KEEP("6", "%[h5]", "7")
+                 NWM_NEXT("7", "6", "1", "0", NWM_ADDC("L"))
+                 ".if %[t]+8 < 64\n\t" NWM_KEEP("7", "%[h6]", "8") ".endif\n\t" "s_nop 0\n\t" NWM_LAST NWM_OPERANDS);
+  }
+#undef NWM_OPERANDS
+  st.H = hs[7];
+  st.diag = x[7];
+}
+#undef NWM_KEEP
+#undef NWM_LAST
+#undef NWM_NEXT
+#undef NWM_FIRST
+#undef NWM_STEP
+#undef NWM_ADDC
+#undef NWM_CMP
+
+typedef float f4v __attribute__((ext_vector_type(4)));
+
+// Lane 63's 16 columns (the carry, then H after the chunk's first 15 steps) to
+// LDS bytes `to` + OFFSET, then the count of columns `col` to `count`.
+// Written in asm: the one lane is picked and all are back in two instructions
+// (every lane is active here).
+template <int OFFSET>
+static __device__ __forceinline__ void put_row(uint32_t to, float carry, const float (&hs)[CHUNK], uint32_t count,
+                                               int col) {
+  const f4v h0 = {carry, hs[0], hs[1], hs[2]}, h1 = {hs[3], hs[4], hs[5], hs[6]}, h2 = {hs[7], hs[8], hs[9], hs[10]},
+            h3 = {hs[11], hs[12], hs[13], hs[14]};
   asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %1\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %2, off sc1\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(save)
-      : "s"(la), "v"(src)
+      "s_brev_b64 exec, 1\n\t"
+      "ds_write_b128 %0, %1 offset:%7\n\t"
+      "ds_write_b128 %0, %2 offset:%8\n\t"
+      "ds_write_b128 %0, %3 offset:%9\n\t"
+      "ds_write_b128 %0, %4 offset:%10\n\t"
+      "ds_write_b32 %5, %6\n\t"
+      "s_mov_b64 exec, -1"
+      :
+      : "v"(to), "v"(h0), "v"(h1), "v"(h2), "v"(h3), "v"(count), "v"(col), "n"(OFFSET), "n"(OFFSET + 16),
+        "n"(OFFSET + 32), "n"(OFFSET + 48)
       : "memory");
 }
 
-struct StripState {
-  float H, diag, pw, col;
-  uint32_t bits;
-};
-
-// 16 steps starting at t0 (a multiple of 16).  MASKED chunks (the first 64
-// steps and the steps past column m) update H only where 1 <= j <= m, so a
-// lane keeps H[i][0] until its column starts and keeps H[i][m] after it ends;
-// in between every lane is active.  Every step also shifts the last-row
-// collector (lane 63 enters), used by strips that have a successor.
-//
-// MAX3: the new H is max(up, left, diag) in one instruction, and the
-// direction (the first of up, left, diag equal to it) is found off the
-// dependency chain from one step to the next.  This is the first maximum
-// with '>' bit for bit whenever no operand is NaN or -0: a finite S and a gap
-// that is not -0 never produce either (H starts at +0 or i*gap != 0, and a
-// sum is -0 only when both terms are).  A gap of -0 takes the compare chain.
+// 16 steps starting at t0 (a multiple of 16) for the fill that stages S in
+// registers.  MASKED chunks (the first 64 steps and the steps past column m)
+// update H only where 1 <= j <= m, so a lane keeps H[i][0] until its column
+// starts and keeps H[i][m] after it ends; in between every lane is active.
+// Every step shifts the last-row collector st.col (lane 63 enters).
 template <bool MASKED, bool MAX3>
 static __device__ __forceinline__ void run16v(StripState &st, const float4 (&sv)[4], int t0, int m, float g,
-                                              int lane) {
+                                              int lane, uint32_t &U, uint32_t &L) {
   float H = st.H, diag = st.diag, pw = st.pw, col = st.col;
-  uint32_t bits = 0;
   int d = t0 - lane;   // column - 1 of this lane at the current step
-  // MAX3: the direction of a step is packed during the next one
-  float up_p = 0.0f, left_p = 0.0f, best_p = 0.0f;
-  auto code3 = [](float up, float left, float best) -> uint32_t {
-    return up == best ? (uint32_t)DIR_UP : (left == best ? (uint32_t)DIR_LEFT : (uint32_t)DIR_DIAG);
-  };
 #pragma unroll
   for (int u = 0; u < 16; ++u) {
     const float4 v4 = sv[u >> 2];
     const float s = (u & 3) == 0 ? v4.x : (u & 3) == 1 ? v4.y : (u & 3) == 2 ? v4.z : v4.w;
+    const float next = dpp_next(pw);
     const float x = dpp_shr1(pw, H);   // H[i-1][j]: lane r-1, or the boundary row for lane 0
-    const float up = x + g;
-    const float left = H + g;
-    const float dg = diag + s;
-    float best;
-    if (MAX3) {
-      best = __builtin_fmaxf(__builtin_fmaxf(up, left), dg);
-      if (u > 0) {
-        bits = (bits << 2) | code3(up_p, left_p, best_p);
-        asm volatile("" : "+v"(bits));
-      }
-      up_p = up;
-      left_p = left;
-      best_p = best;
-    } else {
-      const bool c1 = left > up;
-      const float b1 = c1 ? left : up;
-      const bool c2 = dg > b1;
-      best = c2 ? dg : b1;
-      bits = (bits << 2) | (c2 ? (uint32_t)DIR_DIAG : (c1 ? (uint32_t)DIR_LEFT : (uint32_t)DIR_UP));
-      asm volatile("" : "+v"(bits));   // pack now: do not keep 16 steps of compare masks alive
-    }
+    pw = next;
+    const float best = cell<MAX3>(x + g, H + g, diag + s, U, L);
     if (MASKED) {
       H = ((unsigned)d < (unsigned)m) ? best : H;
       ++d;
@@ -254,33 +364,12 @@ static __device__ __forceinline__ void run16v(StripState &st, const float4 (&sv)
       H = best;
     }
     diag = x;
-    pw = dpp_shl1(pw, pw);
     col = dpp_shl1(H, col);
-    if (!MAX3) __builtin_amdgcn_sched_barrier(0);   // one step at a time
   }
-  if (MAX3) bits = (bits << 2) | code3(up_p, left_p, best_p);
   st.H = H;
   st.diag = diag;
   st.pw = pw;
   st.col = col;
-  st.bits = bits;
-}
-
-// The float offset, within a ring slot, of chunk c (steps 4c .. 4c + 3) of
-// row `lane` (see StripSrc).
-static __device__ __forceinline__ uint32_t chunk_off(int lane, int c) {
-  return (uint32_t)(256 * (lane >> 2) + 4 * (16 * (lane & 3) + ((c + 4 * ((lane >> 2) & 3) + (lane & 3)) & 15)));
-}
-
-// The 16 S values of lane `lane` for the steps [t0, t0 + 16) from the ring
-// slot `grp`; `off` holds the lane's offsets of the four chunks.
-template <bool MASKED, bool MAX3>
-static __device__ __forceinline__ void run16(StripState &st, const float *grp, const uint32_t (&off)[4], int t0,
-                                             int m, float g, int lane) {
-  float4 sv[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) sv[q] = *reinterpret_cast<const float4 *>(grp + off[q]);
-  run16v<MASKED, MAX3>(st, sv, t0, m, g, lane);
 }
 
 struct FillArgs {
@@ -295,18 +384,19 @@ struct FillArgs {
   const int64_t *s_off, *tb_off, *bnd_off;
 };
 
-// LDS of the LDS-ring fill, per workgroup of SLOTS waves: each wave's S
-// ring and window buffers, then a link ring per pair of neighbouring waves
-// (the upper strip's last row, LINK_COLS columns, column j in slot
-// j % LINK_COLS), then the counters: [k] columns wave k has put into link k
-// (-1: it gave up), [SLOTS + k] columns wave k + 1 has taken from it,
-// [2 SLOTS] the task.  SLOTS = 1: one strip per workgroup, no links.
-constexpr int FILL_WAVE_LDS = RING_GROUPS * GROUP_FLOATS * 4 + 2 * 32 * 8;
+// LDS of the LDS-ring fill, per workgroup of SLOTS strips: each strip's S
+// ring, then SLOTS + 1 row rings (ring k holds the row above strip k, ring
+// SLOTS the last strip's last row on its way to memory; LINK_COLS columns,
+// column j in slot (j - 1) % LINK_COLS), then the counters: [k] columns put into row ring k (-1:
+// its writer gave up), [SLOTS + 1 + k] columns taken from it, [2 SLOTS + 2]
+// the task.
 constexpr int LINK_COLS = 512;
 constexpr int fill_lds_bytes(int slots) {
-  return slots * FILL_WAVE_LDS + (slots - 1) * LINK_COLS * 4 + 4 * (2 * slots + 1);
+  return slots * RING_GROUPS * GROUP_BYTES + (slots + 1) * LINK_COLS * 4 + 4 * (2 * slots + 3);
 }
-static_assert((LINK_COLS & (LINK_COLS - 1)) == 0 && LINK_COLS >= 256, "link ring");
+constexpr int FILL_HELPERS = 2;   // waves per workgroup that move boundary rows from and to memory
+constexpr int ALL_COLS = 0x3fffffff;   // columns put of a row that is complete; columns taken by a reader that gave up
+static_assert((LINK_COLS & (LINK_COLS - 1)) == 0 && LINK_COLS >= 256, "row ring");
 
 __global__ __launch_bounds__(256) void k_nw_reset(FillArgs A, uint4 *__restrict__ bnd16, int64_t n_bnd16,
                                                   int32_t *__restrict__ ctl, float g, float *__restrict__ score) {
@@ -324,47 +414,149 @@ __global__ __launch_bounds__(256) void k_nw_reset(FillArgs A, uint4 *__restrict_
 }
 
 template <bool MAX3, int SLOTS>
-__global__ __launch_bounds__(64 * SLOTS) void k_nw_fill(FillArgs A, const float *__restrict__ S, float g,
-                                                        float *__restrict__ score, char *__restrict__ tb,
-                                                        uint64_t *__restrict__ bnd, int32_t *__restrict__ head,
-                                                        int32_t *__restrict__ err) {
+__global__ __launch_bounds__(64 * (SLOTS + FILL_HELPERS)) void k_nw_fill(
+    FillArgs A, const float *__restrict__ S, float g, float *__restrict__ score, char *__restrict__ tb,
+    uint64_t *__restrict__ bnd, int32_t *__restrict__ head, int32_t *__restrict__ err) {
   constexpr uint32_t epoch = 1u;   // tag of a published value (the reset clears to 0)
   extern __shared__ __align__(16) char fill_lds[];   // fill_lds_bytes(SLOTS) bytes
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  float *ring = reinterpret_cast<float *>(fill_lds + wave * FILL_WAVE_LDS);
-  uint64_t *winbufA = reinterpret_cast<uint64_t *>(fill_lds + wave * FILL_WAVE_LDS + RING_GROUPS * GROUP_FLOATS * 4);
-  uint64_t *winbufB = winbufA + 32;   // boundary windows (LDS-direct loads)
-  float *links = reinterpret_cast<float *>(fill_lds + SLOTS * FILL_WAVE_LDS);
-  int *ctr = reinterpret_cast<int *>(fill_lds + SLOTS * FILL_WAVE_LDS + (SLOTS - 1) * LINK_COLS * 4);
-  float *link_in = links + (wave - 1) * LINK_COLS;   // from the wave above (wave > 0)
-  float *link_out = links + wave * LINK_COLS;        // to the wave below (wave < SLOTS - 1)
-  // this lane's ring offsets of the four 16-byte chunks of each 16 steps of
-  // a group
-  uint32_t off[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) off[i][c] = chunk_off(lane, 4 * i + c);
-  // One task (SLOTS strips, one per wave) at a time: the whole
-  // workgroup takes the next task once every wave is done with the last one,
-  // so the link rings and counters start clear.  Every wave passes both
-  // barriers of every task and leaves the loop at the same task.
+  const int wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  float *const rows_lds = reinterpret_cast<float *>(fill_lds + SLOTS * RING_GROUPS * GROUP_BYTES);
+  int *const put = reinterpret_cast<int *>(rows_lds + (SLOTS + 1) * LINK_COLS);
+  int *const taken = put + SLOTS + 1;
+  int *const task_lds = taken + SLOTS + 1;
+  // LDS operations of one wave are performed in order, so a count written
+  // after its values (or after the reads of the slots it frees) is never seen
+  // before them; only the compiler is kept from reordering.
+  auto count = [](const int *c) -> int {
+    return uniform(__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+  };
+  auto set_count = [](int *c, int v) { __hip_atomic_store(c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+
+  // One task (SLOTS strips, one per wave) at a time: the whole workgroup
+  // takes the next task once every wave is done with the last one, so the row
+  // rings and counters start clear.  Every wave passes both barriers of every
+  // task and leaves the loop at the same task.
   for (;;) {
     __syncthreads();
-    if (threadIdx.x < 2 * SLOTS) ctr[threadIdx.x] = 0;
-    if (threadIdx.x == 0) ctr[2 * SLOTS] = atomicAdd(head, 1);
+    if (threadIdx.x < 2 * SLOTS + 2) put[threadIdx.x] = 0;
+    if (threadIdx.x == 0) *task_lds = atomicAdd(head, 1);
     __syncthreads();
-    const int task = uniform(ctr[2 * SLOTS]);
+    const int task = uniform(*task_lds);
     if (task >= A.n_tasks) break;
+
+    if (wave == SLOTS) {
+      // ---- rows above, into the row rings: a pair's first row (j g), or the
+      // last row of a strip of another task, from memory.  Every published
+      // value is one 64-bit agent-coherent (sc1) store of (value, tag 1) into
+      // memory the reset kernel cleared, so a value is there when its tag is
+      // set: no counters, no store drains and no cache flushes.  64 columns of
+      // each strip's row are read per poll; the ready ones at their start go on.
+      __amdgpu_buffer_rsrc_t rs[SLOTS];
+      int at[SLOTS], m[SLOTS];   // columns handed on; columns of the row (at == m: done)
+      bool first[SLOTS];         // a pair's first strip
+      int left = 0;              // strips not done
+      bool polls = false;        // some row comes from memory
+#pragma unroll
+      for (int w = 0; w < SLOTS; ++w) {
+        const int ts = (A.task0 + task) * SLOTS + w;
+        const int b = uniform(A.tk_pair[ts]);
+        const int word = b < 0 ? 0 : uniform(A.tk_slot[ts]);
+        const int s = word & ITEM_STRIP;
+        const bool on = b >= 0 && !(word & ITEM_LINK_IN);
+        first[w] = s == 0;
+        m[w] = on ? uniform(A.m[b]) : 0;
+        at[w] = 0;
+        const uint64_t *row = on && s > 0 ? bnd + A.bnd_off[b] + (int64_t)(s - 1) * bnd_stride(m[w]) : bnd;
+        rs[w] = __builtin_amdgcn_make_buffer_rsrc((void *)uniform_ptr(row), (short)0, uniform(on && s > 0 ? 8 * (m[w] + 1) : 0),
+                                                  0x00020000);
+        left += on;
+        polls |= on && s > 0;
+      }
+      int spins = 0;
+      while (left > 0) {
+        u32x2v v[SLOTS];
+#pragma unroll
+        for (int w = 0; w < SLOTS; ++w)   // past the row's end: 0 (not ready), no memory access
+          v[w] = __builtin_amdgcn_raw_buffer_load_b64(rs[w], 8 * (at[w] + 1 + lane), 0, CPOL_SC1);
+        bool moved = false;
+#pragma unroll
+        for (int w = 0; w < SLOTS; ++w) {
+          if (at[w] == m[w]) continue;
+          const int tk = count(&taken[w]);
+          const int room = tk + LINK_COLS - at[w];   // the ring's free slots
+          const uint64_t wait = __ballot(first[w] ? at[w] + 1 + lane > m[w] : v[w].y != epoch);
+          const int ready = wait ? __builtin_ctzll(wait) : 64;
+          const int n = room < 64 && first[w] ? 0 : min(ready, room);   // (no row dribbles)
+          if (tk == ALL_COLS) {   // the strip gave up
+            at[w] = m[w];
+            --left;
+          } else if (n > 0) {
+            const float x = first[w] ? (float)(at[w] + 1 + lane) * g : __uint_as_float(v[w].x);
+            if (lane < n) rows_lds[w * LINK_COLS + ((at[w] + lane) & (LINK_COLS - 1))] = x;
+            asm volatile("" ::: "memory");
+            at[w] += n;
+            set_count(&put[w], at[w] == m[w] ? ALL_COLS : at[w]);
+            moved = true;
+            left -= at[w] == m[w];
+          } else if (ready == 0 && (spins >= A.spin_limit || uniform((int)v[w].y) == (int)TAG_FAIL)) {
+            // this wave gives up, or the row's writer did
+            set_count(&put[w], -1);
+            at[w] = m[w];
+            --left;
+          }
+        }
+        // (a first row's ring holds some thousand clocks of work)
+        if (moved) spins = 0;
+        else if (++spins, polls) __builtin_amdgcn_s_sleep(1);
+        else __builtin_amdgcn_s_sleep(16);
+      }
+      continue;
+    }
+
+    if (wave == SLOTS + 1) {
+      // ---- the last strip's last row, from its row ring to memory
+      const int ts = (A.task0 + task) * SLOTS + SLOTS - 1;
+      const int b = uniform(A.tk_pair[ts]);
+      const int s = b < 0 ? 0 : uniform(A.tk_slot[ts]) & ITEM_STRIP;
+      if (b < 0 || s == ((uniform(A.n[b]) + 63) >> 6) - 1 || (A.hold && s == 0)) continue;
+      const int m = uniform(A.m[b]);
+      uint64_t *row = bnd + A.bnd_off[b] + (int64_t)s * bnd_stride(m);
+      const __amdgpu_buffer_rsrc_t rs =
+          __builtin_amdgcn_make_buffer_rsrc((void *)uniform_ptr(row), (short)0, uniform(8 * (m + 1)), 0x00020000);
+      const float *ring = rows_lds + SLOTS * LINK_COLS;
+      int at = 0;
+      for (int spins = 0; at < m;) {
+        const int have = min(count(&put[SLOTS]), m);
+        if (have > at) {
+          const int n = min(have - at, 64);
+          asm volatile("" ::: "memory");
+          const float v = ring[(at + lane) & (LINK_COLS - 1)];
+          publish(rs, lane < n, at + 1 + lane, ((uint64_t)epoch << 32) | __float_as_uint(v));
+          asm volatile("" ::: "memory");
+          at += n;
+          set_count(&taken[SLOTS], at);
+          spins = 0;
+        } else if (have < 0 || ++spins > (A.spin_limit > SPIN_LIMIT ? A.spin_limit : SPIN_LIMIT)) {
+          // the strip gave up: the one below must not wait for values that
+          // will never come
+          for (int j = at + 1 + lane; j <= m; j += 64)
+            __hip_atomic_store(row + j, (uint64_t)TAG_FAIL << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          set_count(&taken[SLOTS], ALL_COLS);
+          break;
+        } else {
+          __builtin_amdgcn_s_sleep(1);
+        }
+      }
+      continue;
+    }
+
+    // ---- one strip
     const int ts = (A.task0 + task) * SLOTS + wave;   // this wave's task slot
     const int b = uniform(A.tk_pair[ts]);
     if (b < 0) continue;   // an empty slot
     const int s_tag = uniform(A.tk_slot[ts]);
     const int s = s_tag & ITEM_STRIP;
     const bool hot = (s_tag & ITEM_HOT) != 0;
-    const bool link_up = (s_tag & ITEM_LINK_IN) != 0;     // the boundary comes from the wave above, in LDS
-    const bool link_down = (s_tag & ITEM_LINK_OUT) != 0;  // the last row goes to the wave below, in LDS
-    const bool in_global = s > 0 && !link_up;             // the boundary comes from memory
     if (hot) __builtin_amdgcn_s_setprio(2);
     const int n = uniform(A.n[b]), m = uniform(A.m[b]);
     const int nstrips = (n + 63) >> 6;
@@ -372,21 +564,18 @@ __global__ __launch_bounds__(64 * SLOTS) void k_nw_fill(FillArgs A, const float 
     const int i0 = 64 * s;
     const int rows = min(64, n - i0);
     const float *Sb = S + A.s_off[b];
-    const int64_t mstride = bnd_stride(m);
-    const int64_t bnd_off = uniform64(A.bnd_off[b]), tb_off = uniform64(A.tb_off[b]);
-    const uint64_t *in_row = bnd + bnd_off + (int64_t)(s - 1) * mstride;   // used when s > 0
-    uint64_t *out_row = bnd + bnd_off + (int64_t)s * mstride;               // used when !last
+    const int64_t tb_off = uniform64(A.tb_off[b]);
     const int nG = (m + 63 + 63) >> 6;
-    uint4 *tbs = reinterpret_cast<uint4 *>(tb + tb_off) + (int64_t)s * nG * 64;
+    uint4 *tbs = reinterpret_cast<uint4 *>(tb + tb_off) + (int64_t)s * nG * 64 + lane;
     const int T_end = m + rows - 1;
-    const int T_pad = (T_end + 15) & ~15;
-    const int r_last = n - 1 - i0;   // lane of row n in the last strip
-    bool failed = false;
-
-    // slots 1..m of this strip's published row (nothing when it is the last
-    // or hands its row on through LDS: the store instruction still issues)
-    const __amdgpu_buffer_rsrc_t pub_rs = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)uniform_ptr(out_row), (short)0, (last || link_down) ? 0 : uniform((m + 1) * 8), 0x00020000);
+    // column m of a row that goes on leaves with the step after its own
+    const int nC = (T_end + (last ? 0 : 1) + CHUNK - 1) / CHUNK;
+    const char *ring = fill_lds + wave * RING_GROUPS * GROUP_BYTES;
+    const uint32_t ring_la = (uint32_t)uniform((int)(uint32_t)(uintptr_t)(lds_void *)(fill_lds)) +
+                             wave * RING_GROUPS * GROUP_BYTES;
+    const float *row_in = rows_lds + wave * LINK_COLS;
+    float *row_out = rows_lds + (wave + 1) * LINK_COLS;
+    const bool puts = !last && !(A.hold && s == 0);
 
     StripSrc src;
     src.rs = __builtin_amdgcn_make_buffer_rsrc((void *)uniform_ptr(Sb + (int64_t)i0 * m), (short)0,
@@ -394,219 +583,176 @@ __global__ __launch_bounds__(64 * SLOTS) void k_nw_fill(FillArgs A, const float 
 #pragma unroll
     for (int j = 0; j < 4; ++j) src.base[j] = s_lane_base(lane, j, m);
     src.step = (uint32_t)uniform(64 * (m - 1));
-    src.n_groups = (T_pad + GROUP - 1) / GROUP;
+    // this lane's LDS place of piece c of its row in slot 0
+    const char *piece[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c)
+      piece[c] = ring + 1024 * (lane >> 2) + 16 * (16 * (lane & 3) + ((c + 4 * ((lane >> 2) & 3) + (lane & 3)) & 15));
 
     StripState st;
     const int i = i0 + 1 + lane;
     st.H = (float)i * g;                                    // H[i][0]
     st.diag = (i0 == 0) ? 0.0f : (float)i0 * g;             // lane 0: H[i0][0]
-    st.col = 0.0f;
-    st.bits = 0u;
-    st.pw = 0.0f;
-
+    st.pw = st.col = 0.0f;
+    bool failed = false;
     // The pair's offsets are pinned in scalar registers before the S
     // prologue: a wait for them placed after it would also wait for its loads.
-    asm volatile("" ::"s"(bnd_off), "s"(tb_off));
+    asm volatile("" ::"s"(tb_off));
+    const int n_groups = (nC + 3) >> 2;
+    load_group(ring_la, src, 0u);
+    if (n_groups > 1) load_group(ring_la + GROUP_BYTES, src, 4u * GROUP);
 
-    // Boundary window prev[tw + 1 + lane]: the first row, or the previous
-    // strip's last row published by another wave.  Every published value is
-    // one 64-bit agent-coherent (sc1) store of (value, tag 1) into memory the
-    // reset kernel cleared, so a consumer knows a value is there when its tag
-    // is set: no counters, no store drains and no cache flushes.  Windows
-    // are prefetched two chunks ahead straight into LDS (16-byte agent-coherent
-    // LDS-direct loads, slots tw .. tw + 63), so no register holds a load in
-    // flight; the wait for one is an explicit vmcnt over the fixed sequence of
-    // memory operations of a group (below).
-    // A reload waits for its value inside the same asm statement: a load the
-    // compiler tracked could still be in flight where the spin loop rejoins
-    // the sweep, and the compiler would then drain every load in flight (the
-    // S prefetch included) before each later chunk.  The reload drains the
-    // counter too, but only on this slow path.
-    auto load_window = [&](int tw) -> uint64_t {
-      uint64_t v;
-      asm volatile(
-          "global_load_dwordx2 %0, %1, off sc1\n\t"
-          "s_waitcnt vmcnt(0)"
-          : "=&v"(v)
-          : "v"(in_row + tw + 1 + lane)
-          : "memory");
-      return v;
+    // Chunk c: the values of chunk c + 1 are read, then 16 steps run on cur.
+    // With the last chunk of a group its ring slot (whose values are in
+    // registers by now) takes the group after next; the next group, issued
+    // four chunks ago, has landed (vmcnt 0).  The row above (columns 16 c + 1
+    // .. 16 c + 16, the same 16 values in every lane) comes from row ring
+    // `wave`; its count is read in the middle of the chunk before, and again
+    // while it says that they are not there yet.  A lone wave issues an
+    // instruction about every five clocks whatever it is, so what a chunk does
+    // besides its steps counts as much as they do: the chunks run in blocks of
+    // eight with every LDS address a constant offset, and room in the ring
+    // below is checked once per block.
+    uint32_t U0 = 0u, U1 = 0u, L0 = 0u, L1 = 0u;   // 64 steps of directions
+    int in_have = 0;            // columns put into the row ring above, as last read
+    int out_free = LINK_COLS;   // columns the row ring below has room for, as last read
+    float4 va[4], vb[4];
+    float hs[CHUNK], carry = 0.0f;   // carry: lane 63's H after the chunk before
+    const int *const put_in = &put[wave];
+    auto read_have = [&]() {
+      in_have = __hip_atomic_load(put_in, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      asm volatile("" ::: "memory");
     };
-    // lanes 0..8 bring slots tw .. tw + 17 (16 bytes each), which hold the
-    // 16 values a chunk uses
-    auto prefetch_window = [&](int tw, uint64_t *buf) {
-      if (lane < 9) load_window_lds(buf, in_row + tw + 2 * lane);
-    };
-    // slot tw + 1 + lane of a window buffer (lanes 0..15 matter)
-    const int wslot = 1 + (lane & 15);
-    // lanes 0..15 feed the next 16 steps; columns beyond m are never used
-    auto window_need = [&](int tw) -> bool { return lane < 16 && tw + 1 + lane <= m; };
-    auto window_ready = [&](uint64_t v, int tw) -> bool {
-      return __ballot(window_need(tw) && (uint32_t)(v >> 32) != epoch) == 0;
-    };
-    // the producer has not got this far yet: reload (bounded) until it has;
-    // a value tagged TAG_FAIL means the producer gave up
-    auto wait_window = [&](int tw, uint64_t v) -> uint64_t {
-      int spins = 0;
-      for (;;) {
-        const uint32_t tag = (uint32_t)(v >> 32);
-        if (__ballot(window_need(tw) && tag == TAG_FAIL) != 0) {
-          failed = true;
-          break;
-        }
-        if (__ballot(window_need(tw) && tag != epoch) == 0) break;
-        if (++spins > A.spin_limit) {
-          failed = true;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-        v = load_window(tw);
+    // false: the writer of the row above gave up, or the poll limit passed
+    auto wait_in = [&](int need) -> bool {
+#pragma nounroll
+      for (int spins = 0;; ++spins) {
+        if (spins > 4) __builtin_amdgcn_s_sleep(1);
+        read_have();
+        const int have = uniform(in_have);
+        if (have >= need) return true;
+        if (have < 0 || spins > A.spin_limit) return false;
       }
-      return v;
     };
-    // A bounded wait on a link counter (LDS, written by another wave of the
-    // workgroup) until it reaches `need`; `seen` keeps the last value read,
-    // so most chunks need no read at all.  False if the writer gave up (-1)
-    // or the poll limit passed.  LDS accesses only: no vector memory counts.
-    // A wave's LDS operations are performed in order, so a count written
-    // after its values (or after the reads of the slots it frees) is never
-    // seen before them; only the compiler is kept from reordering.
-    auto link_wait = [&](const int *c, int need, int &seen) -> bool {
-      for (int spins = 0; seen < need; ++spins) {
-        if (spins > A.spin_limit) return false;
+    // room in the row ring below for columns up to `col` (columns past m too:
+    // its reader runs on past them)
+    auto wait_out = [&](int col) -> bool {
+#pragma nounroll
+      for (int spins = 0; col > out_free; ++spins) {
+        if (spins > SPIN_LIMIT) return false;
         if (spins > 0) __builtin_amdgcn_s_sleep(1);
-        seen = uniform(__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-        if (seen < 0) return false;
+        const int tk = count(&taken[wave + 1]);
+        out_free = tk == ALL_COLS ? tk : tk + LINK_COLS;
       }
       return true;
     };
-    int up_put = 0;      // columns the wave above had put, as last read
-    int down_taken = 0;  // columns the wave below had taken, as last read
-    // the boundary of the 16 steps from tw, columns tw + 1 .. tw + 16, from
-    // the wave above; then the columns taken are counted
-    auto link_take = [&](int tw) -> uint64_t {
-      if (!link_wait(&ctr[wave - 1], min(tw + 16, m), up_put)) {
-        failed = true;
-        return 0ull;
-      }
-      asm volatile("" ::: "memory");
-      const float v = link_in[(tw + 1 + (lane & 15)) & (LINK_COLS - 1)];
-      asm volatile("" ::: "memory");
-      if (lane == 0)
-        __hip_atomic_store(&ctr[SLOTS + wave - 1], tw + 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      return ((uint64_t)epoch << 32) | __float_as_uint(v);
-    };
-    // the columns of the strip's last row finished in the chunk at t0 (lanes
-    // 48.. of the collector) to the wave below, once it has taken what they
-    // overwrite; then the count of columns put
-    auto link_put = [&](int t0) {
-      const int jhi = min(t0 - 47, m);
-      if (jhi < 1 || (A.hold && s == 0)) return;
-      if (!link_wait(&ctr[SLOTS + wave], jhi - LINK_COLS, down_taken)) {
-        failed = true;
-        return;
-      }
-      const int j = t0 - 110 + lane;
-      if (lane >= 48 && j >= 1 && j <= m) link_out[j & (LINK_COLS - 1)] = st.col;
-      asm volatile("" ::: "memory");
-      if (lane == 0) __hip_atomic_store(&ctr[wave], jhi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    };
-    // One chunk of 16 steps from its boundary window.  The publish of the
-    // strip's last row is one store instruction in every chunk (see
-    // publish), so the explicit wait counts stay exact.
-    auto chunk = [&](int t0, uint64_t win, const float *grp, const uint32_t(&off)[4]) {
-      st.pw = s > 0 ? __uint_as_float((uint32_t)win) : (float)(t0 + 1 + lane) * g;
-      if (t0 < 64 || t0 + 16 > m) run16<true, MAX3>(st, grp, off, t0, m, g, lane);
-      else run16<false, MAX3>(st, grp, off, t0, m, g, lane);
-      // lane l of the collector holds H of row 64 at step t0 + 15 - 63 + l,
-      // i.e. column t0 - 110 + l; lanes 48.. publish
-      const int j = t0 - 110 + lane;
-      const bool pub = !last && !link_down && lane >= 48 && j >= 1 && j <= m && !(A.hold && s == 0);
-      publish(pub_rs, pub, j, ((uint64_t)epoch << 32) | __float_as_uint(st.col));
-      if (link_down) link_put(t0);
-      return st.bits;
-    };
-
-    // One group of 64 steps (four chunks) per iteration, in a fixed order of
-    // memory operations: per chunk [window of the chunk two ahead, publish],
-    // then [the direction words of the group: one 16-byte store per lane,
-    // 1 KiB per wave] [S of the group after next: 16 loads into the slot just
-    // consumed].  The prologue issues S of group 0, the first two windows,
-    // then S of group 1.  A window is therefore followed by exactly 3 memory
-    // operations when its chunk comes, 20 for the first two chunks of a group
-    // (17 and 18 in the first group), which is the vmcnt it waits for; a
-    // group's S was issued before the window of its first chunk, so that
-    // wait also covers the ring.  Without windows (first strip) the ring's
-    // own wait is 16, then 21 operations.  A drained counter (after a
-    // reload) only makes a wait shorter.  A last group of fewer than four
-    // chunks stops after its last chunk; nothing waits after it but the
-    // final drain.
-    static_assert(RING_GROUPS == 2 && GROUP == 64, "wait counts below assume two ring groups of 64 steps");
-    load_group(ring, src, 0, 0);
-    if (in_global) {
-      prefetch_window(0, winbufA);
-      prefetch_window(16, winbufB);
-    }
-    load_group(ring, src, 1, 1);
-    auto take_window = [&](int tw, const uint64_t *buf, int ahead) -> uint64_t {
-      // ahead: memory operations issued after this window's load
-      if (ahead == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
-      else if (ahead == 20) asm volatile("s_waitcnt vmcnt(20)" ::: "memory");
-      else if (ahead == 17) asm volatile("s_waitcnt vmcnt(17)" ::: "memory");
-      else asm volatile("s_waitcnt vmcnt(18)" ::: "memory");
-      uint64_t v = buf[wslot];
-      if (!window_ready(v, tw)) v = wait_window(tw, v);
-      return v;
-    };
-    const int n_groups = src.n_groups;
-    int slot = 0;   // ring slot of group q
-    for (int q = 0; q < n_groups; ++q) {
-      const float *grp = ring + slot * GROUP_FLOATS;
-      if (!in_global) {   // the ring slot of group q has landed
-        if (q == 0) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(21)" ::: "memory");
-      }
-      uint32_t bits[4] = {0u, 0u, 0u, 0u};
+    // the values of chunk K of two groups
+    auto read_s = [&](float4 (&v)[4], auto k) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int t0 = GROUP * q + 16 * i;
-        if (t0 >= T_pad) break;
-        uint64_t win = 0ull;
-        uint64_t *wbuf = (i & 1) ? winbufB : winbufA;
-        if (in_global) {
-          win = take_window(t0, wbuf, q == 0 ? (i == 0 ? 17 : i == 1 ? 18 : 3) : (i < 2 ? 20 : 3));
-          __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the slot is read before it is refilled
-          prefetch_window(t0 + 32, wbuf);
-        } else if (link_up) {
-          win = link_take(t0);
-        }
-        if (failed) break;
-        bits[i] = chunk(t0, win, grp, off[i]);
+      for (int p = 0; p < 4; ++p)
+        v[p] = *reinterpret_cast<const float4 *>(piece[4 * (k.value & 3) + p] + (k.value >> 2) * GROUP_BYTES);
+    };
+    const uint32_t out_la = (uint32_t)(uintptr_t)(lds_void *)row_out;
+    const uint32_t out_cnt = (uint32_t)(uintptr_t)(lds_void *)&put[wave + 1];
+    // Chunk c, in place K of the ring's eight, its row `from` columns after in,
+    // its output ((K + 4) & 7) * 64 bytes after out; false if it was the
+    // strip's last one
+    auto chunk = [&](auto early, auto k, auto from, int c, const float *in, uint32_t out, float4 (&cur)[4],
+                     float4 (&nxt)[4]) -> bool {
+      constexpr int K = k.value;
+      constexpr bool E = early.value;
+      if (__builtin_expect(uniform(in_have) < CHUNK * c + CHUNK, 0) && !wait_in(CHUNK * c + CHUNK)) {
+        failed = true;
+        return false;
       }
-      if (failed) break;
-      tbs[q * 64 + lane] = make_uint4(bits[0], bits[1], bits[2], bits[3]);
-      // every ring read of this group has returned (lgkmcnt(0)) before its
-      // slot is refilled with the group after next
+      float4 row[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) row[q] = reinterpret_cast<const float4 *>(in + from.value)[q];
+      asm volatile("" ::: "memory");
+      if ((K & 3) == 3 && lane == 0) set_count(&taken[wave], CHUNK * c + CHUNK);
+      if ((K & 3) == 3) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      read_s(nxt, std::integral_constant<int, ((K + 1) & 7)>{});
+      asm volatile("" ::: "memory");
+      if ((K & 3) == 3 && (c >> 2) + RING_GROUPS < n_groups)
+        load_group(ring_la + (K >> 2) * GROUP_BYTES, src, 4u * GROUP * ((c >> 2) + RING_GROUPS));
+      U0 = (U0 << 16) | (U1 >> 16);
+      L0 = (L0 << 16) | (L1 >> 16);
+      if constexpr (MAX3) run8_chain<E ? CHUNK * K : -1>(st, cur, row, g, U1, L1, hs);
+      else run8<E ? CHUNK * K : -1>(st, cur, row, g, U1, L1, hs);
+      read_have();
+      if constexpr (MAX3) run8_chain<E ? CHUNK * K + 8 : -1>(st, cur + 2, row + 2, g, U1, L1, hs + 8);
+      else run8<E ? CHUNK * K + 8 : -1>(st, cur + 2, row + 2, g, U1, L1, hs + 8);
+      // lgkmcnt(0): nxt and the row above have been read (before the writes
+      // below join the queue, and before nxt's slot is refilled)
       __builtin_amdgcn_s_waitcnt(0xc07f);
-      load_group(ring, src, q + RING_GROUPS, slot);
-      slot ^= 1;
+      // the strip's last row, columns 16 c - 63 .. 16 c - 48 (it starts at step 63)
+      if (!E && puts) {
+        const int col = CHUNK * c - 48;
+        put_row<((K + 4) & 7) * 64>(out, carry, hs, out_cnt, col < m ? col : ALL_COLS);
+      }
+      carry = hs[15];
+      if ((K & 3) == 3) tbs[(c >> 2) * 64] = make_uint4(U0, U1, L0, L1);
+      return c + 1 < nC;
+    };
+    auto seg = [&](int q) -> int { return 128 * q & (LINK_COLS - 1); };
+    auto sweep = [&]() {
+      using std::integral_constant;
+      constexpr std::true_type early{};
+      constexpr std::false_type late{};
+      if (!(chunk(early, integral_constant<int, 0>{}, integral_constant<int, 0>{}, 0, row_in, 0u, va, vb) &&
+            chunk(early, integral_constant<int, 1>{}, integral_constant<int, 16>{}, 1, row_in, 0u, vb, va) &&
+            chunk(early, integral_constant<int, 2>{}, integral_constant<int, 32>{}, 2, row_in, 0u, va, vb) &&
+            chunk(early, integral_constant<int, 3>{}, integral_constant<int, 48>{}, 3, row_in, 0u, vb, va)))
+        return;
+      for (int q = 0;; ++q) {
+        const int c = 4 + 8 * q;
+        const float *in = row_in + seg(q), *in2 = row_in + seg(q + 1);
+        const uint32_t out = out_la + 4 * seg(q);
+        if (puts && __builtin_expect(128 * q + 128 > out_free, 0) && !wait_out(128 * q + 128)) {
+          failed = true;
+          return;
+        }
+        if (!(chunk(late, integral_constant<int, 4>{}, integral_constant<int, 64>{}, c, in, out, va, vb) &&
+              chunk(late, integral_constant<int, 5>{}, integral_constant<int, 80>{}, c + 1, in, out, vb, va) &&
+              chunk(late, integral_constant<int, 6>{}, integral_constant<int, 96>{}, c + 2, in, out, va, vb) &&
+              chunk(late, integral_constant<int, 7>{}, integral_constant<int, 112>{}, c + 3, in, out, vb, va) &&
+              chunk(late, integral_constant<int, 0>{}, integral_constant<int, 0>{}, c + 4, in2, out, va, vb) &&
+              chunk(late, integral_constant<int, 1>{}, integral_constant<int, 16>{}, c + 5, in2, out, vb, va) &&
+              chunk(late, integral_constant<int, 2>{}, integral_constant<int, 32>{}, c + 6, in2, out, va, vb) &&
+              chunk(late, integral_constant<int, 3>{}, integral_constant<int, 48>{}, c + 7, in2, out, vb, va)))
+          return;
+      }
+    };
+    if (n_groups > 1) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    read_s(va, std::integral_constant<int, 0>{});
+    read_have();
+    sweep();
+    // the steps of a last block of fewer than four chunks, to the high bits (not
+    // of a block that holds none but the step after column m's)
+    if (!failed && (nC & 3) != 0 && (nC >> 2) < nG) {
+      const int sh = 16 * (4 - (nC & 3));
+      const uint64_t u = (((uint64_t)U0 << 32) | U1) << sh, l = (((uint64_t)L0 << 32) | L1) << sh;
+      tbs[(nC >> 2) * 64] = make_uint4((uint32_t)(u >> 32), (uint32_t)u, (uint32_t)(l >> 32), (uint32_t)l);
     }
-    // no LDS-direct load may still be writing LDS when the next item starts
+    // no LDS-direct load may still be writing LDS when the next task starts
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (last) {
-      // lane r_last stopped updating after column m: it holds H[n][m]
-      const float v = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(st.H), r_last));
-      if (lane == 0) score[b] = failed ? __builtin_nanf("") : v;
-    } else if (failed) {
-      // the strip below must not wait for a row that will never come
-      if (link_down) {
-        if (lane == 0) __hip_atomic_store(&ctr[wave], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      } else {
-        for (int j = 1 + lane; j <= m; j += 64)
-          __hip_atomic_store(out_row + j, (uint64_t)TAG_FAIL << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // H[n][m]: row n's lane after step T_end - 1
+      const int u_last = (T_end - 1) & (CHUNK - 1);
+      float v = hs[0];
+#pragma unroll
+      for (int u = 1; u < CHUNK; ++u) v = u == u_last ? hs[u] : v;
+      if (lane == n - 1 - i0) score[b] = failed ? __builtin_nanf("") : v;
+    }
+    if (failed) {
+      // neither neighbour waits for this strip
+      if (lane == 0) {
+        set_count(&taken[wave], ALL_COLS);
+        if (!last) set_count(&put[wave + 1], -1);
+        __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
-    if (failed && lane == 0) __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (hot) __builtin_amdgcn_s_setprio(0);
   }
 }
@@ -660,7 +806,7 @@ __global__ __launch_bounds__(64) void k_nw_fill_r(FillArgs A, const float *__res
     const uint64_t *in_row = bnd + A.bnd_off[b] + (int64_t)(s - 1) * mstride;   // used when s > 0
     uint64_t *out_row = bnd + A.bnd_off[b] + (int64_t)s * mstride;               // used when !last
     const int nG = (m + 63 + 63) >> 6;
-    uint32_t *tbw = reinterpret_cast<uint32_t *>(reinterpret_cast<uint4 *>(tb + A.tb_off[b]) + (int64_t)s * nG * 64);
+    uint16_t *tbw = reinterpret_cast<uint16_t *>(reinterpret_cast<uint4 *>(tb + A.tb_off[b]) + (int64_t)s * nG * 64);
     const int T_end = m + rows - 1;
     const int T_pad = (T_end + 15) & ~15;
     const int r_last = n - 1 - i0;   // lane of row n in the last strip
@@ -676,7 +822,6 @@ __global__ __launch_bounds__(64) void k_nw_fill_r(FillArgs A, const float *__res
     st.H = (float)i * g;                                    // H[i][0]
     st.diag = (i0 == 0) ? 0.0f : (float)i0 * g;             // lane 0: H[i0][0]
     st.col = 0.0f;
-    st.bits = 0u;
     st.pw = 0.0f;
 
     // the row above: lanes 0..15 hold slots tw + 1 .. tw + 16 (see k_nw_fill)
@@ -723,14 +868,17 @@ __global__ __launch_bounds__(64) void k_nw_fill_r(FillArgs A, const float *__res
       if (failed) break;                                                                           \
     }                                                                                              \
     st.pw = s > 0 ? __uint_as_float((uint32_t)win) : (float)(t0 + 1 + lane) * g;                  \
-    if (t0 < 64 || t0 + 16 > m) run16v<true, MAX3>(st, CUR, t0, m, g, lane);                      \
-    else run16v<false, MAX3>(st, CUR, t0, m, g, lane);                                             \
+    uint32_t U = 0u, L = 0u;                                                                       \
+    if (t0 < 64 || t0 + 16 > m) run16v<true, MAX3>(st, CUR, t0, m, g, lane, U, L);      \
+    else run16v<false, MAX3>(st, CUR, t0, m, g, lane, U, L);                             \
     {                                                                                              \
       const int j = t0 - 110 + lane;                                                               \
       const bool pub = !last && lane >= 48 && j >= 1 && j <= m && !(A.hold && s == 0);             \
       publish(pub_rs, pub, j, ((uint64_t)epoch << 32) | __float_as_uint(st.col));                  \
     }                                                                                              \
-    tbw[((t0 >> 6) * 64 + lane) * 4 + ((t0 >> 4) & 3)] = st.bits;                                  \
+    /* 16-bit places of chunk c in a block row's planes: c ^ 1 of each (first step high) */        \
+    tbw[((t0 >> 6) * 64 + lane) * 8 + (((t0 >> 4) & 3) ^ 1)] = (uint16_t)U;                        \
+    tbw[((t0 >> 6) * 64 + lane) * 8 + 4 + (((t0 >> 4) & 3) ^ 1)] = (uint16_t)L;                    \
     t0 += 16;                                                                                      \
   }
     for (;;) {
@@ -770,24 +918,6 @@ static __device__ __forceinline__ void load_block_lds(uint4 *blk, const uint4 *s
       : "=&s"(save)
       : "s"(la), "v"(src)
       : "memory");
-}
-
-// The 2-bit code at position p (0..63) of a block row held as four words of
-// 16 codes (first position in the high bits); w0..w3 may be per lane.
-static __device__ __forceinline__ uint32_t code_at(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, int p) {
-  const int q = p >> 4;
-  const uint32_t w = q == 0 ? w0 : q == 1 ? w1 : q == 2 ? w2 : w3;
-  return (w >> (2 * (15 - (p & 15)))) & 3u;
-}
-
-// The 16 flags at even bit positions 2 m of x (bits 2 m + 1 ignored) packed
-// into bits m.
-static __device__ __forceinline__ uint32_t pack_even(uint32_t x) {
-  x &= 0x55555555u;
-  x = (x | (x >> 1)) & 0x33333333u;
-  x = (x | (x >> 2)) & 0x0F0F0F0Fu;
-  x = (x | (x >> 4)) & 0x00FF00FFu;
-  return (x | (x >> 8)) & 0x0000FFFFu;
 }
 
 // Traceback (Sec. 5.1): from (n, m) back to the first row or column,
@@ -872,18 +1002,10 @@ __global__ __launch_bounds__(64) void k_nw_walk(PlanDev P, const char *__restric
   // codes other than LEFT, DIAG codes, the other codes (UP)
   uint64_t nl = 0ull, dg = 0ull, up = 0ull;
   auto row_masks = [&](const uint4 &w) {
-    const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-    nl = 0ull;
-    dg = 0ull;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      // code at position k of word q in bits 2 (15 - k) + 1 .. 2 (15 - k):
-      // DIAG 0, UP 1, LEFT 2
-      const uint32_t hi = ws[q] >> 1, lo = ws[q];
-      nl |= (uint64_t)pack_even(~hi | lo) << (16 * (3 - q));
-      dg |= (uint64_t)pack_even(~(hi | lo)) << (16 * (3 - q));
-    }
-    up = nl & ~dg;
+    const uint64_t u = ((uint64_t)w.x << 32) | w.y, l = ((uint64_t)w.z << 32) | w.w;
+    nl = u | ~l;
+    dg = ~(u | l);
+    up = u;
   };
   row_masks(wblk[3 * 64 + lane]);
   int cell = -1;   // this lane's row: the step of its DIAG cell in the current strip
@@ -1030,9 +1152,9 @@ static hipError_t fill_ring_attrs(int &per) {
     e = hipFuncSetAttribute((const void *)k_nw_fill<true, SLOTS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             fill_lds_bytes(SLOTS));
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, k_nw_fill<false, SLOTS>, 64 * SLOTS, fill_lds_bytes(SLOTS));
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, k_nw_fill<false, SLOTS>, 64 * (SLOTS + FILL_HELPERS), fill_lds_bytes(SLOTS));
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&c, k_nw_fill<true, SLOTS>, 64 * SLOTS, fill_lds_bytes(SLOTS));
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&c, k_nw_fill<true, SLOTS>, 64 * (SLOTS + FILL_HELPERS), fill_lds_bytes(SLOTS));
   per = a < c ? a : c;   // either variant's grid is resident at once
   if (per < 1) per = 1;
   return e;
@@ -1132,19 +1254,19 @@ hipError_t launch_nw_fill_items(const PlanDev &P, const float *S, float g, float
     const int grid = std::min(n, g_fill_cus * per);
     constexpr int lds = fill_lds_bytes(1);
     if (max3)
-      hipLaunchKernelGGL((k_nw_fill<true, 1>), dim3(grid), dim3(64), lds, st, A, S, g, score, tb, bnd, head, err);
+      hipLaunchKernelGGL((k_nw_fill<true, 1>), dim3(grid), dim3(64 * (1 + FILL_HELPERS)), lds, st, A, S, g, score, tb, bnd, head, err);
     else
-      hipLaunchKernelGGL((k_nw_fill<false, 1>), dim3(grid), dim3(64), lds, st, A, S, g, score, tb, bnd, head, err);
+      hipLaunchKernelGGL((k_nw_fill<false, 1>), dim3(grid), dim3(64 * (1 + FILL_HELPERS)), lds, st, A, S, g, score, tb, bnd, head, err);
   } else {
     int groups = g_fill_cus * g_fill_per;
     if (waves_per_cu > 0) groups = std::min(groups, std::max(1, g_fill_cus * waves_per_cu / FILL_SLOTS));
     const int grid = std::min(nt, groups);
     constexpr int lds = fill_lds_bytes(FILL_SLOTS);
     if (max3)
-      hipLaunchKernelGGL((k_nw_fill<true, FILL_SLOTS>), dim3(grid), dim3(64 * FILL_SLOTS), lds, st, A, S, g, score, tb,
+      hipLaunchKernelGGL((k_nw_fill<true, FILL_SLOTS>), dim3(grid), dim3(64 * (FILL_SLOTS + FILL_HELPERS)), lds, st, A, S, g, score, tb,
                          bnd, head, err);
     else
-      hipLaunchKernelGGL((k_nw_fill<false, FILL_SLOTS>), dim3(grid), dim3(64 * FILL_SLOTS), lds, st, A, S, g, score,
+      hipLaunchKernelGGL((k_nw_fill<false, FILL_SLOTS>), dim3(grid), dim3(64 * (FILL_SLOTS + FILL_HELPERS)), lds, st, A, S, g, score,
                          tb, bnd, head, err);
   }
   return hipGetLastError();

@@ -56,8 +56,8 @@ constexpr int32_t ITEM_LINK_OUT = 1 << 28;
 constexpr int32_t ITEM_STRIP = ITEM_LINK_OUT - 1;   // the strip index bits
 constexpr int FILL_SLOTS = 4;                        // strips (waves) per task of the LDS-ring fill
 // Steps a strip trails the strip above it (the 63-step skew of a 64-row
-// strip, a 16-step publish chunk, the two-chunk window prefetch and the
-// hand-off's memory round trip): the queue order spaces a pair's strips by it.
+// strip, a 16-step chunk of its last row and, between tasks, the hand-off's
+// memory round trip): the queue order spaces a pair's strips by it.
 constexpr int STRIP_LAG = 128;
 // Pairs whose DP dependency chain is at least this percent of the longest are
 // the "long" pairs: prepared, scored and aligned ahead of the others.
@@ -67,12 +67,11 @@ constexpr int LONG_CHAIN_PERCENT = 10;
 // are scored.
 constexpr int TOP_CHAIN_PERCENT = 60;
 
-// Direction codes of the traceback.
-constexpr int DIR_DIAG = 0, DIR_UP = 1, DIR_LEFT = 2;
-
 // Traceback bits: per pair, per 64-row strip, per 64-step block, per lane
-// (row) one uint4 = four 32-bit words of 16 steps x 2 bits (first step in the
-// high bits).  ceil((m + 63) / 64) blocks per strip, 1 KiB per block.
+// (row) one uint4 = two 64-bit planes, high word first and the first step in
+// the high bits: the cell's maximum is the value from above; it is the value
+// from the left (UP where both are, DIAG where neither is).  ceil((m + 63) /
+// 64) blocks per strip, 1 KiB per block.
 
 // Everything a contraction needs about one tile, in one 64-byte record (rt
 // and ct: the dense contraction's row and column tile).
