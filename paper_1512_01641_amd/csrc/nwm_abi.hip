@@ -731,6 +731,7 @@ nwm_status nwm_plan_sizes(const nwm_plan *plan, nwm_sizes *sizes) {
 void nwm_plan_destroy(nwm_plan *plan) {
   if (!plan) return;
   (void)hipSetDevice(plan->device);
+  if (plan->dmeta) (void)hipFree(plan->dmeta);   // (waits for the device: nothing below is in flight)
   if (plan->graph_exec) (void)hipGraphExecDestroy(plan->graph_exec);
   if (plan->cap_stream) (void)hipStreamDestroy(plan->cap_stream);
   if (plan->aux_stream) (void)hipStreamDestroy(plan->aux_stream);
@@ -746,7 +747,6 @@ void nwm_plan_destroy(nwm_plan *plan) {
   if (plan->ev_long_done) (void)hipEventDestroy(plan->ev_long_done);
   if (plan->ev_top) (void)hipEventDestroy(plan->ev_top);
   if (plan->ev_top_done) (void)hipEventDestroy(plan->ev_top_done);
-  if (plan->dmeta) (void)hipFree(plan->dmeta);
   delete plan;
 }
 
