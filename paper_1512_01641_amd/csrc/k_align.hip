@@ -44,11 +44,11 @@
 //             5000 1.63 ms (1.66: S from HBM, 3.9 TB/s).
 // k_nw_reset  clears the published-row region and the queue; scores of
 //             empty pairs.
-// k_nw_walk   traceback from (n, m): one wave per pair holds one 64-step
-//             block of its strip (both planes of a row per lane) and reads it with
-//             uniform-index readlane, with the previous block prefetched.
-//             Aligned pairs are written right-aligned (ascending) into the
-//             path area.
+// k_nw_walk   traceback from (n, m) over the stored directions: k_nw_walk_map
+//             and k_nw_walk_chain find where the path enters every strip of the
+//             longer pairs, k_nw_walk follows it through all strips at once
+//             (the shorter pairs', strip by strip) and writes the aligned pairs
+//             right-aligned (ascending) into the path area.
 // k_keep      keeps the aligned pairs with S >= threshold, ascending.
 #include "nwm_internal.h"
 
@@ -900,242 +900,369 @@ __global__ __launch_bounds__(64) void k_nw_fill_r(FillArgs A, const float *__res
   }
 }
 
-constexpr int WALK_LDS = 2048;   // path cells buffered in LDS per pair before a flush
+// ---- traceback (Sec. 5.1): from (n, m) back to the first row or column ------------
+// following the stored directions; every DIAG step emits the aligned pair.
+// Position: strip s, row r of the strip, anti-diagonal step t = j - 1 + r.  From
+// step t of row r the path goes LEFT to the first direction that is not LEFT
+// at or before t and leaves the row there by DIAG (step - 2) or UP (step - 1);
+// it ends with a step below r (column 0) or above strip 0.
+//
+// A walk is a chain of table lookups, one per row: a pair of 5000 sentences a
+// side took 0.4 ms of one wave.  So tall pairs (by_strips) are walked by all
+// their strips at once.  k_nw_walk_map climbs each strip from every step of its
+// bottom row that the path may enter it at (MAP_COLS steps around the line from
+// (0, 0) to (n, m)) and keeps where each leaves it and after how many DIAG
+// steps; k_nw_walk_chain composes these maps from the bottom strip up, one
+// lookup per strip (a strip the path enters outside its map is climbed on the
+// spot); k_nw_walk then climbs each strip from its known entry and writes its
+// aligned pairs at their known place.  The other pairs (chains no longer than
+// the three launches) are walked strip by strip by one wave of k_nw_walk.  The
+// maps and entries lie in the pair's published boundary rows, which are done
+// with: every one holds at least BND_PAD slots, and a pair of n_s strips has
+// n_s - 1 of them, one for each strip but the bottom one, whose entry is known.
+// Measured (us, all launches; one wave per pair before): six pairs of about 3000
+// sentences 420 -> 43, 100 pairs of 20 to 2000 160 -> 40, 64 pairs of 5000 394
+// -> 101; a pair of 6400 x 200 whose path runs far off the line, so that no map
+// holds it, 91 -> 247.
+constexpr int MAP_COLS = 256;               // entry steps a strip's map covers
+constexpr int MAP_BLOCKS = 2 * MAP_COLS / 64;   // blocks of directions it may read: as many steps to the left again
+constexpr int WALK_BLOCKS = 5;              // blocks one climbing wave holds
+constexpr uint32_t MAP_NONE = 0xFFFFFFFFu;  // the map does not know
+constexpr uint32_t MAP_END = 0x80000000u;   // the path ends in the strip (| DIAG steps)
+// else (step of the strip above) << 7 | DIAG steps
+static_assert(8 * BND_PAD >= 4 * MAP_COLS + 32, "a strip's map, its entry and the bottom strip's exit fit a boundary row");
 
-// One 1 KiB block of direction words into LDS (lane l: bytes 16 l .. 16 l +
-// 15 of blk), LDS-direct so that no register is written while the load is in
-// flight (the compiler takes an asm load's outputs as written at issue and
-// may copy them).  Readers wait with an explicit vmcnt.
-static __device__ __forceinline__ void load_block_lds(uint4 *blk, const uint4 *src) {
-  const uint32_t la = (uint32_t)uniform((int)(uint32_t)(uintptr_t)(lds_void *)blk);
-  uint32_t save;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %1\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %2, off\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(save)
-      : "s"(la), "v"(src)
-      : "memory");
+// first step of strip s's map (s above the bottom strip): a multiple of 64
+static __device__ __forceinline__ int map_base(int s, int n, int m) {
+  const int t = (int)((int64_t)m * (64 * s + 64) / n) + 62;
+  return max(0, (t - MAP_COLS / 2 + 32) >> 6 << 6);
 }
 
-// Traceback (Sec. 5.1): from (n, m) back to the first row or column,
-// following the stored directions; every DIAG step emits the aligned pair.
-// One wave per pair (longest pair first).  Position: strip s, row r of the
-// strip (lane r), anti-diagonal step t = j - 1 + r; the walk holds the 1 KiB
-// block of codes covering steps [64 G, 64 G + 64) of the strip (lane l: row
-// l's four words), and each lane turns its row into two 64-bit masks, bit
-// 63 - p for step 64 G + p: codes other than LEFT, and DIAG codes.  The walk
-// then moves by runs: from step t of row r the path goes LEFT up to the
-// first code that is not LEFT at or before t (the lowest set bit of the
-// row's mask above bit 63 - (t - 64 G), found on the scalar unit) and leaves
-// the row there by DIAG (step - 2) or UP (step - 1); every lane below tests
-// its row's code where that move enters it, and a ballot finds the first row
-// where the run of the same move ends, so a LEFT run and the DIAG or UP run
-// after it are one iteration.  The DIAG cells are recorded per lane (one per
-// row and strip) and written to LDS together, in path order, when the walk
-// leaves the strip.  The walk is bound by the latency
-// of its steps, and of its block loads, so each strip's blocks are
-// requested a whole strip ahead: the wave holds four blocks of its strip in
-// LDS and, on entering a strip, requests the four blocks of the strip above
-// that the path will cross if it keeps the pair's average slope (m / n
-// columns per row; within a strip the step only decreases, by one block at
-// a time).  A block outside those four is loaded when it is reached, and
-// from then on the block to its left is prefetched.  Path cells reach memory
-// in coalesced stores.
-__global__ __launch_bounds__(64) void k_nw_walk(PlanDev P, const char *__restrict__ tb_bits,
-                                                const float *__restrict__ score, int2 *__restrict__ path,
-                                                int32_t *__restrict__ n_diag, int o0) {
-  __shared__ int2 lbuf[WALK_LDS];
-  // two sets of four blocks (slots 4 k .. 4 k + 3), then the block on the left
-  __shared__ uint4 wblk[9 * 64];
-  const int b = P.dp_order[o0 + blockIdx.x];
+// strip s's boundary row as 32-bit words: the map, then {step, pairs before it}
+// of the strip's entry (step -1: the path ends below it) and, in the last row,
+// the bottom strip's exit
+static __device__ __forceinline__ uint32_t *map_row(const PlanDev &P, uint64_t *bnd, int b, int m, int s) {
+  return reinterpret_cast<uint32_t *>(bnd + P.bnd_off[b] + (int64_t)s * bnd_stride(m));
+}
+constexpr int MAP_ENTRY = MAP_COLS, MAP_BOTTOM = MAP_COLS + 4;
+
+// A row's 64 steps of one block as masks, bit 63 - p for step 64 G + p: not
+// LEFT (nl), and UP (u).  Column 0 (step r - 1 of row r) goes UP, so a climb
+// needs no check for it: a path there leaves the strip without another cell.
+struct RowMasks {
+  uint64_t nl, u;
+};
+static __device__ __forceinline__ RowMasks row_masks(const uint4 &w, int G, int r) {
+  const uint64_t u = ((uint64_t)w.x << 32) | w.y, l = ((uint64_t)w.z << 32) | w.w;
+  const uint64_t col0 = G == 0 && r > 0 ? 1ull << (64 - r) : 0ull;
+  return {u | ~l | col0, u | col0};
+}
+
+// One workgroup per strip, one lane per entry step.  Bound by the lookups'
+// latency: one 16-byte LDS read and some 20 instructions per row.  A lane that
+// leaves the blocks held goes on over block g0 and is dropped at the end (its
+// step only decreases).
+__global__ __launch_bounds__(MAP_COLS) void k_nw_walk_map(PlanDev P, const char *__restrict__ tb_bits,
+                                                          const float *__restrict__ score, uint64_t *__restrict__ bnd,
+                                                          int k0) {
+  __shared__ RowMasks wnd[MAP_BLOCKS * 64];
+  const int b = P.wk_pair[k0 + blockIdx.x], s = P.wk_strip[k0 + blockIdx.x];
+  if (__builtin_isnan(score[b])) return;   // a fill that gave up
   const int n = P.n[b], m = P.m[b];
+  const int nS = (n + 63) >> 6, nG = (m + 63 + 63) >> 6;
+  const bool bottom = s == nS - 1;
+  const int r0 = bottom ? (n - 1) & 63 : 63;
+  const int t_last = m - 1 + r0;   // the step of column m
+  const int w0 = bottom ? max(0, (t_last >> 6 << 6) - (MAP_COLS - 64)) : map_base(s, n, m);
+  const int g0 = max((w0 >> 6) - MAP_BLOCKS / 2, 0);
+  const uint4 *tbs = reinterpret_cast<const uint4 *>(tb_bits + P.tb_off[b]) + (int64_t)s * nG * 64;
+#pragma unroll
+  for (int k = threadIdx.x; k < MAP_BLOCKS * 64; k += MAP_COLS) {
+    const int G = min(g0 + (k >> 6), nG - 1);   // (blocks past the last step: never read)
+    wnd[k] = row_masks(tbs[(int64_t)G * 64 + (k & 63)], G, k & 63);
+  }
+  __syncthreads();
+  const int t0 = 64 * g0;
+  int t = bottom ? t_last : min(w0 + (int)threadIdx.x, t_last), cnt = 0;
+  bool ended = false;
+  for (int r = r0; r >= 0; --r) {
+    uint64_t x, u;
+    for (;;) {
+      const RowMasks w = wnd[(max(t - t0, 0) >> 6) * 64 + r];
+      const int q = ~t & 63;
+      x = w.nl >> q, u = w.u >> q;
+      // LEFT past the first step of the block, in any lane: on in the block
+      // before it (the other lanes look the same masks up again)
+      const bool on = x == 0ull && t >= t0;
+      if (__ballot(on) == 0ull) break;
+      if (on) t = (t & ~63) - 1;
+    }
+    // (only in row 0: column 0 is step -1 there, and no mask has it)
+    ended = t < 0;
+    const int k = __builtin_ctzll(x | (1ull << 63));
+    const int diag = 1 - (int)((u >> k) & 1ull);
+    if (!ended) t -= k + 1 + diag, cnt += diag;
+  }
+  uint32_t out = ended ? MAP_END | (uint32_t)cnt : (uint32_t)(t + 64) << 7 | (uint32_t)cnt;
+  if (t < t0 && t0 > 0) out = MAP_NONE;
+  if (!bottom) map_row(P, bnd, b, m, s)[threadIdx.x] = w0 + (int)threadIdx.x > t_last ? MAP_NONE : out;
+  else if (threadIdx.x == 0) map_row(P, bnd, b, m, nS - 2)[MAP_BOTTOM] = out;
+}
+
+// One 1 KiB row of a map into LDS (lane l: bytes 16 l .. 16 l + 15),
+// LDS-direct so that no register is written while the load is in flight (the
+// compiler takes an asm load's outputs as written at issue and may copy them).
+// Readers wait with an explicit vmcnt.
+static __device__ __forceinline__ void load_map_lds(uint32_t *to, const uint4 *src) {
+  const uint32_t la = (uint32_t)uniform((int)(uint32_t)(uintptr_t)(lds_void *)to);
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, off"
+      :
+      : "s"(la), "v"(src)
+      : "memory", "m0");
+}
+
+// The wave climbs one strip (directions tbs, nG blocks) from step t of row r0.
+// wnd: WALK_BLOCKS KiB of LDS of the wave's own.  cell: this lane's row's
+// column step of its DIAG cell, -1 if it has none.  Returns what a map holds.
+static __device__ __forceinline__ uint32_t climb_strip(const uint4 *__restrict__ tbs, uint4 *wnd, int r0, int t,
+                                                       int lane, int &cell) {
+  cell = -1;
+  int r = uniform(r0);
+  t = uniform(t);
+  int g0 = 0x7fffffff;   // the lowest block in wnd
+  // the WALK_BLOCKS blocks up to G (block 0 again for those below it)
+  u32x4v n0, n1, n2, n3, n4;
+  static_assert(WALK_BLOCKS == 5, "fetch, keep");
+  auto at = [&](int G) { return *reinterpret_cast<const u32x4v *>(tbs + (int64_t)max(G, 0) * 64 + lane); };
+  for (;;) {             // one block of 64 steps at a time
+    if (t < r) return MAP_END | (uint32_t)__popcll(__ballot(cell >= 0));
+    const int G = t >> 6;
+    if (G < g0) {
+      if (G != g0 - 1) n0 = at(G - 4), n1 = at(G - 3), n2 = at(G - 2), n3 = at(G - 1), n4 = at(G);   // (the first)
+      g0 = G - (WALK_BLOCKS - 1);
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      u32x4v *const to = reinterpret_cast<u32x4v *>(wnd) + lane;
+      to[0] = n0, to[64] = n1, to[128] = n2, to[192] = n3, to[256] = n4;
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      // the ones to the left of these, while these are climbed
+      n0 = at(g0 - 5), n1 = at(g0 - 4), n2 = at(g0 - 3), n3 = at(g0 - 2), n4 = at(g0 - 1);
+    }
+    const RowMasks w = row_masks(wnd[(G - g0) * 64 + lane], G, lane);
+    const int nl1 = (int)(uint32_t)(w.nl >> 32), nl0 = (int)(uint32_t)w.nl;
+    const int u1 = (int)(uint32_t)(w.u >> 32), u0 = (int)(uint32_t)w.u;
+    // One row per iteration, on the scalar unit, some 120 clocks (180 as the
+    // compiler orders it).  q: bit of the step in the block; past 63 the block
+    // is done with (the move before left it, or no bit is left in the row).
+    // The row's lane gets the step of its DIAG cell, -1 after UP.
+    int q = ~t & 63;
+    asm("0:\n\t"
+        "v_readlane_b32 s88, %[nl0], %[r]\n\t"
+        "v_readlane_b32 s89, %[nl1], %[r]\n\t"
+        "v_readlane_b32 s90, %[u0], %[r]\n\t"
+        "v_readlane_b32 s91, %[u1], %[r]\n\t"
+        "s_mov_b32 m0, %[r]\n\t"
+        "s_lshr_b64 s[88:89], s[88:89], %[q]\n\t"
+        "s_ff1_i32_b64 s92, s[88:89]\n\t"   // (-1 without a bit)
+        "s_min_u32 s92, s92, 64\n\t"
+        "s_add_i32 s92, s92, %[q]\n\t"
+        "s_cmp_gt_i32 s92, 63\n\t"
+        "s_cbranch_scc1 1f\n\t"
+        "s_sub_i32 s93, %[end], s92\n\t"
+        "s_add_i32 %[q], s92, 2\n\t"
+        "s_bitcmp1_b64 s[90:91], s92\n\t"
+        "s_cselect_b32 s93, -1, s93\n\t"
+        "s_subb_u32 %[q], %[q], 0\n\t"
+        "v_writelane_b32 %[cell], s93, m0\n\t"
+        "s_sub_u32 %[r], %[r], 1\n\t"
+        "s_cbranch_scc0 0b\n\t"
+        "1:"
+        : [cell] "+v"(cell), [r] "+s"(r), [q] "+s"(q)
+        : [nl0] "v"(nl0), [nl1] "v"(nl1), [u0] "v"(u0), [u1] "v"(u1), [end] "s"(64 * G + 63)
+        : "s88", "s89", "s90", "s91", "s92", "s93", "m0", "scc");
+    t = 64 * G + 63 - (r < 0 ? q : max(q, 64));
+    if (r < 0) return (uint32_t)(t + 64) << 7 | (uint32_t)__popcll(__ballot(cell >= 0));
+  }
+}
+
+// The strip's DIAG cells to the path, `before` of the pair's being emitted
+// already: cell number q of the walk (rows descending) at pa[cap - 1 - q].
+static __device__ __forceinline__ void emit_strip(int2 *__restrict__ pa, int cap, int s, int before, int lane, int cell) {
+  const uint64_t has = __ballot(cell >= 0);
+  if (cell < 0) return;
+  const int q = before + __popcll(lane == 63 ? 0ull : has >> (lane + 1));
+  if (q < cap) pa[cap - 1 - q] = make_int2(64 * s + lane, cell - lane);
+}
+
+// One wave per pair, one lookup per strip; the maps come into LDS
+// CHAIN_AHEAD strips ahead, the entries leave 64 strips at a time.
+constexpr int CHAIN_AHEAD = 16;
+__global__ __launch_bounds__(64) void k_nw_walk_chain(PlanDev P, const char *__restrict__ tb_bits,
+                                                      const float *__restrict__ score, uint64_t *__restrict__ bnd,
+                                                      int32_t *__restrict__ n_diag, int k0) {
+  __shared__ __align__(16) uint32_t maps[CHAIN_AHEAD * MAP_COLS];
+  __shared__ uint4 wnd[WALK_BLOCKS * 64];
   const int lane = threadIdx.x;
+  const int b = uniform(P.wp_pair[k0 + blockIdx.x]);
+  if (__builtin_isnan(score[b])) {   // a fill that gave up: no aligned pairs
+    if (lane == 0) n_diag[b] = 0;
+    return;
+  }
+  const int n = uniform(P.n[b]), m = uniform(P.m[b]);
+  const int nS = (n + 63) >> 6, nG = (m + 63 + 63) >> 6;
+  const uint4 *tbw = reinterpret_cast<const uint4 *>(tb_bits + P.tb_off[b]);
+  uint32_t *rows = uniform_ptr(map_row(P, bnd, b, m, 0));
+  const int64_t stride = 2 * bnd_stride(m);   // words per row
+  uint32_t out = (uint32_t)uniform((int)rows[(int64_t)(nS - 2) * stride + MAP_BOTTOM]);
+  int cell;
+  if (out == MAP_NONE)
+    out = climb_strip(tbw + (int64_t)(nS - 1) * nG * 64, wnd, (n - 1) & 63, m - 1 + ((n - 1) & 63), lane, cell);
+  int before = (int)(out & 127u);
+  const uint4 *next = reinterpret_cast<const uint4 *>(rows + (int64_t)(nS - 2) * stride) + lane;   // the next map to load
+  auto load = [&](int s) {   // (strip 0 again below it, so that every strip issues one load: never read)
+    load_map_lds(&maps[(s & (CHAIN_AHEAD - 1)) * MAP_COLS], next);
+    if (s > 0) next -= stride / 4;
+  };
+  for (int k = 0; k < CHAIN_AHEAD; ++k) load(nS - 2 - k);
+  for (int s1 = nS - 2; s1 >= 0; s1 -= 64) {   // lane k: strip s1 - k
+    const int base = map_base(max(s1 - lane, 0), n, m);
+    int2 entry = make_int2(-1, 0);
+    for (int k = 0; k < 64 && k <= s1; ++k) {
+      const int s = s1 - k;
+      if ((out & MAP_END) != 0u) break;
+      const int t = (int)(out >> 7);
+      if (lane == k) entry = make_int2(t, before);
+      const int idx = t - __builtin_amdgcn_readlane(base, k);
+      // every strip loads one map, this one CHAIN_AHEAD strips ago
+      asm volatile("s_waitcnt vmcnt(15)" ::: "memory");
+      static_assert(CHAIN_AHEAD == 16, "the wait above");
+      out = (uint32_t)uniform((int)maps[(s & (CHAIN_AHEAD - 1)) * MAP_COLS + (idx & (MAP_COLS - 1))]);
+      if ((unsigned)idx >= (unsigned)MAP_COLS) out = MAP_NONE;
+      if (out == MAP_NONE) out = climb_strip(tbw + (int64_t)s * nG * 64, wnd, 63, t, lane, cell);
+      before += (int)(out & 127u);
+      load(s - CHAIN_AHEAD);
+    }
+    if (s1 - lane >= 0) *reinterpret_cast<int2 *>(rows + (int64_t)(s1 - lane) * stride + MAP_ENTRY) = entry;
+  }
+  // no LDS-direct load may still be writing LDS when the wave ends
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (lane == 0) n_diag[b] = before;
+}
+
+// One wave per strip of the longer pairs (blocks below n_strips), then one per
+// pair of dp_order[o0 ...]: the others, strip by strip.
+__global__ __launch_bounds__(64) void k_nw_walk(PlanDev P, const char *__restrict__ tb_bits,
+                                                  const float *__restrict__ score, uint64_t *__restrict__ bnd,
+                                                  int2 *__restrict__ path, int32_t *__restrict__ n_diag, int k0,
+                                                  int n_strips, int o0) {
+  __shared__ uint4 wnd[WALK_BLOCKS * 64];
+  const int lane = threadIdx.x;
+  const bool strip = (int)blockIdx.x < n_strips;
+  const int b = uniform(strip ? P.wk_pair[k0 + blockIdx.x] : P.dp_order[o0 + blockIdx.x - n_strips]);
+  const int n = uniform(P.n[b]), m = uniform(P.m[b]);
+  const int nS = (n + 63) >> 6, nG = (m + 63 + 63) >> 6;
   const int cap = min(n, m);
-  int2 *pa = path + P.p_off[b];   // entry q of the walk (descending) at cap - 1 - q
   // an empty side, or a fill that gave up (NaN score): no aligned pairs
-  if (n <= 0 || m <= 0 || __builtin_isnan(score[b])) {
+  const bool none = n <= 0 || m <= 0 || __builtin_isnan(score[b]);
+  int s = nS - 1, r = (n - 1) & 63, t = m - 1 + r, before = 0;
+  if (strip) {
+    if (none) return;
+    s = uniform(P.wk_strip[k0 + blockIdx.x]);
+    if (s < nS - 1) {
+      const int2 entry = *reinterpret_cast<const int2 *>(map_row(P, bnd, b, m, s) + MAP_ENTRY);
+      r = 63, t = uniform(entry.x), before = uniform(entry.y);
+    }
+    if (t < 0) return;   // the path ends below
+  } else if (P.by_strips[b]) {
+    return;   // by its strips
+  } else if (none) {
     if (lane == 0) n_diag[b] = 0;
     return;
   }
   const uint4 *tbw = reinterpret_cast<const uint4 *>(tb_bits + P.tb_off[b]);
-  const int nS = (n + 63) >> 6;
-  const int nG = (m + 63 + 63) >> 6;
-  auto blk_ptr = [&](int s, int G) {
-    // out-of-range candidates read block (0, 0), which always exists
-    const bool ok = s >= 0 && s < nS && G >= 0 && G < nG;
-    return tbw + (ok ? ((int64_t)s * nG + G) * 64 : 0) + lane;
-  };
-  // position: strip s, row r, step t  (i = 64 s + r + 1, j = t - r + 1)
-  int s = (n - 1) >> 6, r = (n - 1) & 63, t = m - 1 + r;
-  int k = 0, kb = 0, flushed = 0;   // cells emitted; cells in lbuf; cells stored
-  // set hs holds blocks ob .. ob + 3 of strip cs; the other set blocks
-  // ab .. ab + 3 of strip cs - 1 (in flight until the strip changes); slot 8
-  // block cG - 1 of strip cs, in flight while pa_live
-  int cs = s, cG = t >> 6;
-  // the entry step of the strip above, relative to this strip's, for a path
-  // of the average slope: one row up (+64 steps) after 64 rows of slope m / n
-  const int d = 1 - (int)(((int64_t)64 * m) / n);
-  auto load_slot = [&](int slot, int bs, int bG) { load_block_lds(&wblk[slot * 64], blk_ptr(bs, bG)); };
-  // the four blocks ending with the one 32 steps right of the predicted entry
-  auto above_base = [&](int t_in) { return ((t_in + d + 32) >> 6) - 3; };
-  int hs = 0, ob = cG - 3, ab = above_base(t);
-  for (int q = 0; q < 4; ++q) load_slot(q, cs, ob + q);
-  for (int q = 0; q < 4; ++q) load_slot(4 + q, cs - 1, ab + q);
-  asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-  auto flush = [&]() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    for (int e = lane; e < kb; e += 64) {
-      const int q = flushed + e;
-      if (q < cap) pa[cap - 1 - q] = lbuf[e];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    flushed += kb;
-    kb = 0;
-  };
-  bool pa_live = false;
-  // this lane's row of the current block as masks (bit 63 - p: step 64 G + p):
-  // codes other than LEFT, DIAG codes, the other codes (UP)
-  uint64_t nl = 0ull, dg = 0ull, up = 0ull;
-  auto row_masks = [&](const uint4 &w) {
-    const uint64_t u = ((uint64_t)w.x << 32) | w.y, l = ((uint64_t)w.z << 32) | w.w;
-    nl = u | ~l;
-    dg = ~(u | l);
-    up = u;
-  };
-  row_masks(wblk[3 * 64 + lane]);
-  int cell = -1;   // this lane's row: the step of its DIAG cell in the current strip
-  // the current strip's DIAG cells to LDS, rows in descending order
-  auto emit = [&]() {
-    const uint64_t has = __ballot(cell >= 0);
-    if (has == 0ull) return;
-    const int nc = __popcll(has);
-    if (kb + nc > WALK_LDS) flush();
-    if (cell >= 0) lbuf[kb + __popcll(lane == 63 ? 0ull : has >> (lane + 1))] = make_int2(64 * s + lane, cell - lane);
-    kb += nc;
-    k += nc;
-    cell = -1;
-  };
+  int2 *pa = path + P.p_off[b];
   for (;;) {
-    if (r < 0) {   // into the strip above
-      emit();
-      --s;
-      r += 64;
-      t += 64;
-    }
-    if (s < 0 || t - r < 0) break;   // i == 0 or j == 0
-    const int G = t >> 6;
-    if (s != cs) {
-      // into the strip above (s = cs - 1): its blocks, requested a strip
-      // ago, become the held set, and the set just left (read for the last
-      // time at an earlier block change) takes the strip above this one
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      hs ^= 1;
-      ob = ab;
-      cs = s;
-      cG = G + 1;   // select below
-      pa_live = false;
-      ab = above_base(t);
-      for (int q = 0; q < 4; ++q) load_slot(4 * (hs ^ 1) + q, cs - 1, ab + q);
-    }
-    if (G != cG) {
-      // within a strip the walk only moves to the block on the left
-      const int x = G - ob;
-      int slot = 8;
-      if (x >= 0 && x < 4) {
-        slot = 4 * hs + x;
-      } else if (pa_live && G == cG - 1) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      } else {
-        load_slot(8, s, G);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      }
-      row_masks(wblk[slot * 64 + lane]);
-      pa_live = false;
-      cG = G;
-      if (G - 1 < ob && G >= 1) {   // past the held blocks: prefetch the next one to the left
-        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): slot 8 has been read before it is refilled
-        load_slot(8, s, G - 1);
-        pa_live = true;
-      }
-    }
-    const int base = 64 * G;
-    const uint64_t nlr = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(nl >> 32), r) << 32) |
-                         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)nl, r);
-    const uint64_t dgr = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(dg >> 32), r) << 32) |
-                         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)dg, r);
-    const uint64_t x = nlr & (~0ull << (63 - (t - base)));
-    if (x == 0ull) {   // LEFT past the block's first step: on in block G - 1
-      t = base - 1;
-      continue;
-    }
-    const int bb = __builtin_ctzll(x);
-    const int tp = base + 63 - bb;   // the step where the path leaves row r
-    if (tp < r) break;               // the LEFT run reaches column 0 first
-    const bool diag = (dgr >> bb) & 1ull;
-    // the run of DIAG (or UP) moves from tp: row rho < r is entered at step
-    // tp - slope (r - rho) and continues the run if its code there is the
-    // same; the first row (from r down) where it is not, or where the step
-    // leaves the block or column 1, is where the next iteration starts
-    const int slope = diag ? 2 : 1;
-    const int tq = tp - slope * (r - lane);
-    const int pq = tq - base;
-    const uint64_t same = diag ? dg : up;
-    const bool ok = lane < r && pq >= 0 && tq >= lane && ((same >> ((63 - pq) & 63)) & 1ull);
-    const uint64_t brk = __ballot(!ok) & ((1ull << r) - 1ull);
-    const int rs = brk ? 63 - __builtin_clzll(brk) : -1;   // highest breaking row below r
-    if (diag && lane > rs && lane <= r) cell = tq;
-    t = tp - slope * (r - rs);
-    r = rs;
+    int cell;
+    const uint32_t out = (uint32_t)uniform((int)climb_strip(tbw + (int64_t)s * nG * 64, wnd, r, t, lane, cell));
+    emit_strip(pa, cap, s, before, lane, cell);
+    if (strip) return;
+    before += (int)(out & 127u);
+    if ((out & MAP_END) != 0u || s == 0) break;
+    --s, r = 63, t = (int)(out >> 7);
   }
-  emit();
-  // no LDS-direct load may still be writing LDS when the wave ends
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  flush();
-  if (lane == 0) n_diag[b] = k;
+  if (lane == 0) n_diag[b] = before;
 }
 
-__global__ __launch_bounds__(64) void k_keep(PlanDev P, const float *__restrict__ S, float thr,
-                                             const int2 *__restrict__ path, const int32_t *__restrict__ n_diag,
-                                             int2 *__restrict__ kept, int32_t *__restrict__ n_kept, int o0) {
-  const int b = P.dp_order[o0 + blockIdx.x];
-  const int n = P.n[b], m = P.m[b];
-  const int lane = threadIdx.x;
+// The aligned pairs with S >= thr, in path order.  KEEP_WAVES waves per
+// workgroup: all of them on one of the n_long longer pairs wp_pair[q0 ...]
+// (what one wave does alone in rounds of 256 cells is a chain of two memory
+// latencies a round: 36 us for 5000 cells, 12 so), then one each on pairs of
+// dp_order[o0 ...].
+constexpr int KEEP_WAVES = 16, KEEP_CELLS = 4;   // cells per lane and round
+__global__ __launch_bounds__(64 * KEEP_WAVES) void k_keep(PlanDev P, const float *__restrict__ S, float thr,
+                                                          const int2 *__restrict__ path,
+                                                          const int32_t *__restrict__ n_diag, int2 *__restrict__ kept,
+                                                          int32_t *__restrict__ n_kept, int q0, int n_long, int o0,
+                                                          int n_pairs) {
+  __shared__ int found[2][KEEP_WAVES];   // kept cells of each wave in a round (two, so that one barrier a round does)
+  const int wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const bool together = (int)blockIdx.x < n_long;
+  int b;
+  if (together) {
+    b = uniform(P.wp_pair[q0 + blockIdx.x]);
+  } else {
+    const int o = ((int)blockIdx.x - n_long) * KEEP_WAVES + wave;
+    if (o >= n_pairs) return;
+    b = uniform(P.dp_order[o0 + o]);
+  }
+  const int n = uniform(P.n[b]), m = uniform(P.m[b]);
+  if (!together && P.by_strips[b]) return;   // by a workgroup
   const int cap = min(n, m);
-  const int k = min(n_diag[b], cap);
+  const int k = min(uniform(n_diag[b]), cap);
   const int2 *pa = path + P.p_off[b] + (cap - k);
   int2 *kp = kept + P.p_off[b];
   const float *Sb = S + P.s_off[b];
+  const int first = together ? 64 * KEEP_CELLS * wave : 0, step = 64 * KEEP_CELLS * (together ? KEEP_WAVES : 1);
   int nk = 0;
-  // 256 path cells per round: the four path loads, then the four S loads
-  // that depend on them, are each in flight together
-  constexpr int U = 4;
-  for (int q0 = 0; q0 < k; q0 += 64 * U) {
-    int2 c[U];
-    float sv[U];
+  // the path loads, then the S loads that depend on them, are each in flight
+  // together
+  for (int q0 = 0, round = 0; q0 < k; q0 += step, ++round) {
+    const int at = q0 + first + lane;
+    int2 c[KEEP_CELLS];
+    float sv[KEEP_CELLS];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int q = q0 + 64 * u + lane;
-      c[u] = q < k ? pa[q] : make_int2(0, 0);
+    for (int u = 0; u < KEEP_CELLS; ++u) c[u] = at + 64 * u < k ? pa[at + 64 * u] : make_int2(0, 0);
+#pragma unroll
+    for (int u = 0; u < KEEP_CELLS; ++u) sv[u] = at + 64 * u < k ? Sb[(int64_t)c[u].x * m + c[u].y] : 0.0f;
+    uint64_t km[KEEP_CELLS];
+    int mine = 0;
+#pragma unroll
+    for (int u = 0; u < KEEP_CELLS; ++u) {
+      km[u] = __ballot(at + 64 * u < k && sv[u] >= thr);
+      mine += __popcll(km[u]);
+    }
+    int to = nk;
+    if (together) {
+      if (lane == 0) found[round & 1][wave] = mine;
+      __syncthreads();
+      const int f = lane < KEEP_WAVES ? found[round & 1][lane] : 0;
+      for (int w = 0; w < KEEP_WAVES; ++w) {
+        const int c = __builtin_amdgcn_readlane(f, w);
+        if (w < wave) to += c;
+        nk += c;
+      }
+    } else {
+      nk += mine;
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int q = q0 + 64 * u + lane;
-      sv[u] = q < k ? Sb[(int64_t)c[u].x * m + c[u].y] : 0.0f;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool keep = q0 + 64 * u + lane < k && sv[u] >= thr;
-      const uint64_t km = __ballot(keep);
-      if (keep) kp[nk + __popcll(km & ((1ull << lane) - 1ull))] = c[u];
-      nk += __popcll(km);
+    for (int u = 0; u < KEEP_CELLS; ++u) {
+      if ((km[u] >> lane) & 1ull) kp[to + __popcll(km[u] & ((1ull << lane) - 1ull))] = c[u];
+      to += __popcll(km[u]);
     }
   }
-  if (lane == 0) n_kept[b] = nk;
+  if (lane == 0 && (!together || wave == 0)) n_kept[b] = nk;
 }
 
 // compute units; resident fill workgroups per unit for the LDS-ring fill
@@ -1281,18 +1408,27 @@ hipError_t launch_nw_fill(const PlanDev &P, const float *S, float g, float *scor
                               spin_limit, hold, staging, st);
 }
 
-// pairs dp_order[o0 .. o0 + n)
-hipError_t launch_nw_walk(const PlanDev &P, const char *tb, const float *score, int2 *path, int32_t *n_diag, int o0,
-                          int n, hipStream_t st) {
+// Pairs dp_order[o0 .. o0 + n), among them the longer pairs wp_pair[q0 .. q0 +
+// nq) with the strips wk_*[k0 .. k0 + nk).
+hipError_t launch_nw_walk(const PlanDev &P, const char *tb, const float *score, uint64_t *bnd, int2 *path,
+                          int32_t *n_diag, int o0, int n, int q0, int nq, int k0, int nk, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_nw_walk, dim3(n), dim3(64), 0, st, P, tb, score, path, n_diag, o0);
+  if (nq > 0) {
+    hipLaunchKernelGGL(k_nw_walk_map, dim3(nk), dim3(MAP_COLS), 0, st, P, tb, score, bnd, k0);
+    hipLaunchKernelGGL(k_nw_walk_chain, dim3(nq), dim3(64), 0, st, P, tb, score, bnd, n_diag, q0);
+  }
+  // (with no other pairs in the range, the strips alone)
+  hipLaunchKernelGGL(k_nw_walk, dim3(nk + (nq < n ? n : 0)), dim3(64), 0, st, P, tb, score, bnd, path, n_diag, k0, nk,
+                     o0);
   return hipGetLastError();
 }
 
 hipError_t launch_keep(const PlanDev &P, const float *S, float thr, const int2 *path, const int32_t *n_diag,
-                       int2 *kept, int32_t *n_kept, int o0, int n, hipStream_t st) {
+                       int2 *kept, int32_t *n_kept, int o0, int n, int q0, int nq, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_keep, dim3(n), dim3(64), 0, st, P, S, thr, path, n_diag, kept, n_kept, o0);
+  const int others = nq < n ? (n + KEEP_WAVES - 1) / KEEP_WAVES : 0;
+  hipLaunchKernelGGL(k_keep, dim3(nq + others), dim3(64 * KEEP_WAVES), 0, st, P, S, thr, path, n_diag, kept, n_kept, q0,
+                     nq, o0, n);
   return hipGetLastError();
 }
 

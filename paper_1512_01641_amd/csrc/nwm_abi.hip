@@ -47,9 +47,10 @@ hipError_t fill_set_attrs(int);
 hipError_t launch_nw_reset(const PlanDev &, float, float *, uint64_t *, int64_t, int32_t *, hipStream_t);
 hipError_t launch_nw_fill_items(const PlanDev &, const float *, float, float *, char *, uint64_t *, int64_t,
                                 int32_t *, int32_t *, int, int, int, int, int, int, int, int, hipStream_t);
-hipError_t launch_nw_walk(const PlanDev &, const char *, const float *, int2 *, int32_t *, int, int, hipStream_t);
-hipError_t launch_keep(const PlanDev &, const float *, float, const int2 *, const int32_t *, int2 *, int32_t *, int,
-                       int, hipStream_t);
+hipError_t launch_nw_walk(const PlanDev &, const char *, const float *, uint64_t *, int2 *, int32_t *, int, int, int,
+                          int, int, int, hipStream_t);
+hipError_t launch_keep(const PlanDev &, const float *, float, const int2 *, const int32_t *, int2 *, int32_t *, int, int,
+                       int, int, hipStream_t);
 hipError_t merge_set_attrs(int max_entries);
 hipError_t launch_union_kept(int, const int64_t *, const int2 *, const int32_t *, const int2 *, const int32_t *,
                              int2 *, int32_t *, hipStream_t);
@@ -169,6 +170,10 @@ struct nwm_plan {
   // their contraction tiles, DP items and pairs lead the long pairs' ranges
   int n_items_top = 0, n_pairs_top = 0;
   int n_tasks_top = 0, n_tasks_long = 0;   // the same ranges in tasks
+  // the pairs walked by their strips and those strips, where those of the top
+  // pairs, the other long pairs and the rest start (a fourth entry ends the
+  // last)
+  int wp_cut[4] = {}, wk_cut[4] = {};
   // the batch in three parts, the top pairs, the other long pairs, the rest:
   // where each starts in every order the score path works through (a fourth
   // entry ends the last), and its SROWS x TN tiles (all, and per column of
@@ -518,6 +523,27 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
     if (is_long[b]) p->n_items_long = (int)it_pair.size();
     if (is_top[b]) p->n_items_top = (int)it_pair.size();
   }
+  std::vector<int32_t> wp_pair, wk_pair, wk_strip, by_strips(B, 0);
+  int most[3] = {0, 0, 0};   // strips of each part's tallest pair
+  for (int q = 0; q < B; ++q) {
+    int &x = most[q < p->n_pairs_top ? 0 : q < p->n_pairs_long ? 1 : 2];
+    if (p->m[order[q]] > 0) x = std::max(x, (p->n[order[q]] + 63) / 64);
+  }
+  for (int q = 0, part = 0; q <= B; ++q) {
+    for (; part < 3 && q >= (part == 0 ? p->n_pairs_top : part == 1 ? p->n_pairs_long : B); ++part) {
+      p->wp_cut[part + 1] = (int)wp_pair.size();
+      p->wk_cut[part + 1] = (int)wk_pair.size();
+    }
+    if (q == B) break;
+    const int b = order[q], ns = (p->n[b] + 63) / 64;
+    if (ns < std::max(WALK_STRIPS, (int)(it_pair.size() / WALK_SHARE)) || most[part] < WALK_TALL || p->m[b] <= 0) continue;
+    by_strips[b] = 1;
+    wp_pair.push_back(b);
+    for (int s = 0; s < ns; ++s) {
+      wk_pair.push_back(b);
+      wk_strip.push_back(s);
+    }
+  }
   // Queue order inside each launch (top pairs, other long pairs, the rest):
   // by the latest step at which a strip can start without lengthening the
   // longest chain, max_chain - chain(pair) + STRIP_LAG * strip.  A strip can
@@ -615,6 +641,8 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
   size_t i_do = add(order.data(), 4 * order.size());
   size_t i_si = add(sent_ids.data(), 8 * sent_ids.size());
   size_t i_ip = add(it_pair.data(), 4 * it_pair.size()), i_is = add(it_strip.data(), 4 * it_strip.size());
+  size_t i_wp = add(wp_pair.data(), 4 * wp_pair.size()), i_wk = add(wk_pair.data(), 4 * wk_pair.size());
+  size_t i_ws = add(wk_strip.data(), 4 * wk_strip.size()), i_bs = add(by_strips.data(), 4 * by_strips.size());
   size_t i_tp = add(tk_pair.data(), 4 * tk_pair.size()), i_ts = add(tk_words.data(), 4 * tk_words.size());
   size_t i_bo = add(bnd_off.data(), 8 * (size_t)(B + 1));
   if (hipSetDevice(ctx->device) != hipSuccess) {
@@ -670,6 +698,10 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
   D.it_pair = (const int32_t *)at(i_ip);
   D.it_strip = (const int32_t *)at(i_is);
   D.n_tasks = (int)(tk_pair.size() / FILL_SLOTS);
+  D.by_strips = (const int32_t *)at(i_bs);
+  D.wp_pair = (const int32_t *)at(i_wp);
+  D.wk_pair = (const int32_t *)at(i_wk);
+  D.wk_strip = (const int32_t *)at(i_ws);
   D.tk_pair = (const int32_t *)at(i_tp);
   D.tk_slot = (const int32_t *)at(i_ts);
   D.bnd_off = (const int64_t *)at(i_bo);
@@ -943,6 +975,22 @@ nwm_status nwm_score_pairs(nwm_plan *p, const nwm_batch *batch, const nwm_dict *
   return dev_err(e);
 }
 
+// The traceback of parts [a, b) (top pairs, other long pairs, the rest).
+static hipError_t walk_parts(const nwm_plan *p, const char *tb, const float *score, uint64_t *bnd, int2 *path,
+                             int32_t *n_diag, int a, int b, hipStream_t st) {
+  const int first[4] = {0, p->n_pairs_top, p->n_pairs_long, p->B};
+  return launch_nw_walk(p->dev, tb, score, bnd, path, n_diag, first[a], first[b] - first[a], p->wp_cut[a],
+                        p->wp_cut[b] - p->wp_cut[a], p->wk_cut[a], p->wk_cut[b] - p->wk_cut[a], st);
+}
+
+// The threshold filter of parts [a, b).
+static hipError_t keep_parts(const nwm_plan *p, const float *S, float thr, const int2 *path, const int32_t *n_diag,
+                             int32_t *kept, int32_t *n_kept, int a, int b, hipStream_t st) {
+  const int first[4] = {0, p->n_pairs_top, p->n_pairs_long, p->B};
+  return launch_keep(p->dev, S, thr, path, n_diag, (int2 *)kept, n_kept, first[a], first[b] - first[a], p->wp_cut[a],
+                     p->wp_cut[b] - p->wp_cut[a], st);
+}
+
 nwm_status nwm_align_batch(nwm_plan *p, const float *S, float gap, float threshold, float *score,
                            int32_t *n_diag, int32_t *kept, int32_t *n_kept, void *tb, void *ws, void *stream) {
   clear_stale_error();
@@ -969,12 +1017,12 @@ nwm_status nwm_align_batch(nwm_plan *p, const float *S, float gap, float thresho
   if (e != hipSuccess) return dev_err(e);
   {
     Mark mk(p, K_WALK, st);
-    e = launch_nw_walk(p->dev, tbc, score, path, n_diag, 0, p->B, st);
+    e = walk_parts(p, tbc, score, (uint64_t *)(w + p->ws.bnd), path, n_diag, 0, 3, st);
     mk.done();
   }
   if (e == hipSuccess) {
     Mark mk(p, K_KEEP, st);
-    e = launch_keep(p->dev, S, threshold, path, n_diag, (int2 *)kept, n_kept, 0, p->B, st);
+    e = keep_parts(p, S, threshold, path, n_diag, kept, n_kept, 0, 3, st);
     mk.done();
   }
   return dev_err(e);
@@ -1019,8 +1067,8 @@ nwm_status nwm_align_batch_noalloc(nwm_plan *p, const float *S, float gap, float
   hipError_t e = launch_nw_fill(p->dev, S, gap, score, tbc, bnd, p->n_bnd, ctl, p->param[NWM_PARAM_FILL_WAVES_PER_CU],
                                 p->param[NWM_PARAM_DP_SPIN_LIMIT], p->param[NWM_PARAM_DP_TEST_HOLD],
                                 p->param[NWM_PARAM_FILL_STAGING], st);
-  if (e == hipSuccess) e = launch_nw_walk(p->dev, tbc, score, path, n_diag, 0, p->B, st);
-  if (e == hipSuccess) e = launch_keep(p->dev, S, threshold, path, n_diag, (int2 *)kept, n_kept, 0, p->B, st);
+  if (e == hipSuccess) e = walk_parts(p, tbc, score, bnd, path, n_diag, 0, 3, st);
+  if (e == hipSuccess) e = keep_parts(p, S, threshold, path, n_diag, kept, n_kept, 0, 3, st);
   return dev_err(e);
 }
 
@@ -1209,8 +1257,8 @@ static nwm_status mine_path(nwm_plan *p, const nwm_batch *batch, const nwm_dict 
       if (e == hipSuccess)
         e = launch_nw_fill_items(D, S, gap, score, tbc, bnd, p->n_bnd, ctl + 2, ctl + 1, 0, itop, 0, ttop, wpc, spin,
                                  hold, stg, lane);
-      if (e == hipSuccess) e = launch_nw_walk(D, tbc, score, path, n_diag, 0, otop, lane);
-      if (e == hipSuccess) e = launch_keep(D, S, threshold, path, n_diag, (int2 *)kept, n_kept, 0, otop, lane);
+      if (e == hipSuccess) e = walk_parts(p, tbc, score, bnd, path, n_diag, 0, 1, lane);
+      if (e == hipSuccess) e = keep_parts(p, S, threshold, path, n_diag, kept, n_kept, 0, 1, lane);
       if (e == hipSuccess) e = hipEventRecord(p->ev_top_done, lane);
     }
     if (ol > otop) {
@@ -1218,9 +1266,9 @@ static nwm_status mine_path(nwm_plan *p, const nwm_batch *batch, const nwm_dict 
       if (e == hipSuccess)
         e = launch_nw_fill_items(D, S, gap, score, tbc, bnd, p->n_bnd, ctl + 3, ctl + 1, itop, il - itop, ttop,
                                  tl - ttop, wpc, spin, hold, stg, aux);
-      if (e == hipSuccess) e = launch_nw_walk(D, tbc, score, path, n_diag, otop, ol - otop, aux);
+      if (e == hipSuccess) e = walk_parts(p, tbc, score, bnd, path, n_diag, 1, 2, aux);
       if (e == hipSuccess)
-        e = launch_keep(D, S, threshold, path, n_diag, (int2 *)kept, n_kept, otop, ol - otop, aux);
+        e = keep_parts(p, S, threshold, path, n_diag, kept, n_kept, 1, 2, aux);
       if (e == hipSuccess) e = hipEventRecord(p->ev_long_done, aux);
     }
     if (rest_after_top) {   // issued last: the long pairs' work is queued first
@@ -1234,8 +1282,8 @@ static nwm_status mine_path(nwm_plan *p, const nwm_batch *batch, const nwm_dict 
   if (e == hipSuccess)
     e = launch_nw_fill_items(D, S, gap, score, tbc, bnd, p->n_bnd, ctl, ctl + 1, il, D.n_items - il, tl,
                              D.n_tasks - tl, wpc, spin, hold, stg, st);
-  if (e == hipSuccess) e = launch_nw_walk(D, tbc, score, path, n_diag, ol, p->B - ol, st);
-  if (e == hipSuccess) e = launch_keep(D, S, threshold, path, n_diag, (int2 *)kept, n_kept, ol, p->B - ol, st);
+  if (e == hipSuccess) e = walk_parts(p, tbc, score, bnd, path, n_diag, 2, 3, st);
+  if (e == hipSuccess) e = keep_parts(p, S, threshold, path, n_diag, kept, n_kept, 2, 3, st);
   if (e == hipSuccess && ol > 0 && otop > 0) e = hipStreamWaitEvent(st, p->ev_top_done, 0);
   if (e == hipSuccess && ol > otop) e = hipStreamWaitEvent(st, p->ev_long_done, 0);
   return dev_err(e);

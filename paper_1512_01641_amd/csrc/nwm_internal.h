@@ -59,6 +59,18 @@ constexpr int FILL_SLOTS = 4;                        // strips (waves) per task 
 // strip, a 16-step chunk of its last row and, between tasks, the hand-off's
 // memory round trip): the queue order spaces a pair's strips by it.
 constexpr int STRIP_LAG = 128;
+// In a part of the batch (top pairs, other long pairs, the rest) whose tallest
+// pair has WALK_TALL strips, pairs of at least WALK_STRIPS strips are traced
+// back by all their strips at once: one wave per pair takes some 4 us a strip,
+// the three launches of the other way some 30 us (a lone pair of 4 strips 13
+// against 26 us), and where they are due anyway, pairs of a few strips are
+// better there too.  Or of at least a WALK_SHARE-th of the batch's strips, if
+// that is more: then one wave per pair fills the chip as long as that, and the
+// other way climbs every strip five times (20000 pairs of median 60, 41000
+// strips: 174 us against 373 with 4).
+constexpr int WALK_TALL = 8;
+constexpr int WALK_STRIPS = 4;
+constexpr int WALK_SHARE = 2048;
 // Pairs whose DP dependency chain is at least this percent of the longest are
 // the "long" pairs: prepared, scored and aligned ahead of the others.
 constexpr int LONG_CHAIN_PERCENT = 10;
@@ -124,6 +136,11 @@ struct PlanDev {
   // the same strips as tasks of FILL_SLOTS slots (pair -1: an empty slot)
   int n_tasks;
   const int32_t *tk_pair, *tk_slot;
+  // which pairs are walked by all their strips at once, those pairs in dp_order
+  // and their strips
+  const int32_t *by_strips;   // [B]
+  const int32_t *wp_pair;
+  const int32_t *wk_pair, *wk_strip;
   const int64_t *bnd_off;   // [B+1] offset of a pair's published boundary rows (uint64 units)
 };
 

@@ -47,3 +47,26 @@ def test_fill_infinite_similarities():
     ora = oracle.align(ns, ms, S, -0.25, -1e30)
     gpu = H.gpu_align_only(ns, ms, S, -0.25, -1e30)
     H.assert_align_equal(gpu, ora, ns, ms, check_path_as_kept=True)
+
+
+@pytest.mark.parametrize("n,m,shift", [(193, 60, 0), (256, 4, 0), (257, 1, 0), (300, 900, 500), (900, 300, -500),
+                                       (640, 640, 250), (640, 640, -250), (1100, 1100, 0), (4100, 40, 0)])
+def test_walk_by_strips_bitexact(n, m, shift):
+    """Paths of pairs walked by all their strips at once: along the diagonal,
+    far off it (entries no strip's map holds), along a side, and from column 0;
+    beside them a pair walked by one wave."""
+    rng = np.random.default_rng(13)
+    S = (rng.integers(0, 3, (n, m)) / 8.0).astype(np.float32)
+    i = np.arange(n)
+    j = i + shift
+    ok = (j >= 0) & (j < m)
+    S[i[ok], j[ok]] += 0.75
+    small = rng.random(70 * 50).astype(np.float32)
+    flat = np.concatenate([S.ravel(), small])
+    ora = oracle.align([n, 70], [m, 50], flat, -0.125, 0.5)
+    gpu = H.gpu_align_only([n, 70], [m, 50], flat, -0.125, 0.5)
+    H.assert_align_equal(gpu, ora, [n, 70], [m, 50])
+    np.testing.assert_array_equal(gpu["n_diag"], ora["n_diag"])
+    every = H.gpu_align_only([n, 70], [m, 50], flat, -0.125, -1e30)   # kept = the whole path
+    H.assert_align_equal(every, oracle.align([n, 70], [m, 50], flat, -0.125, -1e30), [n, 70], [m, 50],
+                         check_path_as_kept=True)
