@@ -147,6 +147,44 @@ def similarity(auto_sets, ref_sets) -> float:
     return 100.0 if tot == 0 else 200.0 * m / tot
 
 
+class _SharedPairs:
+    """Counts the reference pairs among a miner's kept pairs on the GPU, where
+    no reference alignment names a source sentence twice: column[k] is the
+    target sentence the reference gives source sentence k of the batch, or -1."""
+
+    def __init__(self, miner: Miner, gold_off, gold):
+        n, m = miner.batch.n.astype(np.int64), miner.batch.m.astype(np.int64)
+        first = np.concatenate([[0], np.cumsum(n)])
+        self.ok = (len(gold_off) == len(n) + 1 and gold_off[0] == 0 and gold_off[-1] == len(gold)
+                   and bool(np.all(np.diff(gold_off) >= 0)))
+        if not self.ok:
+            return
+        pair = np.repeat(np.arange(len(n)), np.diff(gold_off))
+        i, j = gold[:, 0].astype(np.int64), gold[:, 1].astype(np.int64)
+        at = first[pair] + i
+        self.ok = bool(np.all((i >= 0) & (i < n[pair]) & (j >= 0) & (j < m[pair]))) and len(np.unique(at)) == len(at)
+        if not self.ok:
+            return
+        column = np.full(int(first[-1]) + 1, -1, np.int32)
+        column[at] = j
+        p_off = np.asarray(miner.p_off, np.int64)
+        slots = np.diff(p_off)
+        slot_pair = np.repeat(np.arange(len(n)), slots)
+        dev = miner.kept.device
+        self.column = torch.as_tensor(column).to(dev)
+        self.pair = torch.as_tensor(slot_pair).to(dev)
+        self.first = torch.as_tensor(first[slot_pair]).to(dev)
+        self.slot = torch.as_tensor((np.arange(int(p_off[-1])) - p_off[slot_pair]).astype(np.int32)).to(dev)
+
+    def count(self, miner: Miner):
+        """Device int64 [2]: reference pairs kept, pairs kept."""
+        n_kept = miner.n_kept[:miner.batch.B]
+        kept = miner.kept[:len(self.pair)]
+        valid = self.slot < n_kept[self.pair]
+        at = torch.where(valid, self.first + kept[:, 0], len(self.column) - 1)
+        return torch.stack([(valid & (self.column[at] == kept[:, 1])).sum(), n_kept.sum()])
+
+
 def random_search(miner: Miner, scorer, gold_off, gold, trials: int = 32, tau=(0.05, 0.95), gap=(-1.0, -0.01),
                   seed: int = 0):
     """The paper's tuning script (Sec. 5.2): naive random selection of the
@@ -161,16 +199,27 @@ def random_search(miner: Miner, scorer, gold_off, gold, trials: int = 32, tau=(0
     gold = np.asarray(gold, np.int32).reshape(-1, 2)
     ref = [gold[gold_off[b]:gold_off[b + 1]] for b in range(B)]
     miner.score_pairs(scorer, want_raw=False)
-    hist = []
+    # The similarity of a trial is two counts.  On the GPU they are some ten
+    # small launches and all trials are queued without a synchronization; on the
+    # host a trial of 100 pairs took 0.7 ms beside 0.2 ms of alignment.
+    shared = _SharedPairs(miner, gold_off, gold)
+    hist, counts = [], []
     for _ in range(trials):
         th = float(np.float32(rng.uniform(*tau)))
         g = float(np.float32(rng.uniform(*gap)))
         miner.align(g, th)
+        if shared.ok:
+            hist.append((th, g))
+            counts.append(shared.count(miner))
+            continue
         torch.cuda.synchronize()
         nk = miner.n_kept[:B].cpu().numpy()
         kept = miner.kept.cpu().numpy()
         auto = [kept[int(miner.p_off[b]):int(miner.p_off[b]) + int(nk[b])] for b in range(B)]
         hist.append((th, g, similarity(auto, ref)))
+    if counts:
+        hist = [(th, g, 100.0 if k + len(gold) == 0 else 200.0 * m / (k + len(gold)))
+                for (th, g), (m, k) in zip(hist, torch.stack(counts).cpu().tolist())]
     best = max(range(len(hist)), key=lambda k: (hist[k][2], -k)) if hist else None
     out = {"history": hist}
     if best is not None:
