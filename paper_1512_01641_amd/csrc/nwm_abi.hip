@@ -56,7 +56,7 @@ hipError_t launch_union_kept(int, const int64_t *, const int2 *, const int32_t *
                              int2 *, int32_t *, hipStream_t);
 hipError_t launch_backward(const PlanDev &, const int64_t *, const int64_t *, const int2 *, const int32_t *,
                            const float *, const float *, float *, double *, const float *, const float *,
-                           double *, float *, float *, hipStream_t);
+                           double *, float *, float *, int64_t, hipStream_t);
 }  // namespace nwm
 
 using namespace nwm;
@@ -1095,7 +1095,8 @@ nwm_status nwm_align_backward(nwm_plan *p, const nwm_batch *batch, const void *t
   float *part_dense = part_path + 4 * (size_t)p->B;
   Mark mk(p, K_BWD, st);
   hipError_t e = launch_backward(p->dev, batch->src_off, batch->tgt_off, path, n_diag, grad_score, grad_S_extra,
-                                 grad_S, grad_gap, S, S_raw, grad_wb, part_path, part_dense, st);
+                                 grad_S, grad_gap, S, S_raw, grad_wb, part_path, part_dense,
+                                 (int64_t)p->sizes.S_elems, st);
   mk.done();
   return dev_err(e);
 }
