@@ -389,14 +389,16 @@ static __device__ __forceinline__ void score_epilogue_regs(const f32x4 (&acc)[4]
   }
 }
 
-// The record of contraction tile gt: its pair by binary search of the pairs'
-// first tiles in lane order.
+// The record of contraction tile gt: its pair by a search of the pairs' first
+// tiles in lane order, 64 of them per step, one per lane of the wave (three
+// dependent loads for 20000 pairs, where a binary search takes 15).
 static __device__ __forceinline__ GtMeta locate_tile(const PlanDev &P, int gt) {
   int lo = 0, hi = P.B;   // lane_gt[lo] <= gt < lane_gt[hi]
   while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (P.lane_gt[mid] <= gt) lo = mid;
-    else hi = mid;
+    const int step = (hi - lo + 63) >> 6, at = lo + (int)(threadIdx.x & 63) * step;
+    const uint64_t below = __ballot(at < hi && P.lane_gt[min(at, hi - 1)] <= gt);
+    lo += (__builtin_popcountll(below) - 1) * step;
+    hi = min(hi, lo + step);
   }
   GtMeta g;
   const int k = gt - P.lane_gt[lo], nct = P.lane_ct[lo + 1] - P.lane_ct[lo];

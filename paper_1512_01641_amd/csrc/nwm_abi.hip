@@ -270,11 +270,21 @@ bool finite(float x) { return std::isfinite(x); }
 //   at 256 (the table is not used often enough); FP32 gains at every size,
 //   583 / 531 at 64.
 // The target sentences' length does not matter (1000 tokens: BF16 942 / 693).
+// A batch of fewer than SPLIT_TILES of the sparse contraction's tiles takes one
+// kind for all its parts: its kernels are latencies, and a part of either kind
+// costs both kinds' (119 pairs of median 74: 139 us, 165 with two kinds).
+constexpr int64_t SPLIT_TILES = 8192;
 bool sparse(const nwm_plan *p, int k) {
   const int64_t entries = p->src_tokens * p->max_deg;
   if (!p->param[NWM_PARAM_SCORE_COMPACT]) return false;
   if (p->tgt_tokens >= ((int64_t)1 << 29)) return false;   // list offsets of a run of sentences stay 32-bit
-  if (p->prec == NWM_BF16) return entries <= 128 * p->n_src && p->part[k].tiles >= 2 * p->part[k].rows;
+  if (p->prec == NWM_BF16) {
+    if (entries > 128 * p->n_src) return false;
+    int64_t tiles = 0, rows = 0;
+    for (int i = 0; i < 3; ++i) tiles += p->part[i].tiles, rows += p->part[i].rows;
+    if (tiles < SPLIT_TILES) return tiles >= 2 * rows;
+    return p->part[k].tiles >= 2 * p->part[k].rows;
+  }
   return entries <= 256 * p->n_src;
 }
 
@@ -728,10 +738,24 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
   W.a_base = carve(8 * (size_t)D.n_rt);
   W.b_base = carve(8 * (size_t)D.n_ct);
   W.p_voc = carve(4 * (size_t)B * (size_t)nch);
-  // (a 16-byte load may read past the last list)
-  W.t_list = carve(2 * ((size_t)p->tgt_tokens + 8 * (size_t)p->n_tgt + 8) + 64);
-  W.t_rec = carve(8 * (size_t)p->n_tgt);
-  W.t_len = carve(4 * (size_t)p->n_tgt);
+  {
+    // the sparse contraction's target side (a 16-byte load may read past the
+    // last list): in the dense contraction's row lists where no part takes
+    // that one and they fit
+    const size_t bytes[3] = {2 * ((size_t)p->tgt_tokens + 8 * (size_t)p->n_tgt + 8) + 64, 8 * (size_t)p->n_tgt,
+                             4 * (size_t)p->n_tgt};
+    size_t *const to[3] = {&W.t_list, &W.t_rec, &W.t_len};
+    bool all_sparse = true;
+    for (int k = 0; k < 3; ++k) all_sparse = all_sparse && (p->part[k].tiles == 0 || sparse(p, k));
+    size_t in = W.a_list;
+    for (int k = 0; k < 3; ++k) in = align_up(in + bytes[k], 256);
+    const bool shared = all_sparse && in <= W.a_choff;
+    in = W.a_list;
+    for (int k = 0; k < 3; ++k) {
+      *to[k] = shared ? in : carve(bytes[k]);
+      in = align_up(in + bytes[k], 256);
+    }
+  }
   W.bwd = carve(16 * ((size_t)B + (size_t)D.n_rt));
   // published rows, + 2 entries (cleared in 16-byte units)
   W.bnd = carve(8 * ((size_t)bnd_off[B] + 2));
