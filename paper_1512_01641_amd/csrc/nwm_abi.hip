@@ -99,9 +99,12 @@ struct Timer {
     used = 0;
     marks.clear();
   }
-  ~Timer() {
+  void destroy() {
+    clear();
     for (auto e : pool) (void)hipEventDestroy(e);
+    pool.clear();
   }
+  ~Timer() { destroy(); }
 };
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -789,20 +792,12 @@ void nwm_plan_destroy(nwm_plan *plan) {
   (void)hipSetDevice(plan->device);
   if (plan->dmeta) (void)hipFree(plan->dmeta);   // (waits for the device: nothing below is in flight)
   if (plan->graph_exec) (void)hipGraphExecDestroy(plan->graph_exec);
-  if (plan->cap_stream) (void)hipStreamDestroy(plan->cap_stream);
-  if (plan->aux_stream) (void)hipStreamDestroy(plan->aux_stream);
-  if (plan->ev_fork) (void)hipEventDestroy(plan->ev_fork);
-  if (plan->ev_join) (void)hipEventDestroy(plan->ev_join);
-  if (plan->ev_long) (void)hipEventDestroy(plan->ev_long);
-  if (plan->ev_b_long) (void)hipEventDestroy(plan->ev_b_long);
-  if (plan->ev_b_top) (void)hipEventDestroy(plan->ev_b_top);
-  if (plan->ev_b_rest) (void)hipEventDestroy(plan->ev_b_rest);
-  if (plan->lane_stream) (void)hipStreamDestroy(plan->lane_stream);
-  if (plan->exp_stream) (void)hipStreamDestroy(plan->exp_stream);
-  if (plan->ev_a_rest) (void)hipEventDestroy(plan->ev_a_rest);
-  if (plan->ev_long_done) (void)hipEventDestroy(plan->ev_long_done);
-  if (plan->ev_top) (void)hipEventDestroy(plan->ev_top);
-  if (plan->ev_top_done) (void)hipEventDestroy(plan->ev_top_done);
+  plan->timer.destroy();   // events before the streams they were recorded on
+  for (hipEvent_t ev : {plan->ev_fork, plan->ev_join, plan->ev_long, plan->ev_b_long, plan->ev_b_top, plan->ev_b_rest,
+                        plan->ev_a_rest, plan->ev_long_done, plan->ev_top, plan->ev_top_done})
+    if (ev) (void)hipEventDestroy(ev);
+  for (hipStream_t s : {plan->cap_stream, plan->aux_stream, plan->lane_stream, plan->exp_stream})
+    if (s) (void)hipStreamDestroy(s);
   delete plan;
 }
 
