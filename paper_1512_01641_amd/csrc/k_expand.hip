@@ -51,8 +51,9 @@ constexpr uint32_t HEMPTY = 0xFFFFFFFFu;
 // registers and is stored at the start of the next sentence by unconditional
 // buffer stores whose range check drops the lanes past the row's end, so the
 // next wait for the pipelined loads never waits for these stores.
-constexpr int MERGE_OUT_REGS = 4;   // merged entries per lane held for the deferred store
-constexpr int MERGE_ROUNDS = 3;     // pipelined rounds of 16 tokens
+// merged entries per lane held for the deferred store (at least four)
+constexpr int merge_out_regs(int rounds, int epl) { return rounds * epl < 4 ? 4 : rounds * epl; }
+constexpr int MERGE_ROUNDS = 3;     // rounds of 16 tokens of the fused expansion
 typedef unsigned int m_u32x2 __attribute__((ext_vector_type(2)));
 
 struct MergeId {
@@ -63,27 +64,31 @@ struct MergeOff {
   int64_t sent, id;
   m_u32x2 t0, t1;   // the sentence's token range, as loaded
 };
+template <int R>
 struct MergeTok {
   int64_t id, t0;
   int len;
-  int tok[MERGE_ROUNDS];   // the lane's token in each round
+  int tok[R];   // the lane's token in each round
 };
+template <int R>
 struct MergeRow {
   int64_t id, t0;
   int len;
-  int e0[MERGE_ROUNDS], e1[MERGE_ROUNDS];   // its row [e0, e1) (e1 = e0 if none)
+  int e0[R], e1[R];   // its row [e0, e1) (e1 = e0 if none)
 };
+template <int R, int EPL>
 struct MergeEnt {
   int64_t id, t0;
   int len;
-  int e0[MERGE_ROUNDS], deg[MERGE_ROUNDS];
-  uint32_t u[MERGE_ROUNDS];   // the lane's entry (valid if lane % 4 < deg)
-  float v[MERGE_ROUNDS];
+  int e0[R], deg[R];
+  uint32_t u[EPL][R];   // the lane's entries lane % 4 + 4 d (valid if below deg)
+  float v[EPL][R];
 };
+template <int OUT>
 struct MergeOut {
   int64_t base, id;
   int n;   // merged entries (-1: nothing to store)
-  uint2 v[MERGE_OUT_REGS];
+  uint2 v[OUT];
 };
 constexpr uint32_t BUF_OOB = 0xFFFFFFF0u;
 
@@ -98,8 +103,9 @@ static __device__ __forceinline__ int64_t first_lane64(int64_t x) {
 }
 
 // A wave's merge table in LDS: 2^hbits slots of (word, FP64 sum), and the
-// slots claimed by the current sentence in claim order (at most half the
-// slots, which the plan's bound on tokens x degree never exceeds).
+// slots claimed by the current sentence in claim order (at most
+// merge_cap, which the plan's bound on tokens x degree never exceeds).
+constexpr int merge_cap(int slots) { return slots - slots / 4; }   // words a table of `slots` slots takes
 struct MergeTable {
   double *acc;
   uint32_t *key;
@@ -113,7 +119,7 @@ struct MergeTable {
 // lane order; nuniq counts them (wave-uniform).  A full table drops entries.
 static __device__ __forceinline__ void table_insert(const MergeTable &T, int V, uint32_t u, float v, int lane,
                                                     int &nuniq) {
-  const int HS = 1 << T.hbits, CAPU = HS >> 1;
+  const int HS = 1 << T.hbits, CAPU = merge_cap(HS);
   const bool act = u < (uint32_t)V;
   uint32_t h = act ? (u * 0x9E3779B1u) >> (32 - T.hbits) : 0u;
   bool pending = act, claimed = false, placed = false;
@@ -141,12 +147,13 @@ static __device__ __forceinline__ void table_insert(const MergeTable &T, int V, 
 
 // One wave per source sentence (grid-stride): T'[i][u] = sum over the
 // sentence's tokens t of D[t][u], merged by target word u through an LDS
-// hash table of 2^hbits slots (open addressing, linear probing, at most half
-// full by the plan's bound on tokens x degree).  The sums are FP64 LDS atomics
+// hash table of 2^hbits slots (open addressing, linear probing, at most three
+// quarters full by the plan's bound on tokens x degree).  The sums are FP64 LDS atomics
 // of FP32 terms -- exact, so independent of the order of the atomics --
 // rounded to FP32 once on the way out.  A sentence longer than the caller's
 // max_sent_tokens (a contract violation) cannot hang or write out of bounds:
 // a full table or slot list drops entries.
+template <int R, int EPL>
 __global__ __launch_bounds__(64) void k_merge_src(int64_t n_sent, const int64_t *__restrict__ sent_ids,
                                                   const int64_t *__restrict__ src_off,
                                                   const int32_t *__restrict__ src_tok,
@@ -154,12 +161,12 @@ __global__ __launch_bounds__(64) void k_merge_src(int64_t n_sent, const int64_t 
                                                   const int32_t *__restrict__ d_col, const float *__restrict__ d_val,
                                                   int V, int max_deg, int hbits, uint2 *__restrict__ merged,
                                                   int32_t *__restrict__ cnt) {
+  constexpr int OUT = merge_out_regs(R, EPL);
   extern __shared__ __align__(16) char smem[];
   const int HS = 1 << hbits;
-  const int CAPU = HS >> 1;                                  // distinct words per sentence
   double *acc = reinterpret_cast<double *>(smem);            // [HS]
   uint32_t *key = reinterpret_cast<uint32_t *>(acc + HS);    // [HS]
-  int *slots = reinterpret_cast<int *>(key + HS);            // [CAPU] claimed slots, claim order
+  int *slots = reinterpret_cast<int *>(key + HS);            // [merge_cap(HS)] claimed slots, claim order
   const int lane = threadIdx.x;
   for (int h = lane; h < HS; h += 64) {
     key[h] = HEMPTY;
@@ -195,58 +202,62 @@ __global__ __launch_bounds__(64) void k_merge_src(int64_t n_sent, const int64_t 
     return O;
   };
   auto load_tok = [&](const MergeOff &O) {
-    MergeTok T;
+    MergeTok<R> T;
     T.id = O.id;
     T.t0 = first_lane64((int64_t)(((uint64_t)O.t0.y << 32) | O.t0.x));
     const int64_t t1 = first_lane64((int64_t)(((uint64_t)O.t1.y << 32) | O.t1.x));
     T.len = O.sent < n_sent ? (int)max(t1 - T.t0, (int64_t)0) : 0;
-    // a buffer over this sentence's first 16 * MERGE_ROUNDS tokens
+    // a buffer over this sentence's first 16 * R tokens
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(src_tok + T.t0), (short)0, min(T.len, 16 * MERGE_ROUNDS) * 4, 0x00020000);
+        (void *)(src_tok + T.t0), (short)0, min(T.len, 16 * R) * 4, 0x00020000);
 #pragma unroll
-    for (int q = 0; q < MERGE_ROUNDS; ++q) T.tok[q] = (int)buf_u32(r, (uint32_t)(16 * q + (lane >> 2)) * 4u);
+    for (int q = 0; q < R; ++q) T.tok[q] = (int)buf_u32(r, (uint32_t)(16 * q + (lane >> 2)) * 4u);
     return T;
   };
-  auto load_row = [&](const MergeTok &T) {
-    MergeRow R;
-    R.id = T.id;
-    R.t0 = T.t0;
-    R.len = T.len;
+  auto load_row = [&](const MergeTok<R> &T) {
+    MergeRow<R> W;
+    W.id = T.id;
+    W.t0 = T.t0;
+    W.len = T.len;
 #pragma unroll
-    for (int q = 0; q < MERGE_ROUNDS; ++q) {
+    for (int q = 0; q < R; ++q) {
       const bool ok = 16 * q + (lane >> 2) < T.len && (unsigned)T.tok[q] < (unsigned)V;
       const uint32_t off = ok ? (uint32_t)T.tok[q] * 4u : BUF_OOB;
-      R.e0[q] = (int)buf_u32(r_row, off);
-      R.e1[q] = (int)buf_u32(r_row, ok ? off + 4u : BUF_OOB);
+      W.e0[q] = (int)buf_u32(r_row, off);
+      W.e1[q] = (int)buf_u32(r_row, ok ? off + 4u : BUF_OOB);
     }
-    return R;
+    return W;
   };
-  auto load_ent = [&](const MergeRow &R) {
-    MergeEnt E;
-    E.id = R.id;
-    E.t0 = R.t0;
-    E.len = R.len;
+  auto load_ent = [&](const MergeRow<R> &W) {
+    MergeEnt<R, EPL> E;
+    E.id = W.id;
+    E.t0 = W.t0;
+    E.len = W.len;
 #pragma unroll
-    for (int q = 0; q < MERGE_ROUNDS; ++q) {
-      E.e0[q] = R.e0[q];
-      E.deg[q] = max(0, min(R.e1[q] - R.e0[q], max_deg));
-      const uint32_t off = (lane & 3) < E.deg[q] ? (uint32_t)(E.e0[q] + (lane & 3)) * 4u : BUF_OOB;
-      E.u[q] = buf_u32(r_col, off);
-      E.v[q] = __uint_as_float(buf_u32(r_val, off));
+    for (int q = 0; q < R; ++q) {
+      E.e0[q] = W.e0[q];
+      E.deg[q] = max(0, min(W.e1[q] - W.e0[q], max_deg));
+#pragma unroll
+      for (int d = 0; d < EPL; ++d) {
+        const int x = (lane & 3) + 4 * d;
+        const uint32_t off = x < E.deg[q] ? (uint32_t)(E.e0[q] + x) * 4u : BUF_OOB;
+        E.u[d][q] = buf_u32(r_col, off);
+        E.v[d][q] = __uint_as_float(buf_u32(r_val, off));
+      }
     }
     return E;
   };
   // the merged row held in registers and the count; lanes past the row's end
   // (and every lane of an empty record) fall outside the buffer ranges
   // (base, id and n are wave-uniform; stating it keeps the resources scalar)
-  auto store_out = [&](const MergeOut &M) {
+  auto store_out = [&](const MergeOut<OUT> &M) {
     const int n_rec = __builtin_amdgcn_readfirstlane(M.n);
     const int n = max(n_rec, 0);
     const int64_t id = first_lane64(M.id);
     const __amdgpu_buffer_rsrc_t r_m =
         __builtin_amdgcn_make_buffer_rsrc((void *)(merged + first_lane64(M.base)), (short)0, n * 8, 0x00020000);
 #pragma unroll
-    for (int r = 0; r < MERGE_OUT_REGS; ++r)
+    for (int r = 0; r < OUT; ++r)
       __builtin_amdgcn_raw_buffer_store_b64((m_u32x2){M.v[r].x, M.v[r].y}, r_m, (uint32_t)(lane + 64 * r) * 8u, 0,
                                             0);
     const __amdgpu_buffer_rsrc_t r_c =
@@ -260,35 +271,40 @@ __global__ __launch_bounds__(64) void k_merge_src(int64_t n_sent, const int64_t 
 
   const int64_t G = gridDim.x;
   int64_t sent = blockIdx.x;
-  MergeEnt E = load_ent(load_row(load_tok(load_off(load_id(sent)))));
-  MergeRow R = load_row(load_tok(load_off(load_id(sent + G))));
-  MergeTok T = load_tok(load_off(load_id(sent + 2 * G)));
+  MergeEnt<R, EPL> E = load_ent(load_row(load_tok(load_off(load_id(sent)))));
+  MergeRow<R> W = load_row(load_tok(load_off(load_id(sent + G))));
+  MergeTok<R> T = load_tok(load_off(load_id(sent + 2 * G)));
   MergeOff O = load_off(load_id(sent + 3 * G));
   MergeId I = load_id(sent + 4 * G);
-  MergeOut out;
+  MergeOut<OUT> out;
   out.base = out.id = 0;
   out.n = -1;
 #pragma unroll
-  for (int r = 0; r < MERGE_OUT_REGS; ++r) out.v[r] = make_uint2(0u, 0u);
+  for (int r = 0; r < OUT; ++r) out.v[r] = make_uint2(0u, 0u);
   for (; sent < n_sent; sent += G) {
-    const MergeEnt cur = E;
-    E = load_ent(R);
-    R = load_row(T);
+    const MergeEnt<R, EPL> cur = E;
+    E = load_ent(W);
+    W = load_row(T);
     T = load_tok(O);
     O = load_off(I);
     I = load_id(sent + 5 * G);
     store_out(out);   // the previous sentence's row
 
     nuniq = 0;
-    // first 16 * MERGE_ROUNDS tokens: four entries of every row loaded ahead,
-    // further entries (rows longer than four) here
-    const int rounds = min((cur.len + 15) >> 4, MERGE_ROUNDS);
+    // first 16 * R tokens: 4 * EPL entries of every row loaded ahead, further
+    // entries (longer rows) here
+    const int rounds = min((cur.len + 15) >> 4, R);
 #pragma unroll
-    for (int q = 0; q < MERGE_ROUNDS; ++q) {
+    for (int q = 0; q < R; ++q) {
       if (q >= rounds) break;
-      insert((lane & 3) < cur.deg[q] ? cur.u[q] : HEMPTY, cur.v[q]);
-      if (max_deg > 4) {
-        for (int d = 4 + (lane & 3);; d += 4) {
+#pragma unroll
+      for (int d = 0; d < EPL; ++d) {
+        const int x = (lane & 3) + 4 * d;
+        if (d > 0 && __ballot(x < cur.deg[q]) == 0) break;
+        insert(x < cur.deg[q] ? cur.u[d][q] : HEMPTY, cur.v[d][q]);
+      }
+      if (max_deg > 4 * EPL) {
+        for (int d = 4 * EPL + (lane & 3);; d += 4) {
           if (__ballot(d < cur.deg[q]) == 0) break;
           uint32_t u = HEMPTY;
           float v = 0.0f;
@@ -301,7 +317,7 @@ __global__ __launch_bounds__(64) void k_merge_src(int64_t n_sent, const int64_t 
       }
     }
     // tokens past those (long sentences), one per lane
-    for (int c0 = 16 * MERGE_ROUNDS; c0 < cur.len; c0 += 64) {
+    for (int c0 = 16 * R; c0 < cur.len; c0 += 64) {
       int e0 = 0, deg = 0;
       if (c0 + lane < cur.len) {
         const int tok = src_tok[cur.t0 + c0 + lane];
@@ -329,7 +345,7 @@ __global__ __launch_bounds__(64) void k_merge_src(int64_t n_sent, const int64_t 
     out.id = cur.id;
     out.n = nuniq;
 #pragma unroll
-    for (int r = 0; r < MERGE_OUT_REGS; ++r) {
+    for (int r = 0; r < OUT; ++r) {
       const int e = lane + 64 * r;
       uint2 v = make_uint2(0u, 0u);
       if (e < nuniq) {
@@ -340,7 +356,7 @@ __global__ __launch_bounds__(64) void k_merge_src(int64_t n_sent, const int64_t 
       }
       out.v[r] = v;
     }
-    for (int e = 64 * MERGE_OUT_REGS + lane; e < nuniq; e += 64) {
+    for (int e = 64 * OUT + lane; e < nuniq; e += 64) {
       const int h = slots[e];
       merged[out.base + e] = make_uint2(key[h], __float_as_uint((float)acc[h]));
       key[h] = HEMPTY;
@@ -1002,19 +1018,44 @@ int merge_hbits(int max_entries) {
   return hb;
 }
 
+// Slots of k_merge_src's table: the plan's bound on a sentence's entries fills
+// three quarters of it (sentences of ordinary length half that).  Half full at
+// the bound, the table of 640 entries left room for five waves per compute unit
+// instead of ten: 320 us against 265 for 60000 sentences of 10 to 80 tokens.
+static int merge_src_hbits(int max_entries) {
+  int hb = 6;
+  while (merge_cap(1 << hb) < max_entries) ++hb;
+  return hb;
+}
+
 size_t merge_lds_bytes(int hbits) {
   const size_t hs = (size_t)1 << hbits;
-  return hs * (sizeof(double) + sizeof(uint32_t)) + (hs / 2) * sizeof(int);
+  return hs * (sizeof(double) + sizeof(uint32_t)) + (size_t)merge_cap((int)hs) * sizeof(int);
 }
 
 // Sentences sent_ids[k0 .. k0 + n_sent).
+template <typename F>
+static void merge_kernel(int max_sent_tokens, int max_deg, F &&go) {
+  const bool deep = max_deg > 4;
+  if (max_sent_tokens <= 48) {
+    if (deep) go(k_merge_src<3, 2>);
+    else go(k_merge_src<3, 1>);
+  } else if (max_sent_tokens <= 80) {
+    if (deep) go(k_merge_src<5, 2>);
+    else go(k_merge_src<5, 1>);
+  } else {
+    if (deep) go(k_merge_src<8, 2>);
+    else go(k_merge_src<8, 1>);
+  }
+}
+
 hipError_t launch_merge_src(int64_t n_sent, const int64_t *sent_ids, int64_t k0, const int64_t *src_off,
                             const int32_t *src_tok, const int32_t *d_row_off, const int32_t *d_col,
-                            const float *d_val, int V, int max_deg, int max_entries, uint2 *merged, int32_t *cnt,
-                            int waves_per_cu, hipStream_t st) {
+                            const float *d_val, int V, int max_deg, int max_entries, int max_sent_tokens,
+                            uint2 *merged, int32_t *cnt, int waves_per_cu, hipStream_t st) {
   if (n_sent <= 0) return hipSuccess;
   if (n_sent >= ((int64_t)1 << 28)) return hipErrorInvalidValue;   // byte offsets of sent_ids stay 32-bit
-  const int hb = merge_hbits(max_entries);
+  const int hb = merge_src_hbits(max_entries);
   const size_t lds = merge_lds_bytes(hb);
   static int cus = 0;
   if (cus == 0) {
@@ -1029,8 +1070,16 @@ hipError_t launch_merge_src(int64_t n_sent, const int64_t *sent_ids, int64_t k0,
   if (waves_per_cu > 0 && waves_per_cu < per) per = waves_per_cu;
   const int64_t want = (int64_t)cus * per;
   const int grid = (int)(n_sent < want ? n_sent : want);
-  hipLaunchKernelGGL(k_merge_src, dim3(grid), dim3(64), lds, st, n_sent, sent_ids + k0, src_off, src_tok, d_row_off,
-                     d_col, d_val, V, max_deg, hb, merged, cnt);
+  // Rounds of 16 tokens and entries per lane (of four lanes per token) loaded
+  // ahead.  What a sentence or a dictionary row has past them is loaded where
+  // it is merged, a memory latency per step: 60000 sentences of 10 to 80 tokens
+  // with 8 entries each took 447 us with 3 x 1, 320 us with 5 x 2; on sentences
+  // of 5 to 40 tokens with 4 entries the larger kinds gain nothing.
+  auto go = [&](auto k) {
+    hipLaunchKernelGGL(k, dim3(grid), dim3(64), lds, st, n_sent, sent_ids + k0, src_off, src_tok, d_row_off, d_col, d_val,
+                       V, max_deg, hb, merged, cnt);
+  };
+  merge_kernel(max_sent_tokens, max_deg, go);
   return hipGetLastError();
 }
 
@@ -1131,9 +1180,13 @@ hipError_t build_set_attrs(int nch, int V) {
                              (int)build_b_lds_bytes(nch, V));
 }
 
-hipError_t merge_set_attrs(int max_entries) {
-  return hipFuncSetAttribute((const void *)k_merge_src, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)merge_lds_bytes(merge_hbits(max_entries)));
+hipError_t merge_set_attrs(int max_entries, int max_sent_tokens, int max_deg) {
+  hipError_t e = hipSuccess;
+  merge_kernel(max_sent_tokens, max_deg, [&](auto k) {
+    e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)merge_lds_bytes(merge_src_hbits(max_entries)));
+  });
+  return e;
 }
 
 }  // namespace nwm

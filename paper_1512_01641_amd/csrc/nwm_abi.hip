@@ -17,7 +17,7 @@
 
 namespace nwm {
 hipError_t launch_merge_src(int64_t, const int64_t *, int64_t, const int64_t *, const int32_t *, const int32_t *,
-                            const int32_t *, const float *, int, int, int, uint2 *, int32_t *, int, hipStream_t);
+                            const int32_t *, const float *, int, int, int, int, uint2 *, int32_t *, int, hipStream_t);
 hipError_t launch_build_a(const PlanDev &, const int64_t *, const uint2 *, const int32_t *, uint2 *, int32_t *,
                           int, int, int, int64_t *, const uint32_t *, int, int, hipStream_t);
 hipError_t launch_build_b(const PlanDev &, const int64_t *, const int32_t *, uint32_t *, int32_t *, int, int, int,
@@ -51,7 +51,7 @@ hipError_t launch_nw_walk(const PlanDev &, const char *, const float *, uint64_t
                           int, int, int, hipStream_t);
 hipError_t launch_keep(const PlanDev &, const float *, float, const int2 *, const int32_t *, int2 *, int32_t *, int, int,
                        int, int, hipStream_t);
-hipError_t merge_set_attrs(int max_entries);
+hipError_t merge_set_attrs(int max_entries, int max_sent_tokens, int max_deg);
 hipError_t launch_union_kept(int, const int64_t *, const int2 *, const int32_t *, const int2 *, const int32_t *,
                              int2 *, int32_t *, hipStream_t);
 hipError_t launch_backward(const PlanDev &, const int64_t *, const int64_t *, const int2 *, const int32_t *,
@@ -770,7 +770,7 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
   p->sizes.tb_bytes = (size_t)D.path_base + 8 * (size_t)p_off[B];
   p->sizes.ws_bytes = W.total;
   // ---- kernel attributes (dynamic LDS above the default) ---------------------------
-  if (merge_set_attrs(p->max_entries) != hipSuccess || score_set_attrs(nch) != hipSuccess ||
+  if (merge_set_attrs(p->max_entries, p->max_sent_tokens, p->max_deg) != hipSuccess || score_set_attrs(nch) != hipSuccess ||
       build_set_attrs(nch, p->V) != hipSuccess || sparse_set_attrs() != hipSuccess ||
       fill_set_attrs(0) != hipSuccess) {
     (void)hipFree(p->dmeta);
@@ -871,7 +871,7 @@ static hipError_t expand_src(nwm_plan *p, const nwm_batch *batch, const nwm_dict
     }
     Mark mk(p, K_MERGE, st);
     hipError_t x = launch_merge_src(ns, p->dev.sent_ids, k0, batch->src_off, batch->src_tok, dict->row_off, dict->col,
-                                    dict->val, p->V, p->max_deg, p->max_entries, merged, cnt,
+                                    dict->val, p->V, p->max_deg, p->max_entries, p->max_sent_tokens, merged, cnt,
                                     p->param[NWM_PARAM_MERGE_WAVES_PER_CU], st);
     mk.done();
     if (sp) return x;
