@@ -14,8 +14,8 @@
 //                first maximum of (up, left, diag) with '>' (UP > LEFT > DIAG)
 //             The value from the row above moves one lane per step by a DPP
 //             wave shift.  The row above the strip comes from an LDS row ring,
-//             16 columns at a time, the same values in every lane (lane 0 uses
-//             them); the strip's own last row leaves lane 63 into the next row
+//             16 columns at a time (lane 0 uses them; the other lanes read
+//             zeros); the strip's own last row leaves lane 63 into the next row
 //             ring every 16 steps, with a count of columns put and taken.  So a
 //             strip trails the one above it by 80 steps.  What does not come
 //             from or go to a strip of the same task is the row waves' work:
@@ -36,11 +36,11 @@
 //             directions in two bit planes, and every 64 steps the wave writes
 //             one coalesced 1 KiB block.  H never reaches HBM.
 //             What bounds it is a strip wave's issue: one wave per SIMD, about
-//             225 instructions per 16 steps (150 of them the cells') at about
-//             4.7 clocks.  Measured: one strip of 64 x 20000 566 us (774 with
+//             190 instructions per 16 steps (144 of them the cells') at about
+//             5 clocks.  Measured: one strip of 64 x 20000 511 us (774 with
 //             the row above shifted through a register window, directions
 //             packed by selects and S waits spread over the chunk), 256 x
-//             20000 674 us (981), 2000 x 2000 180 us (260), 64 pairs of 5000 x
+//             20000 611 us (981), 2000 x 2000 169 us (260), 64 pairs of 5000 x
 //             5000 1.63 ms (1.66: S from HBM, 3.9 TB/s).
 // k_nw_reset  clears the published-row region and the queue; scores of
 //             empty pairs.
@@ -128,6 +128,7 @@ struct StripSrc {
 };
 
 typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(3))) const int lds_int;
 
 typedef unsigned int u32x2v __attribute__((ext_vector_type(2)));
 constexpr int CPOL_SC1 = 16;          // cache-policy bit of an agent-coherent access
@@ -209,7 +210,8 @@ static __device__ __forceinline__ float cell(float up, float left, float dg, uin
 // column goes on with values no lattice cell sees: a lane's cell of column j
 // uses the lane above at columns j - 1 and j only, and what leaves the strip
 // (its last row, the score) is taken at the step of its column.  row: the row
-// above the strip at the columns of lane 0; hs receives H after every step.
+// above the strip at the columns of lane 0, 0 in the other lanes; hs receives H
+// after every step.
 template <int EARLY>
 static __device__ __forceinline__ void run8(StripState &st, const float4 *sv, const float4 *row, float g, uint32_t &U,
                                             uint32_t &L, float *hs) {
@@ -238,15 +240,16 @@ static __device__ __forceinline__ void run8(StripState &st, const float4 *sv, co
 
 // The same eight steps (gap not -0) as one block, in the order a lone wave
 // needs.  A chain of strips runs one wave per SIMD, where every vector
-// instruction costs about 4.7 clocks whatever it is: nine per step (a lane
-// shift, three adds, one max3, and compare + add-with-carry per direction
-// plane; two-bit codes packed by selects took 16).  The chain of a step (lane
-// shift, add, max3) has other instructions behind each of its own, which cover
-// their latency and the two wait states that a lane shift needs after the
-// write of its source and an add-with-carry after the write of its carry; the
-// directions of a step are taken in the steps after it.  Left to itself the
-// compiler moves the directions of all steps behind the chain, 50 clocks a
-// step against 42.
+// instruction costs about 4.7 clocks whatever it is: nine per step (an add that
+// shifts lanes: H of the lane above plus the row above the strip, which is 0 in
+// every lane but 0, where there is no lane above; three adds, one max3, and
+// compare + add-with-carry per direction plane; two-bit codes packed by selects
+// took 16).  The chain of a step (shift, add, max3) has other instructions
+// behind each of its own, which cover their latency and the two wait states
+// that a lane shift needs after the write of its source and an add-with-carry
+// after the write of its carry; the directions of a step are taken in the steps
+// after it.  Left to itself the compiler moves the directions of all steps
+// behind the chain, 50 clocks a step against 42.
 //
 // The new H is max(up, left, diag) in one instruction: the first maximum with
 // '>' bit for bit whenever no operand is NaN or -0.  A finite S and a gap that
@@ -258,7 +261,7 @@ static __device__ __forceinline__ void run8(StripState &st, const float4 *sv, co
 // A: the step before that one's L; B, C, D: the step before's
 #define NWM_STEP(k, Hp, Xp, u, A, B, C, D)                                     \
   "v_add_f32 %[h" k "], " Xp ", %[s" k "]\n\t" A B                             \
-  "v_mov_b32_dpp %[b" k "], " Hp " wave_shr:1 row_mask:0xf bank_mask:0xf\n\t"  \
+  "v_add_f32_dpp %[b" k "], " Hp ", %[a" k "] wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"  \
   "v_add_f32 %[l" u "], %[g], " Hp "\n\t"                                      \
   "v_add_f32 %[u" u "], %[g], %[b" k "]\n\t" C D                               \
   "v_max3_f32 %[h" k "], %[u" u "], %[l" u "], %[h" k "]\n\t"
@@ -274,16 +277,16 @@ static __device__ __forceinline__ void run8(StripState &st, const float4 *sv, co
 template <int EARLY>
 static __device__ __forceinline__ void run8_chain(StripState &st, const float4 *sv, const float4 *row, float g,
                                                   uint32_t &U, uint32_t &L, float *hs) {
-  float x[8] = {row[0].x, row[0].y, row[0].z, row[0].w, row[1].x, row[1].y, row[1].z, row[1].w};
-  float u0, u1, l0, l1;
+  float x[8], u0, u1, l0, l1;
   uint64_t m;
 #define NWM_OPERANDS                                                                                                  \
   : [h0] "=&v"(hs[0]), [h1] "=&v"(hs[1]), [h2] "=&v"(hs[2]), [h3] "=&v"(hs[3]), [h4] "=&v"(hs[4]), [h5] "=&v"(hs[5]), \
-    [h6] "=&v"(hs[6]), [h7] "=&v"(hs[7]), [b0] "+v"(x[0]), [b1] "+v"(x[1]), [b2] "+v"(x[2]), [b3] "+v"(x[3]),          \
-    [b4] "+v"(x[4]), [b5] "+v"(x[5]), [b6] "+v"(x[6]), [b7] "+v"(x[7]), [U] "+v"(U), [L] "+v"(L), [u0] "=&v"(u0),      \
+    [h6] "=&v"(hs[6]), [h7] "=&v"(hs[7]), [b0] "=&v"(x[0]), [b1] "=&v"(x[1]), [b2] "=&v"(x[2]), [b3] "=&v"(x[3]),          \
+    [b4] "=&v"(x[4]), [b5] "=&v"(x[5]), [b6] "=&v"(x[6]), [b7] "=&v"(x[7]), [U] "+v"(U), [L] "+v"(L), [u0] "=&v"(u0),      \
     [u1] "=&v"(u1), [l0] "=&v"(l0), [l1] "=&v"(l1), [m] "=&s"(m)                                                      \
   : [s0] "v"(sv[0].x), [s1] "v"(sv[0].y), [s2] "v"(sv[0].z), [s3] "v"(sv[0].w), [s4] "v"(sv[1].x), [s5] "v"(sv[1].y), \
-    [s6] "v"(sv[1].z), [s7] "v"(sv[1].w), [H] "v"(st.H), [X] "v"(st.diag), [g] "s"(g), [t] "n"(EARLY)                 \
+    [s6] "v"(sv[1].z), [s7] "v"(sv[1].w), [a0] "v"(row[0].x), [a1] "v"(row[0].y), [a2] "v"(row[0].z),                   \
+    [a3] "v"(row[0].w), [a4] "v"(row[1].x), [a5] "v"(row[1].y), [a6] "v"(row[1].z), [a7] "v"(row[1].w), [H] "v"(st.H), [X] "v"(st.diag), [g] "s"(g), [t] "n"(EARLY)                 \
   : "vcc"
   if constexpr (EARLY < 0) {
     asm volatile(NWM_FIRST("0", "%[H]", "%[X]", "0")
@@ -387,12 +390,14 @@ struct FillArgs {
 // LDS of the LDS-ring fill, per workgroup of SLOTS strips: each strip's S
 // ring, then SLOTS + 1 row rings (ring k holds the row above strip k, ring
 // SLOTS the last strip's last row on its way to memory; LINK_COLS columns,
-// column j in slot (j - 1) % LINK_COLS), then the counters: [k] columns put into row ring k (-1:
-// its writer gave up), [SLOTS + 1 + k] columns taken from it, [2 SLOTS + 2]
-// the task.
+// column j in slot (j - 1) % LINK_COLS), then ZERO_BYTES of zeros (what the
+// lanes but 0 read as the row above), then the counters: [k] columns put into
+// row ring k (-1: its writer gave up), [SLOTS + 1 + k] columns taken from it,
+// [2 SLOTS + 2] the task.
 constexpr int LINK_COLS = 512;
+constexpr int ZERO_BYTES = 512;
 constexpr int fill_lds_bytes(int slots) {
-  return slots * RING_GROUPS * GROUP_BYTES + (slots + 1) * LINK_COLS * 4 + 4 * (2 * slots + 3);
+  return slots * RING_GROUPS * GROUP_BYTES + (slots + 1) * LINK_COLS * 4 + ZERO_BYTES + 4 * (2 * slots + 3);
 }
 constexpr int FILL_HELPERS = 2;   // waves per workgroup that move boundary rows from and to memory
 constexpr int ALL_COLS = 0x3fffffff;   // columns put of a row that is complete; columns taken by a reader that gave up
@@ -421,7 +426,8 @@ __global__ __launch_bounds__(64 * (SLOTS + FILL_HELPERS)) void k_nw_fill(
   extern __shared__ __align__(16) char fill_lds[];   // fill_lds_bytes(SLOTS) bytes
   const int wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
   float *const rows_lds = reinterpret_cast<float *>(fill_lds + SLOTS * RING_GROUPS * GROUP_BYTES);
-  int *const put = reinterpret_cast<int *>(rows_lds + (SLOTS + 1) * LINK_COLS);
+  float *const zeros = rows_lds + (SLOTS + 1) * LINK_COLS;
+  int *const put = reinterpret_cast<int *>(zeros + ZERO_BYTES / 4);
   int *const taken = put + SLOTS + 1;
   int *const task_lds = taken + SLOTS + 1;
   // LDS operations of one wave are performed in order, so a count written
@@ -432,6 +438,7 @@ __global__ __launch_bounds__(64 * (SLOTS + FILL_HELPERS)) void k_nw_fill(
   };
   auto set_count = [](int *c, int v) { __hip_atomic_store(c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
 
+  for (int k = threadIdx.x; k < ZERO_BYTES / 4; k += 64 * (SLOTS + FILL_HELPERS)) zeros[k] = 0.0f;
   // One task (SLOTS strips, one per wave) at a time: the whole workgroup
   // takes the next task once every wave is done with the last one, so the row
   // rings and counters start clear.  Every wave passes both barriers of every
@@ -575,7 +582,7 @@ __global__ __launch_bounds__(64 * (SLOTS + FILL_HELPERS)) void k_nw_fill(
                              wave * RING_GROUPS * GROUP_BYTES;
     const float *row_in = rows_lds + wave * LINK_COLS;
     float *row_out = rows_lds + (wave + 1) * LINK_COLS;
-    const bool puts = !last && !(A.hold && s == 0);
+    bool puts = !last && !(A.hold && s == 0);
 
     StripSrc src;
     src.rs = __builtin_amdgcn_make_buffer_rsrc((void *)uniform_ptr(Sb + (int64_t)i0 * m), (short)0,
@@ -606,7 +613,7 @@ __global__ __launch_bounds__(64 * (SLOTS + FILL_HELPERS)) void k_nw_fill(
     // With the last chunk of a group its ring slot (whose values are in
     // registers by now) takes the group after next; the next group, issued
     // four chunks ago, has landed (vmcnt 0).  The row above (columns 16 c + 1
-    // .. 16 c + 16, the same 16 values in every lane) comes from row ring
+    // .. 16 c + 16, in lane 0; the others read zeros) comes from row ring
     // `wave`; its count is read in the middle of the chunk before, and again
     // while it says that they are not there yet.  A lone wave issues an
     // instruction about every five clocks whatever it is, so what a chunk does
@@ -618,33 +625,47 @@ __global__ __launch_bounds__(64 * (SLOTS + FILL_HELPERS)) void k_nw_fill(
     int out_free = LINK_COLS;   // columns the row ring below has room for, as last read
     float4 va[4], vb[4];
     float hs[CHUNK], carry = 0.0f;   // carry: lane 63's H after the chunk before
-    const int *const put_in = &put[wave];
+    uint32_t put_in = (uint32_t)(uintptr_t)(lds_void *)&put[wave];
+    asm volatile("" : "+v"(put_in));   // (kept in a vector register, where it is used)
     auto read_have = [&]() {
-      in_have = __hip_atomic_load(put_in, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      in_have = __hip_atomic_load((lds_int *)(uintptr_t)put_in, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       asm volatile("" ::: "memory");
     };
-    // false: the writer of the row above gave up, or the poll limit passed
-    auto wait_in = [&](int need) -> bool {
+    // the sweep ends with the chunk it is in, whose values go nowhere
+    int end = nC;
+    auto give_up = [&]() {
+      failed = true;
+      puts = false;
+      end = 0;
+    };
+    // until the row above has `need` columns, or its writer gave up, or the
+    // poll limit passed
+    auto wait_in = [&](int need) {
 #pragma nounroll
       for (int spins = 0;; ++spins) {
         if (spins > 4) __builtin_amdgcn_s_sleep(1);
         read_have();
         const int have = uniform(in_have);
-        if (have >= need) return true;
-        if (have < 0 || spins > A.spin_limit) return false;
+        if (have >= need) break;
+        if (have < 0 || spins > A.spin_limit) {
+          give_up();
+          break;
+        }
       }
     };
-    // room in the row ring below for columns up to `col` (columns past m too:
-    // its reader runs on past them)
-    auto wait_out = [&](int col) -> bool {
+    // until the row ring below has room for columns up to `col` (columns past
+    // m too: its reader runs on past them)
+    auto wait_out = [&](int col) {
 #pragma nounroll
       for (int spins = 0; col > out_free; ++spins) {
-        if (spins > SPIN_LIMIT) return false;
+        if (spins > SPIN_LIMIT) {
+          give_up();
+          break;
+        }
         if (spins > 0) __builtin_amdgcn_s_sleep(1);
         const int tk = count(&taken[wave + 1]);
         out_free = tk == ALL_COLS ? tk : tk + LINK_COLS;
       }
-      return true;
     };
     // the values of chunk K of two groups
     auto read_s = [&](float4 (&v)[4], auto k) {
@@ -653,7 +674,8 @@ __global__ __launch_bounds__(64 * (SLOTS + FILL_HELPERS)) void k_nw_fill(
         v[p] = *reinterpret_cast<const float4 *>(piece[4 * (k.value & 3) + p] + (k.value >> 2) * GROUP_BYTES);
     };
     const uint32_t out_la = (uint32_t)(uintptr_t)(lds_void *)row_out;
-    const uint32_t out_cnt = (uint32_t)(uintptr_t)(lds_void *)&put[wave + 1];
+    uint32_t out_cnt = (uint32_t)(uintptr_t)(lds_void *)&put[wave + 1];
+    asm volatile("" : "+v"(out_cnt));
     // Chunk c, in place K of the ring's eight, its row `from` columns after in,
     // its output ((K + 4) & 7) * 64 bytes after out; false if it was the
     // strip's last one
@@ -661,10 +683,7 @@ __global__ __launch_bounds__(64 * (SLOTS + FILL_HELPERS)) void k_nw_fill(
                      float4 (&nxt)[4]) -> bool {
       constexpr int K = k.value;
       constexpr bool E = early.value;
-      if (__builtin_expect(uniform(in_have) < CHUNK * c + CHUNK, 0) && !wait_in(CHUNK * c + CHUNK)) {
-        failed = true;
-        return false;
-      }
+      if (__builtin_expect(uniform(in_have) < CHUNK * c + CHUNK, 0)) wait_in(CHUNK * c + CHUNK);
       float4 row[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) row[q] = reinterpret_cast<const float4 *>(in + from.value)[q];
@@ -692,26 +711,26 @@ __global__ __launch_bounds__(64 * (SLOTS + FILL_HELPERS)) void k_nw_fill(
       }
       carry = hs[15];
       if ((K & 3) == 3) tbs[(c >> 2) * 64] = make_uint4(U0, U1, L0, L1);
-      return c + 1 < nC;
+      return c + 1 < end;
     };
     auto seg = [&](int q) -> int { return 128 * q & (LINK_COLS - 1); };
+    auto lane0 = [&](const float *p) { return lane == 0 ? p : zeros; };
     auto sweep = [&]() {
+      const float *const in0 = lane0(row_in);
       using std::integral_constant;
       constexpr std::true_type early{};
       constexpr std::false_type late{};
-      if (!(chunk(early, integral_constant<int, 0>{}, integral_constant<int, 0>{}, 0, row_in, 0u, va, vb) &&
-            chunk(early, integral_constant<int, 1>{}, integral_constant<int, 16>{}, 1, row_in, 0u, vb, va) &&
-            chunk(early, integral_constant<int, 2>{}, integral_constant<int, 32>{}, 2, row_in, 0u, va, vb) &&
-            chunk(early, integral_constant<int, 3>{}, integral_constant<int, 48>{}, 3, row_in, 0u, vb, va)))
+      if (!(chunk(early, integral_constant<int, 0>{}, integral_constant<int, 0>{}, 0, in0, 0u, va, vb) &&
+            chunk(early, integral_constant<int, 1>{}, integral_constant<int, 16>{}, 1, in0, 0u, vb, va) &&
+            chunk(early, integral_constant<int, 2>{}, integral_constant<int, 32>{}, 2, in0, 0u, va, vb) &&
+            chunk(early, integral_constant<int, 3>{}, integral_constant<int, 48>{}, 3, in0, 0u, vb, va)))
         return;
       for (int q = 0;; ++q) {
         const int c = 4 + 8 * q;
-        const float *in = row_in + seg(q), *in2 = row_in + seg(q + 1);
-        const uint32_t out = out_la + 4 * seg(q);
-        if (puts && __builtin_expect(128 * q + 128 > out_free, 0) && !wait_out(128 * q + 128)) {
-          failed = true;
-          return;
-        }
+        const float *in = lane0(row_in + seg(q)), *in2 = lane0(row_in + seg(q + 1));
+        uint32_t out = out_la + 4 * seg(q);
+        asm volatile("" : "+v"(out));
+        if (puts && __builtin_expect(128 * q + 128 > out_free, 0)) wait_out(128 * q + 128);
         if (!(chunk(late, integral_constant<int, 4>{}, integral_constant<int, 64>{}, c, in, out, va, vb) &&
               chunk(late, integral_constant<int, 5>{}, integral_constant<int, 80>{}, c + 1, in, out, vb, va) &&
               chunk(late, integral_constant<int, 6>{}, integral_constant<int, 96>{}, c + 2, in, out, va, vb) &&
