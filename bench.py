@@ -62,7 +62,8 @@ def _time_steps(fn, steps, warmup, torch):
 
 def profiled_traffic(kernel):
     """HBM bytes per launch of `kernel` from the committed rocprofv3 counter
-    summary, or None once the kernel's source differs from the profiled one."""
+    summary, or None once the kernel's source differs from the profiled one
+    ("also": the sources of the class's other kernels, counted with it)."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
@@ -71,9 +72,10 @@ def profiled_traffic(kernel):
         rec = json.load(f).get(kernel)
     if not rec:
         return None
-    with open(os.path.join(ROOT, rec["source"]), "rb") as f:
-        if hashlib.sha256(f.read()).hexdigest() != rec["source_sha256"]:
-            return None
+    for source, sha in dict(rec.get("also", {}), **{rec["source"]: rec["source_sha256"]}).items():
+        with open(os.path.join(ROOT, source), "rb") as f:
+            if hashlib.sha256(f.read()).hexdigest() != sha:
+                return None
     return rec["bytes_per_launch"]
 
 
