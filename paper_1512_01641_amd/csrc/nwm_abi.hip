@@ -44,7 +44,7 @@ hipError_t score_set_attrs(int nch_max);
 hipError_t launch_nw_fill(const PlanDev &, const float *, float, float *, char *, uint64_t *, int64_t, int32_t *,
                           int, int, int, int, hipStream_t);
 hipError_t fill_set_attrs(int);
-hipError_t launch_nw_reset(const PlanDev &, float, float *, uint64_t *, int64_t, int32_t *, hipStream_t);
+hipError_t launch_nw_reset(const PlanDev &, float, float *, uint64_t *, int32_t *, int, hipStream_t);
 hipError_t launch_nw_fill_items(const PlanDev &, const float *, float, float *, char *, uint64_t *, int64_t,
                                 int32_t *, int32_t *, int, int, int, int, int, int, int, int, hipStream_t);
 hipError_t launch_nw_walk(const PlanDev &, const char *, const float *, uint64_t *, int2 *, int32_t *, int, int, int,
@@ -1254,7 +1254,7 @@ static nwm_status mine_path(nwm_plan *p, const nwm_batch *batch, const nwm_dict 
   const int ttop = p->n_tasks_top, tl = p->n_tasks_long;
   const bool rest_after_top = ol > 0 && p->part[0].tiles > 0;
   if (!rest_after_top) rest_src();
-  if (e == hipSuccess) e = launch_nw_reset(D, gap, score, bnd, p->n_bnd, ctl, st);
+  if (e == hipSuccess) e = launch_nw_reset(D, gap, score, bnd, ctl, p->param[NWM_PARAM_FILL_STAGING], st);
   if (ol > 0) {
     // the long pairs: expand and score on the main stream, the top pairs
     // first (their lists, then their tiles); the top pairs' DP on the lane
