@@ -61,7 +61,7 @@ def _time_steps(fn, steps, warmup, torch):
 
 
 def profiled_traffic(kernel):
-    """HBM bytes per launch of `kernel` from the committed rocprofv3 counter
+    """HBM bytes per step of `kernel` from the committed rocprofv3 counter
     summary, or None once the kernel's source differs from the profiled one
     ("also": the sources of the class's other kernels, counted with it)."""
     import hashlib
@@ -101,7 +101,7 @@ def compacted_chunks(batch):
 
 
 def work_model(batch):
-    """Algorithmic work of one launch of each kernel class over the batch,
+    """Algorithmic work of each kernel class over the batch,
     with its roofline bound and the definition used."""
     B, V = batch.B, batch.V
     n = batch.n.astype(np.int64)
@@ -144,8 +144,8 @@ def work_model(batch):
 
 
 def rooflines(model, kernel_ms, prec_name):
-    """Roofline object per timed kernel class (achieved = algorithmic work
-    per launch / average launch duration)."""
+    """Roofline object per timed kernel class (achieved = the class's
+    algorithmic work over the batch / its launches' time per step)."""
     out = {}
     for k, (bound, work, definition) in model.items():
         ms = kernel_ms.get(k)
@@ -209,7 +209,7 @@ def batched(nw, torch, ctx, batch, prec_name, prec, args, db=None, dd=None):
     eager_ms = _time_steps(step, args.steps, 0, torch)
     km = mn.plan.kernel_ms(reset=True)
     mn.plan.set_timing(False)
-    kernel = {k: v[0] / max(v[1], 1) for k, v in km.items() if v[1]}
+    kernel = {k: v[0] / args.steps for k, v in km.items() if v[1]}
     launches = {k: v[1] / args.steps for k, v in km.items() if v[1]}
     ms = eager_ms
     if not args.no_graph:
