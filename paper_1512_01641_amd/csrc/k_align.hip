@@ -269,8 +269,9 @@ static __device__ __forceinline__ void run8(StripState &st, const float4 *sv, co
 #define NWM_NEXT(k, p, u, v, A)                                                                              \
   NWM_STEP(k, "%[h" p "]", "%[b" p "]", u, A, NWM_CMP("u" v, "%[h" p "]"), NWM_ADDC("U"),                    \
            NWM_CMP("l" v, "%[h" p "]"))
-#define NWM_LAST                                                                           \
-  NWM_ADDC("L") NWM_CMP("u1", "%[h7]") "v_cmp_eq_f32_e64 %[m], %[l1], %[h7]\n\ts_nop 0\n\t" \
+// (two wait states between a compare and the add-with-carry that takes it)
+#define NWM_LAST                                                                                    \
+  "v_cmp_eq_f32_e64 %[m], %[l1], %[h7]\n\t" NWM_ADDC("L") NWM_CMP("u1", "%[h7]") "s_nop 1\n\t" \
   NWM_ADDC("U") "v_addc_co_u32_e64 %[L], %[m], %[L], %[L], %[m]"
 // lanes past lane t keep H
 #define NWM_KEEP(k, Hp, T) "s_bfm_b64 %[m], " T "+%[t], 0\n\tv_cndmask_b32_e64 %[h" k "], " Hp ", %[h" k "], %[m]\n\t"
@@ -303,7 +304,7 @@ static __device__ __forceinline__ void run8_chain(StripState &st, const float4 *
                  NWM_NEXT("5", "4", "1", "0", NWM_ADDC("L")) NWM_KEEP("5", "%[h4]", "6")
                  NWM_NEXT("6", "5", "0", "1", NWM_ADDC("L")) NWM_KEEP("6", "%[h5]", "7")
                  NWM_NEXT("7", "6", "1", "0", NWM_ADDC("L"))
-                 ".if %[t]+8 < 64\n\t" NWM_KEEP("7", "%[h6]", "8") ".endif\n\t" "s_nop 0\n\t" NWM_LAST NWM_OPERANDS);
+                 ".if %[t]+8 < 64\n\t" NWM_KEEP("7", "%[h6]", "8") ".endif\n\t" NWM_LAST NWM_OPERANDS);
   }
 #undef NWM_OPERANDS
   st.H = hs[7];
