@@ -1,0 +1,70 @@
+"""The scoring kernels' own sources on the host wave machine, under the address
+and undefined-behaviour sanitizers, against the FP64 oracle: the batches of
+test_gpu_sparse.py (list lengths around the sorting network and past it, repeated
+words, a vocabulary larger than the table, runs of column tiles), parts of one
+batch by different contractions, and plans drawn at random."""
+import numpy as np
+import pytest
+
+import oracle
+from tests import helpers as H
+from tests import host_machine as M
+from tests.test_gpu_sparse import CASES, _batch
+
+
+@pytest.fixture(scope="session")
+def program(tmp_path_factory):
+    return M.build(tmp_path_factory.mktemp("host"))
+
+
+def _bits(x):
+    return x.view(np.uint32)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_contractions_in_bounds(program, case, prec):
+    b = CASES[case]()
+    two = M.run(program, b, prec=prec, params={"expand_fused": 0}, apart=True)
+    if prec == 0 or case != "table":
+        assert two["launches"]["merge"] > 0 and two["launches"]["build_a"] == 0   # the sparse route ran
+    one = M.run(program, b, prec=prec, passes=2)
+    np.testing.assert_array_equal(_bits(one["S"]), _bits(two["S"]))
+    np.testing.assert_array_equal(_bits(one["S_raw"]), _bits(two["S_raw"]))
+    quiet = M.run(program, b, prec=prec, raw=False)
+    np.testing.assert_array_equal(_bits(quiet["S"]), _bits(one["S"]))
+    ora = oracle.score(b)
+    if prec == 0:
+        assert H.s_rel_err(one["S"], ora["S64"]).max() <= 1e-5
+    else:
+        assert np.abs(one["S"].astype(np.float64) - ora["S64"]).max() <= 2e-2
+    if case != "runs":   # (a minute on this machine)
+        dense = M.run(program, b, prec=prec, params={"score_compact": 0})
+        if prec == 0:   # the same sums in the same order
+            np.testing.assert_array_equal(_bits(one["S_raw"]), _bits(dense["S_raw"]))
+
+
+def test_parts_by_different_contractions_in_bounds(program):
+    # a long pair (summed) among short ones (BF16 operands: dense tiles)
+    b = _batch([200] + [20, 40, 64] * 4, [700] + [25, 64, 33] * 4, 2048, [5, 22, 40], [5, 22, 40])
+    ora = oracle.score(b)
+    one = M.run(program, b, prec=1, params={"expand_fused": 0}, apart=True, split=64)
+    assert one["launches"]["build_a"] > 0 and one["launches"]["build_a"] < one["launches"]["merge"]
+    assert np.abs(one["S"].astype(np.float64) - ora["S64"]).max() <= 2e-2
+    mined = M.run(program, b, op="mine", prec=1, passes=2, split=64)
+    np.testing.assert_array_equal(_bits(mined["S"]), _bits(one["S"]))
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_drawn_plans_in_bounds(program, seed):
+    rng = np.random.default_rng([41, seed])
+    pairs = int(rng.integers(1, 7))
+    n = rng.integers(0, 90, pairs)
+    m = rng.integers(0, 150, pairs)
+    n[0], m[0] = rng.integers(1, 300), rng.integers(1, 300)
+    b = _batch(n, m, int(rng.integers(4, 20000)), rng.integers(0, 49, 7), rng.integers(0, [50, 130][seed % 2], 9), seed=seed)
+    prec = seed // 2 % 2
+    S = oracle.score(b)["S64"]
+    for params in ({}, {"expand_fused": 0}):
+        got = M.run(program, b, op=("score", "mine")[seed // 3], prec=prec, params=params)["S"]
+        assert np.abs(got.astype(np.float64) - S).max(initial=0.0) <= (2e-2 if prec else 1e-5)
