@@ -67,6 +67,10 @@ __global__ __launch_bounds__(256) void k_bwd_dense(PlanDev P, const int64_t *__r
   const int pair = P.rt_pair[rt];
   const int row0 = P.rt_row0[rt], rows = P.rt_rows[rt];
   const int m = P.m[pair];
+  if (m == 0) {   // an empty target side: no cells (and nothing to divide by)
+    if (threadIdx.x < 3) part[4 * rt + threadIdx.x] = 0.0f;
+    return;
+  }
   const int64_t s_first = P.sfirst[pair] + row0;
   const int64_t t_first = P.tfirst[pair];
   const int64_t base = P.s_off[pair] + (int64_t)row0 * m;

@@ -68,3 +68,22 @@ def test_drawn_plans_in_bounds(program, seed):
     for params in ({}, {"expand_fused": 0}):
         got = M.run(program, b, op=("score", "mine")[seed // 3], prec=prec, params=params)["S"]
         assert np.abs(got.astype(np.float64) - S).max(initial=0.0) <= (2e-2 if prec else 1e-5)
+
+
+@pytest.mark.parametrize("n,m", [([5, 70], [0, 20]), ([3], [0]), ([130, 0, 64], [1, 9, 300])])
+def test_dense_backward_in_bounds(program, n, m):
+    # pairs with an empty side; one column; lengths past a row tile
+    rng = np.random.default_rng([43, len(n)])
+    b = _batch(n, m, 50, [4, 0, 9], [1, 0, 12], seed=5)
+    cells = int(np.dot(n, m))
+    S, S_raw, E = rng.random(cells), rng.random(cells), rng.standard_normal(cells)
+    S, S_raw, E = (x.astype(np.float32) for x in (S, S_raw, E))
+    got = M.run(program, b, op="backward", E=E, S=S, S_raw=S_raw)
+    np.testing.assert_array_equal(_bits(got["S"]), _bits(E))   # (the gradient of S)
+    o = oracle.score(b)
+    e, s = E.astype(np.float64), S.astype(np.float64)
+    dz = e * s * (1.0 - s)
+    ref = np.array([(dz * S_raw).sum(), (dz * o["rho"]).sum(), dz.sum()])
+    # FP32 sums of at most `cells` terms, each below 2^-2 * |E|
+    tol = 2.0 ** -24 * (64 + np.ceil(cells / 256)) * np.abs(e).sum() / 4
+    assert np.abs(got["grad_wb"] - ref).max() <= tol
