@@ -62,7 +62,12 @@ constexpr int CHUNK = 16;             // steps per chunk
 constexpr int GROUP = 64;             // steps per S staging group (four chunks)
 constexpr int GROUP_BYTES = 64 * GROUP * 4;   // LDS bytes per group (64 rows x 256 bytes)
 constexpr int RING_GROUPS = 2;        // groups in a strip's S ring: one in flight while one is read
-constexpr int SPIN_LIMIT = 1 << 22;   // default polls before a wave gives up (error flag)
+constexpr int SPIN_LIMIT = 1 << 22;   // default polls before a wave gives up (error flag): of a row in memory
+// LDS_POLLS polls of an LDS count count as one poll of the limit: one takes 0.11
+// us, a poll of a row in memory 0.17 (the fill that stages S in registers) to
+// 0.27 (a row wave).  So a strip waits for a row in LDS no shorter than the row
+// waves wait for one in memory (4000 polls: 1.7 ms, 0.4 counted singly).
+constexpr uint32_t LDS_POLLS = 4;
 constexpr uint32_t TAG_FAIL = 2u;     // tag of a boundary value whose producer gave up
 
 static __device__ __forceinline__ float dpp_shr1(float old, float src) {
@@ -551,6 +556,7 @@ __global__ __launch_bounds__(64 * (SLOTS + FILL_HELPERS)) void k_nw_fill(
           __builtin_amdgcn_make_buffer_rsrc((void *)uniform_ptr(row), (short)0, uniform(8 * (m + 1)), 0x00020000);
       const float *ring = rows_lds + SLOTS * LINK_COLS;
       int at = 0;
+      uint32_t poll = 0;
       for (int spins = 0; at < m;) {
         const int have = min(count(&put[SLOTS]), m);
         if (have > at) {
@@ -562,7 +568,7 @@ __global__ __launch_bounds__(64 * (SLOTS + FILL_HELPERS)) void k_nw_fill(
           at += n;
           set_count(&taken[SLOTS], at);
           spins = 0;
-        } else if (have < 0 || ++spins > (A.spin_limit > SPIN_LIMIT ? A.spin_limit : SPIN_LIMIT)) {
+        } else if (spins += ++poll % LDS_POLLS == 0, have < 0 || spins > std::max(A.spin_limit, SPIN_LIMIT)) {
           // the strip gave up: the one below must not wait for values that
           // will never come
           for (int j = at + 1 + lane; j <= m; j += 64)
@@ -660,12 +666,14 @@ __global__ __launch_bounds__(64 * (SLOTS + FILL_HELPERS)) void k_nw_fill(
     // until the row above has `need` columns, or its writer gave up, or the
     // poll limit passed
     auto wait_in = [&](int need) {
+      int spins = 0;
 #pragma nounroll
-      for (int spins = 0;; ++spins) {
-        if (spins > 4) __builtin_amdgcn_s_sleep(1);
+      for (uint32_t poll = 1;; ++poll) {
+        if (poll > 5) __builtin_amdgcn_s_sleep(1);
         read_have();
         const int have = uniform(in_have);
         if (have >= need) break;
+        spins += poll % LDS_POLLS == 0;
         if (have < 0 || spins > A.spin_limit) {
           give_up();
           break;
@@ -675,13 +683,15 @@ __global__ __launch_bounds__(64 * (SLOTS + FILL_HELPERS)) void k_nw_fill(
     // until the row ring below has room for columns up to `col` (columns past
     // m too: its reader runs on past them)
     auto wait_out = [&](int col) {
+      int spins = 0;
 #pragma nounroll
-      for (int spins = 0; col > out_free; ++spins) {
+      for (uint32_t poll = 1; col > out_free; ++poll) {
+        spins += poll % LDS_POLLS == 0;
         if (spins > SPIN_LIMIT) {
           give_up();
           break;
         }
-        if (spins > 0) __builtin_amdgcn_s_sleep(1);
+        if (poll > 1) __builtin_amdgcn_s_sleep(1);
         const int tk = count(&taken[wave + 1]);
         out_free = tk == ALL_COLS ? tk : tk + LINK_COLS;
       }
