@@ -88,6 +88,7 @@ template <int OUT>
 struct MergeOut {
   int64_t base, id;
   int n;   // merged entries (-1: nothing to store)
+  bool odd;   // the lane holds a value that is not finite (see ROW_ODD)
   uint2 v[OUT];
 };
 constexpr uint32_t BUF_OOB = 0xFFFFFFF0u;
@@ -262,7 +263,7 @@ __global__ __launch_bounds__(64) void k_merge_src(int64_t n_sent, const int64_t 
                                             0);
     const __amdgpu_buffer_rsrc_t r_c =
         __builtin_amdgcn_make_buffer_rsrc((void *)(cnt + id), (short)0, n_rec >= 0 ? 4 : 0, 0x00020000);
-    __builtin_amdgcn_raw_buffer_store_b32(n_rec, r_c, (uint32_t)lane * 4u, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(n_rec | (__ballot(M.odd) != 0ull ? ROW_ODD : 0), r_c, (uint32_t)lane * 4u, 0, 0);
   };
 
   int nuniq = 0;
@@ -279,6 +280,7 @@ __global__ __launch_bounds__(64) void k_merge_src(int64_t n_sent, const int64_t 
   MergeOut<OUT> out;
   out.base = out.id = 0;
   out.n = -1;
+  out.odd = false;
 #pragma unroll
   for (int r = 0; r < OUT; ++r) out.v[r] = make_uint2(0u, 0u);
   for (; sent < n_sent; sent += G) {
@@ -344,6 +346,7 @@ __global__ __launch_bounds__(64) void k_merge_src(int64_t n_sent, const int64_t 
     out.base = cur.t0 * (int64_t)max_deg;
     out.id = cur.id;
     out.n = nuniq;
+    out.odd = false;
 #pragma unroll
     for (int r = 0; r < OUT; ++r) {
       const int e = lane + 64 * r;
@@ -355,10 +358,13 @@ __global__ __launch_bounds__(64) void k_merge_src(int64_t n_sent, const int64_t 
         acc[h] = 0.0;
       }
       out.v[r] = v;
+      out.odd |= odd_bf16(v.y);
     }
     for (int e = 64 * OUT + lane; e < nuniq; e += 64) {
       const int h = slots[e];
-      merged[out.base + e] = make_uint2(key[h], __float_as_uint((float)acc[h]));
+      const uint2 v = make_uint2(key[h], __float_as_uint((float)acc[h]));
+      merged[out.base + e] = v;
+      out.odd |= odd_bf16(v.y);
       key[h] = HEMPTY;
       acc[h] = 0.0;
     }
@@ -448,7 +454,7 @@ __global__ __launch_bounds__(256) void k_build_a(PlanDev P, const int64_t *__res
   const int64_t srow = s0 + (vrow ? myrow : 0);
   const int rc_ld = cnt[srow];
   const int64_t rb = src_off[srow] * (int64_t)P.max_deg;
-  const int rc = vrow ? rc_ld : 0;
+  const int rc = vrow ? rc_ld & ROW_COUNT : 0;
   auto row_cnt = [&](int k) { return __builtin_amdgcn_readlane(rc, k); };
   auto row_base = [&](int k) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)rb, k);
@@ -774,6 +780,7 @@ __global__ __launch_bounds__(64 * EXA_WAVES) void k_expand_a(PlanDev P, const in
       const __amdgpu_buffer_rsrc_t r_m = __builtin_amdgcn_make_buffer_rsrc(
           (void *)(merged + (int64_t)(((uint64_t)hi << 32) | lo) * P.max_deg), (short)0, 0x7FFFFFFF, 0x00020000);
       int n = 0;
+      bool odd = false;
 #pragma unroll
       for (int r = 0; r < MERGE_ROUNDS; ++r) {
         const bool ok = out[k][r].x != HEMPTY;
@@ -783,7 +790,9 @@ __global__ __launch_bounds__(64 * EXA_WAVES) void k_expand_a(PlanDev P, const in
         __builtin_amdgcn_raw_buffer_store_b64((m_u32x2){out[k][r].x, out[k][r].y}, r_m,
                                               ok ? (uint32_t)pos * 8u : BUF_OOB, 0, 0);
         n += (int)__popcll(bm);
+        odd |= odd_bf16(out[k][r].y);   // (0 without an entry)
       }
+      n |= __ballot(odd) != 0ull ? ROW_ODD : 0;
       if (lane == 0) mcnt[s0 + row] = n;
     }
     return;

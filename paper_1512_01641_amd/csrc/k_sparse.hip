@@ -298,9 +298,9 @@ __global__ __launch_bounds__(64 * WAVES, 4) void k_score_s(PlanDev P, const int6
   const int myrow = wave + WAVES * lane;
   const bool vrow = lane < RPW && myrow < g.rows;
   const int64_t srow = g.s_first + (vrow ? myrow : 0);
-  const int rc_ld = mcnt[srow];
+  const int rc_ld = mcnt[srow], tile_ld = BF16 ? mcnt[g.s_first + min(lane, g.rows - 1)] : 0;
   const int64_t rb = src_off[srow] * (int64_t)P.max_deg;
-  const int rc = vrow ? rc_ld : 0;
+  const int rc = vrow ? rc_ld & ROW_COUNT : 0;
   auto row_cnt = [&](int k) { return __builtin_amdgcn_readlane(rc, k); };
   auto row_base = [&](int k) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)rb, k);
@@ -330,10 +330,18 @@ __global__ __launch_bounds__(64 * WAVES, 4) void k_score_s(PlanDev P, const int6
     rlen[tid] = (float)(src_off[x + 1] - src_off[x]);
   }
   __syncthreads();
+  // (BF16) rows with an operand that is not finite: the sums take 0 x every
+  // other row of a line, so such a row stands alone, its neighbours' sums going
+  // nowhere
+  const uint32_t odd = BF16 ? (uint32_t)__ballot((tile_ld & ROW_ODD) != 0) & ((1u << g.rows) - 1u) : 0u;
   // all rows at once unless their vocabulary exceeds the table (then fewer at
-  // a time; one row always fits)
+  // a time; one row always fits) or some stand alone
   int rs = 0, re = g.rows;
   while (rs < g.rows) {
+    if (odd != 0u) {
+      const uint32_t after = odd >> rs;
+      re = min(re, (after & 1u) ? rs + 1 : after ? rs + __builtin_ctz(after) : re);
+    }
     // the first 64 EREG entries of every row of this wave, loaded together
     uint2 e[RPW][EREG];
 #pragma unroll

@@ -38,6 +38,10 @@ constexpr int SROWS = 16;
 constexpr int SCOLS = 32;
 
 // ---- dictionary-row merge ---------------------------------------------------
+// A merged row's count carries ROW_ODD where a value of the row is infinite or
+// NaN once rounded to BF16.
+constexpr int32_t ROW_ODD = 1 << 30, ROW_COUNT = ROW_ODD - 1;
+__host__ __device__ inline bool odd_bf16(uint32_t bits) { return (bits << 1) >= 2u * 0x7F7F8000u; }
 constexpr int MERGE_SLOTS = 1024;     // bound on tokens x max_deg per source sentence
 constexpr int MAX_V = 32768;          // vocabulary bound (LDS tables of V / 32 words per tile)
 constexpr int MAX_DEG = 64;           // dictionary entries per word

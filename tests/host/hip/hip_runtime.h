@@ -125,6 +125,7 @@ template <typename T> static inline T atomicAdd(T *p, std::common_type_t<T> v) {
 static inline uint32_t atomicOr(uint32_t *p, uint32_t v) { uint32_t o = *p; *p = o | v; return o; }
 static inline uint32_t atomicCAS(uint32_t *p, uint32_t c, uint32_t v) { uint32_t o = *p; if (o == c) *p = v; return o; }
 #define __syncthreads() wave::sync_block()
+#define __threadfence() ((void)0)
 #define __builtin_amdgcn_fence(...) ((void)0)
 #define __builtin_amdgcn_wave_barrier() wave::sync_wave("barrier", __LINE__)
 #define __builtin_amdgcn_sched_barrier(...) ((void)0)

@@ -87,3 +87,50 @@ def test_dense_backward_in_bounds(program, n, m):
     # FP32 sums of at most `cells` terms, each below 2^-2 * |E|
     tol = 2.0 ** -24 * (64 + np.ceil(cells / 256)) * np.abs(e).sum() / 4
     assert np.abs(got["grad_wb"] - ref).max() <= tol
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("m", [130, 600])   # a workgroup or a wave per tile
+def test_values_that_are_not_finite_stay_in_their_cells(program, prec, m):
+    """A dictionary value that is infinite, NaN or (BF16) rounds to infinity
+    reaches the cells whose source sentence brings it and whose target sentence
+    holds its word, and no other."""
+    import dataclasses
+    b = _batch([21], [m], 300, [3, 1, 0, 12, 40], [5, 33, 0, 70], seed=6)
+    bad = np.arange(0, len(b.d_val), 37)
+    val = b.d_val.copy()
+    val[bad] = np.resize(np.array([np.inf, 3.4e38, np.nan, -np.inf, -3.4e38], np.float32), len(bad))
+    if prec == 0:
+        val[np.abs(val) == np.float32(3.4e38)] = np.inf
+    zero = b.d_val.copy()
+    zero[bad] = 0.0
+    got = M.run(program, dataclasses.replace(b, d_val=val), prec=prec)
+    fin = M.run(program, dataclasses.replace(b, d_val=zero), prec=prec)
+    # merged rows in FP64, rounded to FP32; which are not finite as operands
+    T = np.zeros((21, b.V))
+    with np.errstate(invalid="ignore", over="ignore"):
+        for i in range(21):
+            for t in b.src_tok[b.src_off[i]:b.src_off[i + 1]]:
+                e = slice(b.d_row_off[t], b.d_row_off[t + 1])
+                np.add.at(T[i], b.d_col[e], val[e].astype(np.float64))
+        T = T.astype(np.float32)
+        if prec == 1:
+            T[np.abs(T) > 3.3895e38] *= np.float32(10.0)   # (rounds up to infinity)
+        ls, lt = np.diff(b.src_off), np.diff(b.tgt_off)
+        hit = np.zeros((21, m), bool)
+        dot = np.zeros((21, m))
+        for j in range(m):
+            u = np.unique(b.tgt_tok[b.tgt_off[j]:b.tgt_off[j + 1]])
+            odd = ~np.isfinite(T[:, u])
+            hit[:, j] = odd.any(1)
+            dot[:, j] = np.where(odd, T[:, u], 0.0).sum(1)
+        hi, lo = np.maximum(ls[:, None], lt), np.minimum(ls[:, None], lt)
+        rho = np.where(hi > 0, lo / np.maximum(hi, 1), 1.0)
+        z = b.scorer[0] * dot + b.scorer[1] * rho + b.scorer[2]
+        S = 1.0 / (1.0 + np.exp(-z))
+    assert hit.any() and not hit.all()
+    raw, s = got["S_raw"].reshape(21, m), got["S"].reshape(21, m)
+    np.testing.assert_array_equal(raw[hit], dot[hit].astype(np.float32))
+    np.testing.assert_array_equal(s[hit], S[hit].astype(np.float32))
+    np.testing.assert_array_equal(_bits(raw[~hit]), _bits(fin["S_raw"].reshape(21, m)[~hit]))
+    np.testing.assert_array_equal(_bits(s[~hit]), _bits(fin["S"].reshape(21, m)[~hit]))
