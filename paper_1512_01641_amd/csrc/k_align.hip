@@ -961,8 +961,8 @@ __global__ __launch_bounds__(64) void k_nw_fill_r(FillArgs A, const float *__res
 // bottom row that the path may enter it at (MAP_COLS steps around the line from
 // (0, 0) to (n, m)) and keeps where each leaves it and after how many DIAG
 // steps; k_nw_walk_chain composes these maps from the bottom strip up, one
-// lookup per strip (a strip the path enters outside its map is climbed on the
-// spot); k_nw_walk then climbs each strip from its known entry and writes its
+// lookup per strip (strips the path enters outside their maps are climbed on the
+// spot, several at once); k_nw_walk then climbs each strip from its known entry and writes its
 // aligned pairs at their known place.  The other pairs (chains no longer than
 // the three launches) are walked strip by strip by one wave of k_nw_walk.  The
 // maps and entries lie in the pair's published boundary rows, which are done
@@ -970,8 +970,8 @@ __global__ __launch_bounds__(64) void k_nw_fill_r(FillArgs A, const float *__res
 // n_s - 1 of them, one for each strip but the bottom one, whose entry is known.
 // Measured (us, all launches; one wave per pair before): six pairs of about 3000
 // sentences 420 -> 43, 100 pairs of 20 to 2000 160 -> 40, 64 pairs of 5000 394
-// -> 101; a pair of 6400 x 200 whose path runs far off the line, so that no map
-// holds it, 91 -> 247.
+// -> 101; far off the line: 5000 x 3000 with a preface of 2000 86 -> 78, with an
+// appendix of 2000 99 -> 111, 6400 x 400 along a side 118 -> 116.
 constexpr int MAP_COLS = 256;               // entry steps a strip's map covers
 constexpr int MAP_BLOCKS = 2 * MAP_COLS / 64;   // blocks of directions it may read: as many steps to the left again
 constexpr int WALK_BLOCKS = 5;              // blocks one climbing wave holds
@@ -980,10 +980,14 @@ constexpr uint32_t MAP_END = 0x80000000u;   // the path ends in the strip (| DIA
 // else (step of the strip above) << 7 | DIAG steps
 static_assert(8 * BND_PAD >= 4 * MAP_COLS + 32, "a strip's map, its entry and the bottom strip's exit fit a boundary row");
 
-// first step of strip s's map (s above the bottom strip): a multiple of 64
+// first step of strip s's map (s above the bottom strip): a multiple of 64.  The
+// path enters at steps 63 .. m + 62, so the map ends no later than it has to
+// and starts at 64 rather than 0 where it can: up to 193 columns it holds all
+// of them, up to 257 all but the first.
 static __device__ __forceinline__ int map_base(int s, int n, int m) {
   const int t = (int)((int64_t)m * (64 * s + 64) / n) + 62;
-  return max(0, (t - MAP_COLS / 2 + 32) >> 6 << 6);
+  const int last = max(0, (m + 62 - MAP_COLS + 64) & ~63);
+  return min(max((t - MAP_COLS / 2 + 32) & ~63, 64), last);
 }
 
 // strip s's boundary row as 32-bit words: the map, then {step, pairs before it}
@@ -1006,10 +1010,37 @@ static __device__ __forceinline__ RowMasks row_masks(const uint4 &w, int G, int 
   return {u | ~l | col0, u | col0};
 }
 
-// One workgroup per strip, one lane per entry step.  Bound by the lookups'
-// latency: one 16-byte LDS read and some 20 instructions per row.  A lane that
-// leaves the blocks held goes on over block g0 and is dropped at the end (its
-// step only decreases).
+// Every lane of the wave climbs one strip from step t of row r0, over the blocks
+// from step t0 on held in wnd (t lies in them); returns what a map holds.  Bound
+// by the lookups' latency: one 16-byte LDS read and some 20 instructions per row.
+// A lane that leaves the blocks held goes on over the first and is dropped at
+// the end (its step only decreases).
+static __device__ __forceinline__ uint32_t climb_lanes(const RowMasks *wnd, int t0, int r0, int t) {
+  int cnt = 0;
+  bool ended = false;
+  for (int r = r0; r >= 0; --r) {
+    uint64_t x, u;
+    for (;;) {
+      const RowMasks w = wnd[(max(t - t0, 0) >> 6) * 64 + r];
+      const int q = ~t & 63;
+      x = w.nl >> q, u = w.u >> q;
+      // LEFT past the first step of the block, in any lane: on in the block
+      // before it (the other lanes look the same masks up again)
+      const bool on = x == 0ull && t >= t0;
+      if (__ballot(on) == 0ull) break;
+      if (on) t = (t & ~63) - 1;
+    }
+    // (only in row 0: column 0 is step -1 there, and no mask has it)
+    ended = t < 0;
+    const int k = __builtin_ctzll(x | (1ull << 63));
+    const int diag = 1 - (int)((u >> k) & 1ull);
+    if (!ended) t -= k + 1 + diag, cnt += diag;
+  }
+  if (t < t0 && t0 > 0) return MAP_NONE;
+  return ended ? MAP_END | (uint32_t)cnt : (uint32_t)(t + 64) << 7 | (uint32_t)cnt;
+}
+
+// One workgroup per strip, one lane per entry step.
 __global__ __launch_bounds__(MAP_COLS) void k_nw_walk_map(PlanDev P, const char *__restrict__ tb_bits,
                                                           const float *__restrict__ score, uint64_t *__restrict__ bnd,
                                                           int k0) {
@@ -1030,29 +1061,7 @@ __global__ __launch_bounds__(MAP_COLS) void k_nw_walk_map(PlanDev P, const char 
     wnd[k] = row_masks(tbs[(int64_t)G * 64 + (k & 63)], G, k & 63);
   }
   __syncthreads();
-  const int t0 = 64 * g0;
-  int t = bottom ? t_last : min(w0 + (int)threadIdx.x, t_last), cnt = 0;
-  bool ended = false;
-  for (int r = r0; r >= 0; --r) {
-    uint64_t x, u;
-    for (;;) {
-      const RowMasks w = wnd[(max(t - t0, 0) >> 6) * 64 + r];
-      const int q = ~t & 63;
-      x = w.nl >> q, u = w.u >> q;
-      // LEFT past the first step of the block, in any lane: on in the block
-      // before it (the other lanes look the same masks up again)
-      const bool on = x == 0ull && t >= t0;
-      if (__ballot(on) == 0ull) break;
-      if (on) t = (t & ~63) - 1;
-    }
-    // (only in row 0: column 0 is step -1 there, and no mask has it)
-    ended = t < 0;
-    const int k = __builtin_ctzll(x | (1ull << 63));
-    const int diag = 1 - (int)((u >> k) & 1ull);
-    if (!ended) t -= k + 1 + diag, cnt += diag;
-  }
-  uint32_t out = ended ? MAP_END | (uint32_t)cnt : (uint32_t)(t + 64) << 7 | (uint32_t)cnt;
-  if (t < t0 && t0 > 0) out = MAP_NONE;
+  const uint32_t out = climb_lanes(wnd, 64 * g0, r0, bottom ? t_last : min(w0 + (int)threadIdx.x, t_last));
   if (!bottom) map_row(P, bnd, b, m, s)[threadIdx.x] = w0 + (int)threadIdx.x > t_last ? MAP_NONE : out;
   else if (threadIdx.x == 0) map_row(P, bnd, b, m, nS - 2)[MAP_BOTTOM] = out;
 }
@@ -1144,25 +1153,70 @@ static __device__ __forceinline__ void emit_strip(int2 *__restrict__ pa, int cap
   if (q < cap) pa[cap - 1 - q] = make_int2(64 * s + lane, cell - lane);
 }
 
-// One wave per pair, one lookup per strip; the maps come into LDS
-// CHAIN_AHEAD strips ahead, the entries leave 64 strips at a time.
+// One workgroup per pair; its first wave looks one strip up after another, in the
+// maps, which come into LDS CHAIN_AHEAD strips ahead; the entries leave 64
+// strips at a time.  Where the path is off the maps (a preface without a
+// counterpart shifts it by the preface's length) all waves climb ahead: wave w
+// climbs w strips up, from the 64 entry steps around where the path comes if it
+// goes on as in the strip before, and the first wave follows the path through
+// these for as far as they hold it.  Without this the strips were climbed one
+// by one, 3.7 us each (5000 x 3000 sentences with a preface of 2000, the whole
+// traceback: 78 us, 237 so and 86 by one wave in LDS; a pair on the line 37).
 constexpr int CHAIN_AHEAD = 16;
-__global__ __launch_bounds__(64) void k_nw_walk_chain(PlanDev P, const char *__restrict__ tb_bits,
+constexpr int AHEAD_BLOCKS = 4;   // blocks held of a strip climbed ahead
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_nw_walk_chain(PlanDev P, const char *__restrict__ tb_bits,
                                                       const float *__restrict__ score, uint64_t *__restrict__ bnd,
                                                       int32_t *__restrict__ n_diag, int k0) {
   __shared__ __align__(16) uint32_t maps[CHAIN_AHEAD * MAP_COLS];
-  __shared__ uint4 wnd[WALK_BLOCKS * 64];
-  const int lane = threadIdx.x;
+  // climbing ahead, then its results (each wave's over the blocks it held); or
+  // the strip that wave 0 climbs alone
+  __shared__ RowMasks held[WAVES][AHEAD_BLOCKS * 64];
+  __shared__ int order[3];   // strip (-1: no more), entry step, how far the entry moves per strip
+  const int wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int b = uniform(P.wp_pair[k0 + blockIdx.x]);
   if (__builtin_isnan(score[b])) {   // a fill that gave up: no aligned pairs
-    if (lane == 0) n_diag[b] = 0;
+    if (threadIdx.x == 0) n_diag[b] = 0;
     return;
   }
   const int n = uniform(P.n[b]), m = uniform(P.m[b]);
   const int nS = (n + 63) >> 6, nG = (m + 63 + 63) >> 6;
   const uint4 *tbw = reinterpret_cast<const uint4 *>(tb_bits + P.tb_off[b]);
+  // first entry step of the strip w above strip s, entered at step t
+  auto ahead_base = [&](int w, int t, int move) { return min(max(t - w * move - 32, 0), max(m + 62 - 63, 0)); };
+  auto climb_ahead = [&](int s, int t, int move) {
+    const int strip = s - wave;
+    if (strip < 0) return;
+    const int first = ahead_base(wave, t, move);
+    const int g0 = max(((first + 63) >> 6) - (AHEAD_BLOCKS - 1), 0);
+    const uint4 *tbs = tbw + (int64_t)strip * nG * 64;
+    uint4 w[AHEAD_BLOCKS];
+#pragma unroll
+    for (int k = 0; k < AHEAD_BLOCKS; ++k) w[k] = tbs[(int64_t)min(g0 + k, nG - 1) * 64 + lane];
+    RowMasks *mine = held[wave];
+#pragma unroll
+    for (int k = 0; k < AHEAD_BLOCKS; ++k) mine[64 * k + lane] = row_masks(w[k], g0 + k, lane);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int t_in = first + lane;
+    uint32_t out = climb_lanes(mine, 64 * g0, 63, min(t_in, m + 62));
+    if (t_in > m + 62) out = MAP_NONE;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    reinterpret_cast<uint32_t *>(mine)[lane] = out;
+  };
+  if (wave > 0) {   // climbs when wave 0 says so
+    for (;;) {
+      __syncthreads();
+      const int s = order[0], t = order[1], move = order[2];
+      if (s < 0) return;
+      climb_ahead(s, t, move);
+      __syncthreads();
+    }
+  }
   uint32_t *rows = uniform_ptr(map_row(P, bnd, b, m, 0));
   const int64_t stride = 2 * bnd_stride(m);   // words per row
+  uint4 *const wnd = reinterpret_cast<uint4 *>(held);
   uint32_t out = (uint32_t)uniform((int)rows[(int64_t)(nS - 2) * stride + MAP_BOTTOM]);
   int cell;
   if (out == MAP_NONE)
@@ -1174,6 +1228,32 @@ __global__ __launch_bounds__(64) void k_nw_walk_chain(PlanDev P, const char *__r
     if (s > 0) next -= stride / 4;
   };
   for (int k = 0; k < CHAIN_AHEAD; ++k) load(nS - 2 - k);
+  int climbed = -1, c_t = 0, c_move = 0;   // the strips climbed ahead: from this one up
+  int t_below = -1;                        // entry of the strip below s1
+  // strip s entered at step t, outside its map
+  auto off_map = [&](int s, int t, int below) {
+    auto look = [&]() {
+      const int w = climbed - s, x = t - ahead_base(w, c_t, c_move);
+      if (climbed < 0 || w >= WAVES || (unsigned)x >= 64u) return MAP_NONE;
+      return (uint32_t)uniform((int)reinterpret_cast<const uint32_t *>(held[w])[x]);
+    };
+    uint32_t to = look();
+    if (to != MAP_NONE) return to;
+    // how far the entry moves per strip: as it just did
+    climbed = s, c_t = t, c_move = below < 0 ? 64 : below - t;
+    if (lane == 0) order[0] = s, order[1] = t, order[2] = c_move;
+    __syncthreads();
+    climb_ahead(s, t, c_move);
+    __syncthreads();
+    to = look();
+    if (to != MAP_NONE) return to;
+    climbed = -1;   // farther to the left than the blocks held: alone, in their space
+    to = climb_strip(tbw + (int64_t)s * nG * 64, wnd, 63, t, lane, cell);
+    // vmcnt(0) here, or the compiler puts it where the strips on their maps come
+    // by, and they wait for the maps ahead (14 -> 27 us for 79 strips)
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    return to;
+  };
   for (int s1 = nS - 2; s1 >= 0; s1 -= 64) {   // lane k: strip s1 - k
     const int base = map_base(max(s1 - lane, 0), n, m);
     int2 entry = make_int2(-1, 0);
@@ -1188,15 +1268,19 @@ __global__ __launch_bounds__(64) void k_nw_walk_chain(PlanDev P, const char *__r
       static_assert(CHAIN_AHEAD == 16, "the wait above");
       out = (uint32_t)uniform((int)maps[(s & (CHAIN_AHEAD - 1)) * MAP_COLS + (idx & (MAP_COLS - 1))]);
       if ((unsigned)idx >= (unsigned)MAP_COLS) out = MAP_NONE;
-      if (out == MAP_NONE) out = climb_strip(tbw + (int64_t)s * nG * 64, wnd, 63, t, lane, cell);
+      if (__builtin_expect(out == MAP_NONE, 0))
+        out = off_map(s, t, k > 0 ? __builtin_amdgcn_readlane(entry.x, max(k - 1, 0)) : t_below);
       before += (int)(out & 127u);
       load(s - CHAIN_AHEAD);
     }
+    t_below = __builtin_amdgcn_readlane(entry.x, 63);
     if (s1 - lane >= 0) *reinterpret_cast<int2 *>(rows + (int64_t)(s1 - lane) * stride + MAP_ENTRY) = entry;
   }
+  if (lane == 0) order[0] = -1;
   // no LDS-direct load may still be writing LDS when the wave ends
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if (lane == 0) n_diag[b] = before;
+  __syncthreads();
 }
 
 // One wave per strip of the longer pairs (blocks below n_strips), then one per
@@ -1465,7 +1549,12 @@ hipError_t launch_nw_walk(const PlanDev &P, const char *tb, const float *score, 
   if (n <= 0) return hipSuccess;
   if (nq > 0) {
     hipLaunchKernelGGL(k_nw_walk_map, dim3(nk), dim3(MAP_COLS), 0, st, P, tb, score, bnd, k0);
-    hipLaunchKernelGGL(k_nw_walk_chain, dim3(nq), dim3(64), 0, st, P, tb, score, bnd, n_diag, q0);
+    // sixteen waves' blocks leave room for one workgroup per compute unit, eight
+    // waves' for three
+    if (nq <= g_fill_cus)
+      hipLaunchKernelGGL(k_nw_walk_chain<16>, dim3(nq), dim3(64 * 16), 0, st, P, tb, score, bnd, n_diag, q0);
+    else
+      hipLaunchKernelGGL(k_nw_walk_chain<8>, dim3(nq), dim3(64 * 8), 0, st, P, tb, score, bnd, n_diag, q0);
   }
   // (with no other pairs in the range, the strips alone)
   hipLaunchKernelGGL(k_nw_walk, dim3(nk + (nq < n ? n : 0)), dim3(64), 0, st, P, tb, score, bnd, path, n_diag, k0, nk,

@@ -128,6 +128,7 @@ static inline uint32_t atomicCAS(uint32_t *p, uint32_t c, uint32_t v) { uint32_t
 #define __threadfence() ((void)0)
 #define __builtin_amdgcn_fence(...) ((void)0)
 #define __builtin_amdgcn_wave_barrier() wave::sync_wave("barrier", __LINE__)
+#define __builtin_amdgcn_s_waitcnt(...) ((void)0)
 #define __builtin_amdgcn_sched_barrier(...) ((void)0)
 #define __builtin_amdgcn_sched_group_barrier(...) ((void)0)
 template <typename T> static inline T w_readlane(T x, int k, int line) { return wave::exchange(x, "readlane", line)[k & 63]; }

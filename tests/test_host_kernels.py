@@ -134,3 +134,45 @@ def test_values_that_are_not_finite_stay_in_their_cells(program, prec, m):
     np.testing.assert_array_equal(s[hit], S[hit].astype(np.float32))
     np.testing.assert_array_equal(_bits(raw[~hit]), _bits(fin["S_raw"].reshape(21, m)[~hit]))
     np.testing.assert_array_equal(_bits(s[~hit]), _bits(fin["S"].reshape(21, m)[~hit]))
+
+
+def _path_case(n, m, cells, rng):
+    """Similarities whose best path goes through the given cells."""
+    S = (rng.integers(0, 3, (n, m)) / 8.0).astype(np.float32)
+    for i, j in cells:
+        S[i, j] += 0.75
+    return S.ravel()
+
+
+def _diagonal(i, j, k):
+    return [(i + x, j + x) for x in range(k)]
+
+
+# paths of pairs walked by all their strips at once: on the line from corner to
+# corner, a preface or an appendix without a counterpart on either side, along a
+# side, in steps, and far to the left within one strip
+PATHS = {
+    "line": (640, 660, _diagonal(0, 0, 640)),
+    "preface": (1100, 500, _diagonal(600, 0, 500)),
+    "appendix": (1100, 500, _diagonal(0, 0, 500)),
+    "target preface": (560, 1400, _diagonal(0, 840, 560)),
+    "target appendix": (560, 1400, _diagonal(0, 0, 560)),
+    "side": (1500, 210, _diagonal(0, 0, 210)),
+    "steps": (1200, 1200, _diagonal(0, 0, 150) + _diagonal(150, 600, 300) + _diagonal(900, 900, 300)),
+    "left": (900, 3000, _diagonal(0, 0, 450) + _diagonal(450, 2550, 450)),
+    "narrow": (700, 3, _diagonal(300, 0, 3)),
+}
+
+
+@pytest.mark.parametrize("pairs", [1, 7])   # sixteen or eight strips climbed ahead
+def test_traceback_in_bounds(program, pairs):
+    rng = np.random.default_rng(47)
+    names = sorted(PATHS) if pairs > 1 else ["preface"]
+    ns = [PATHS[k][0] for k in names] + [70, 0, 5]
+    ms = [PATHS[k][1] for k in names] + [50, 9, 0]
+    S = np.concatenate([_path_case(*PATHS[k], rng) for k in names] + [rng.random(70 * 50).astype(np.float32)])
+    b = _batch(ns, ms, 10, [0], [0])
+    for threshold in (0.5, -1e30):
+        got = M.run(program, b, op="align", S=S, gap=-0.125, threshold=threshold, passes=2)
+        ora = oracle.align(ns, ms, S, -0.125, threshold)
+        H.assert_align_equal(got, ora, ns, ms, check_path_as_kept=threshold < 0)
