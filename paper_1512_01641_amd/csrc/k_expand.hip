@@ -1042,22 +1042,35 @@ size_t merge_lds_bytes(int hbits) {
   return hs * (sizeof(double) + sizeof(uint32_t)) + (size_t)merge_cap((int)hs) * sizeof(int);
 }
 
-// Sentences sent_ids[k0 .. k0 + n_sent).
+// Rounds of 16 tokens and entries per lane (of four lanes per token) loaded
+// ahead.  What a sentence or a dictionary row has past them is loaded where it
+// is merged, a memory latency per step; what is loaded ahead for nothing, and
+// the registers it takes, cost as well.  Measured (us, 30000 sentences, 3 x 1 /
+// 5 x 1 / 5 x 2 / 8 x 1 / 8 x 2, the chosen kind starred):
+//   5 to 48 tokens, 8 entries a row     66* /  73 /  76 /  82 / 103 (3 x 2: 67)
+//   10 to 80, 1 / 2                     40* /  42 /  53 /  53 /  74, 45* / 47 / 59 / 58 / 80
+//   10 to 80, 4                         65  /  55*/  63 /  64 /  86
+//   10 to 80, 8                        148  / 113 / 108*/ 117 / 152
+//   20 to 128, 3                        72* /  80 /  91 /  82 / 108
+//   20 to 128, 4                       100  /  95 /  98 /  82*/ 123
+//   20 to 128, 6                       180  / 174 / 173 / 164*/ 213
+//   60 to 128, 8                       525  / 481 / 457 / 408 / 380*
+//   20 to 200, 3                       121  / 117 / 123 / 120*/ 170
 template <typename F>
 static void merge_kernel(int max_sent_tokens, int max_deg, F &&go) {
-  const bool deep = max_deg > 4;
-  if (max_sent_tokens <= 48) {
-    if (deep) go(k_merge_src<3, 2>);
-    else go(k_merge_src<3, 1>);
-  } else if (max_sent_tokens <= 80) {
-    if (deep) go(k_merge_src<5, 2>);
-    else go(k_merge_src<5, 1>);
-  } else {
-    if (deep) go(k_merge_src<8, 2>);
-    else go(k_merge_src<8, 1>);
-  }
+  if (max_sent_tokens <= 48 || max_deg <= 2 || (max_sent_tokens > 80 && max_sent_tokens <= 128 && max_deg == 3))
+    go(k_merge_src<3, 1>);
+  else if (max_sent_tokens <= 80 && max_deg <= 4)
+    go(k_merge_src<5, 1>);
+  else if (max_sent_tokens <= 80)
+    go(k_merge_src<5, 2>);
+  else if (max_deg <= 6)
+    go(k_merge_src<8, 1>);
+  else
+    go(k_merge_src<8, 2>);
 }
 
+// Sentences sent_ids[k0 .. k0 + n_sent).
 hipError_t launch_merge_src(int64_t n_sent, const int64_t *sent_ids, int64_t k0, const int64_t *src_off,
                             const int32_t *src_tok, const int32_t *d_row_off, const int32_t *d_col,
                             const float *d_val, int V, int max_deg, int max_entries, int max_sent_tokens,
@@ -1079,11 +1092,6 @@ hipError_t launch_merge_src(int64_t n_sent, const int64_t *sent_ids, int64_t k0,
   if (waves_per_cu > 0 && waves_per_cu < per) per = waves_per_cu;
   const int64_t want = (int64_t)cus * per;
   const int grid = (int)(n_sent < want ? n_sent : want);
-  // Rounds of 16 tokens and entries per lane (of four lanes per token) loaded
-  // ahead.  What a sentence or a dictionary row has past them is loaded where
-  // it is merged, a memory latency per step: 60000 sentences of 10 to 80 tokens
-  // with 8 entries each took 447 us with 3 x 1, 320 us with 5 x 2; on sentences
-  // of 5 to 40 tokens with 4 entries the larger kinds gain nothing.
   auto go = [&](auto k) {
     hipLaunchKernelGGL(k, dim3(grid), dim3(64), lds, st, n_sent, sent_ids + k0, src_off, src_tok, d_row_off, d_col, d_val,
                        V, max_deg, hb, merged, cnt);

@@ -176,3 +176,18 @@ def test_traceback_in_bounds(program, pairs):
         got = M.run(program, b, op="align", S=S, gap=-0.125, threshold=threshold, passes=2)
         ora = oracle.align(ns, ms, S, -0.125, threshold)
         H.assert_align_equal(got, ora, ns, ms, check_path_as_kept=threshold < 0)
+
+
+@pytest.mark.parametrize("tokens,deg", [(48, 8), (49, 2), (49, 3), (80, 4), (80, 5), (81, 2), (81, 3), (81, 4), (128, 6),
+                                        (128, 8), (129, 3), (146, 7)])
+def test_merge_kinds_in_bounds(program, tokens, deg):
+    import dataclasses
+    rng = np.random.default_rng([67, tokens, deg])
+    V = 600
+    b = _batch([9], [40], V, [tokens, 1, 0, tokens // 2], [12, 30, 1], seed=8)
+    val = rng.random(V * deg).astype(np.float32)
+    b = dataclasses.replace(b, d_row_off=(np.arange(V + 1) * deg).astype(np.int32), d_val=val, d_deg=deg,
+                            d_col=rng.integers(0, V, V * deg).astype(np.int32))
+    got = M.run(program, b, params={"expand_fused": 0}, apart=True)
+    assert got["launches"]["merge"] > 0
+    assert H.s_rel_err(got["S"], oracle.score(b)["S64"]).max() <= 1e-5
