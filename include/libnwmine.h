@@ -325,6 +325,12 @@ nwm_status nwm_union_kept(const nwm_plan *plan, const int32_t *kept_fwd, const i
  *                                 drops (words outside the pair's target
  *                                 vocabulary, which no tile's contraction
  *                                 reads): identical results.
+ *   NWM_PARAM_SCORE_KIND          with SCORE_COMPACT = 1, which contraction: 0 =
+ *                                 the plan chooses for each part of the batch; 1
+ *                                 = over the words of a tile's target sentences
+ *                                 throughout; 2 = over each target sentence's own
+ *                                 words (batches of less than 2^29 target
+ *                                 tokens).  Default 0.
  * Out-of-range values give NWM_EINVAL.  Setting DP_HOT_PERCENT uploads the
  * plan's work list (synchronous).  A graph captured by nwm_mine is captured
  * again after any change. */
@@ -339,10 +345,16 @@ typedef enum {
   NWM_PARAM_SCORE_KGROUP = 7,
   NWM_PARAM_FILL_STAGING = 8,
   NWM_PARAM_EXPAND_FUSED = 9,
-  NWM_N_PARAMS = 10
+  NWM_PARAM_SCORE_KIND = 10,
+  NWM_N_PARAMS = 11
 } nwm_param;
 nwm_status nwm_plan_set_param(nwm_plan *plan, nwm_param param, int32_t value);
 nwm_status nwm_plan_get_param(const nwm_plan *plan, nwm_param param, int32_t *value);
+
+/* Cells of S (sum_b n_b m_b in all) by the contraction that scores them under
+ * the plan's present parameters: cells[0] over dense tiles, cells[1] as sums
+ * over each target sentence's words. */
+nwm_status nwm_plan_score_cells(const nwm_plan *plan, int64_t cells[2]);
 
 /* --- measurement ------------------------------------------------------------ */
 

@@ -157,6 +157,13 @@ class Plan:
         _abi.check(self.lib.nwm_plan_get_param(self.h, _abi.PARAMS[name], ctypes.byref(v)), "nwm_plan_get_param")
         return int(v.value)
 
+    def score_cells(self):
+        """(cells scored over dense tiles, cells scored as sums over each target
+        sentence's words) under the present parameters."""
+        c = (ctypes.c_int64 * 2)()
+        _abi.check(self.lib.nwm_plan_score_cells(self.h, c), "nwm_plan_score_cells")
+        return int(c[0]), int(c[1])
+
     def set_graph(self, on: bool):
         _abi.check(self.lib.nwm_plan_set_graph(self.h, int(bool(on))), "nwm_plan_set_graph")
 

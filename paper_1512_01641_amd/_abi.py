@@ -17,11 +17,11 @@ SYMBOLS = ["nwm_create", "nwm_destroy", "nwm_strerror", "nwm_plan_create", "nwm_
            "nwm_plan_destroy", "nwm_score_pairs", "nwm_align_batch", "nwm_align_backward", "nwm_mine",
            "nwm_plan_set_graph", "nwm_plan_set_param", "nwm_plan_get_param", "nwm_plan_set_timing",
            "nwm_plan_kernel_ms", "nwm_union_kept", "nwm_align_check", "nwm_last_device_error",
-           "nwm_align_batch_noalloc"]
+           "nwm_align_batch_noalloc", "nwm_plan_score_cells"]
 
 PARAMS = {"fill_waves_per_cu": 0, "merge_waves_per_cu": 1, "score_xcd_map": 2, "dp_hot_percent": 3,
           "score_compact": 4, "dp_spin_limit": 5, "dp_test_hold": 6, "score_kgroup": 7,
-          "fill_staging": 8, "expand_fused": 9}
+          "fill_staging": 8, "expand_fused": 9, "score_kind": 10}
 
 P = ctypes.c_void_p
 
@@ -93,6 +93,8 @@ def load(path: str | None = None):
     lib.nwm_plan_set_param.restype = I
     lib.nwm_plan_get_param.argtypes = [P, I, ctypes.POINTER(ctypes.c_int32)]
     lib.nwm_plan_get_param.restype = I
+    lib.nwm_plan_score_cells.argtypes = [P, ctypes.POINTER(ctypes.c_int64)]
+    lib.nwm_plan_score_cells.restype = I
     lib.nwm_plan_set_timing.argtypes = [P, I]
     lib.nwm_plan_set_timing.restype = I
     lib.nwm_plan_kernel_ms.argtypes = [P, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int32), I]

@@ -154,7 +154,7 @@ struct nwm_plan {
   int64_t n_bnd = 0;   // uint64 entries of the published-row region
   int max_entries = 1; // dictionary entries of the longest source sentence (tokens x max_deg)
   // launch parameters (nwm_param) and what re-deriving the DP priority flags needs
-  int32_t param[NWM_N_PARAMS] = {0, 0, 1, 50, 1, 0, 0, 1, 0, 1};
+  int32_t param[NWM_N_PARAMS] = {0, 0, 1, 50, 1, 0, 0, 1, 0, 1, 0};
   int max_sent_tokens = 0;   // the batch's bound on tokens per sentence
   uint64_t param_version = 0;
   std::vector<int32_t> it_strip;   // strip index per DP item (no flags)
@@ -183,7 +183,7 @@ struct nwm_plan {
   // them: the row tiles)
   struct Part {
     int rt, ct, gt, gs;
-    int64_t sent, tiles, rows;
+    int64_t sent, tiles, rows, cells;
   } part[4] = {};
   hipStream_t lane_stream = nullptr;   // the top pairs' DP
   hipEvent_t ev_top = nullptr, ev_top_done = nullptr;
@@ -281,6 +281,7 @@ bool sparse(const nwm_plan *p, int k) {
   const int64_t entries = p->src_tokens * p->max_deg;
   if (!p->param[NWM_PARAM_SCORE_COMPACT]) return false;
   if (p->tgt_tokens >= ((int64_t)1 << 29)) return false;   // list offsets of a run of sentences stay 32-bit
+  if (p->param[NWM_PARAM_SCORE_KIND]) return p->param[NWM_PARAM_SCORE_KIND] == 2;
   if (p->prec == NWM_BF16) {
     if (entries > 128 * p->n_src) return false;
     int64_t tiles = 0, rows = 0;
@@ -433,6 +434,7 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
     nwm_plan::Part &x = p->part[is_top[b] ? 0 : is_long[b] ? 1 : 2];
     x.tiles += r * c;
     x.rows += c > 0 ? r : 0;
+    x.cells += (int64_t)p->n[b] * p->m[b];
     wave_tiles += r * c;
   }
   const int run = (int)std::min<int64_t>(SCOLS, std::max<int64_t>(8, wave_tiles / 1024));
@@ -1143,6 +1145,7 @@ nwm_status nwm_plan_set_param(nwm_plan *p, nwm_param param, int32_t value) {
     case NWM_PARAM_SCORE_KGROUP:
       if (value != 1 && value != 2) return NWM_EINVAL;
       break;
+    case NWM_PARAM_SCORE_KIND:
     case NWM_PARAM_FILL_STAGING:
       if (value < 0 || value > 2) return NWM_EINVAL;
       break;
@@ -1171,6 +1174,13 @@ nwm_status nwm_plan_set_param(nwm_plan *p, nwm_param param, int32_t value) {
 nwm_status nwm_plan_get_param(const nwm_plan *p, nwm_param param, int32_t *value) {
   if (!p || !value || (int)param < 0 || (int)param >= NWM_N_PARAMS) return NWM_EINVAL;
   *value = p->param[param];
+  return NWM_OK;
+}
+
+nwm_status nwm_plan_score_cells(const nwm_plan *p, int64_t cells[2]) {
+  if (!p || !cells) return NWM_EINVAL;
+  cells[0] = cells[1] = 0;
+  for (int k = 0; k < 3; ++k) cells[sparse(p, k)] += p->part[k].cells;
   return NWM_OK;
 }
 

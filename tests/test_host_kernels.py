@@ -191,3 +191,13 @@ def test_merge_kinds_in_bounds(program, tokens, deg):
     got = M.run(program, b, params={"expand_fused": 0}, apart=True)
     assert got["launches"]["merge"] > 0
     assert H.s_rel_err(got["S"], oracle.score(b)["S64"]).max() <= 1e-5
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("case", ["lengths", "repeats", "row", "table"])
+def test_chosen_contractions_in_bounds(program, case, prec):
+    b = CASES[case]()
+    S = oracle.score(b)["S64"]
+    for params in ({"score_kind": 1}, {"score_kind": 1, "expand_fused": 0, "score_kgroup": 2}, {"score_kind": 2}):
+        got = M.run(program, b, prec=prec, params=params)["S"]
+        assert np.abs(got.astype(np.float64) - S).max() <= (2e-2 if prec else 1e-5)
