@@ -1478,7 +1478,7 @@ hipError_t launch_nw_reset(const PlanDev &P, float g, float *score, uint64_t *bn
 // head `head` (cleared by the reset).  Strips of one pair must all be in one
 // launch.
 hipError_t launch_nw_fill_items(const PlanDev &P, const float *S, float g, float *score, char *tb, uint64_t *bnd,
-                                int64_t n_bnd, int32_t *head, int32_t *err, int item0, int n, int task0, int nt,
+                                int32_t *head, int32_t *err, int item0, int n, int task0, int nt,
                                 int waves_per_cu, int spin_limit, int hold, int staging, hipStream_t st) {
   if (P.B <= 0 || n <= 0) return hipSuccess;
   if (g_fill_cus == 0) {
@@ -1534,11 +1534,11 @@ hipError_t launch_nw_fill_items(const PlanDev &P, const float *S, float g, float
 }
 
 hipError_t launch_nw_fill(const PlanDev &P, const float *S, float g, float *score, char *tb, uint64_t *bnd,
-                          int64_t n_bnd, int32_t *ctl, int waves_per_cu, int spin_limit, int hold, int staging,
+                          int32_t *ctl, int waves_per_cu, int spin_limit, int hold, int staging,
                           hipStream_t st) {
   hipError_t e = launch_nw_reset(P, g, score, bnd, ctl, staging, st);
   if (e != hipSuccess) return e;
-  return launch_nw_fill_items(P, S, g, score, tb, bnd, n_bnd, ctl, ctl + 1, 0, P.n_items, 0, P.n_tasks, waves_per_cu,
+  return launch_nw_fill_items(P, S, g, score, tb, bnd, ctl, ctl + 1, 0, P.n_items, 0, P.n_tasks, waves_per_cu,
                               spin_limit, hold, staging, st);
 }
 

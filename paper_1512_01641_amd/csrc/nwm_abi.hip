@@ -41,12 +41,12 @@ hipError_t launch_score(const PlanDev &, bool, const int64_t *, const int64_t *,
                         const int32_t *, const int2 *, const int64_t *, const int64_t *, int, int, hipStream_t);
 size_t score_lds_bytes(int nch, bool bf16);
 hipError_t score_set_attrs(int nch_max);
-hipError_t launch_nw_fill(const PlanDev &, const float *, float, float *, char *, uint64_t *, int64_t, int32_t *,
-                          int, int, int, int, hipStream_t);
+hipError_t launch_nw_fill(const PlanDev &, const float *, float, float *, char *, uint64_t *, int32_t *, int, int, int,
+                          int, hipStream_t);
 hipError_t fill_set_attrs(int);
 hipError_t launch_nw_reset(const PlanDev &, float, float *, uint64_t *, int32_t *, int, hipStream_t);
-hipError_t launch_nw_fill_items(const PlanDev &, const float *, float, float *, char *, uint64_t *, int64_t,
-                                int32_t *, int32_t *, int, int, int, int, int, int, int, int, hipStream_t);
+hipError_t launch_nw_fill_items(const PlanDev &, const float *, float, float *, char *, uint64_t *, int32_t *,
+                                int32_t *, int, int, int, int, int, int, int, int, hipStream_t);
 hipError_t launch_nw_walk(const PlanDev &, const char *, const float *, uint64_t *, int2 *, int32_t *, int, int, int,
                           int, int, int, hipStream_t);
 hipError_t launch_keep(const PlanDev &, const float *, float, const int2 *, const int32_t *, int2 *, int32_t *, int, int,
@@ -1029,7 +1029,7 @@ nwm_status nwm_align_batch(nwm_plan *p, const float *S, float gap, float thresho
   hipError_t e;
   {
     Mark mk(p, K_FILL, st);
-    e = launch_nw_fill(p->dev, S, gap, score, tbc, (uint64_t *)(w + p->ws.bnd), p->n_bnd,
+    e = launch_nw_fill(p->dev, S, gap, score, tbc, (uint64_t *)(w + p->ws.bnd),
                        (int32_t *)(w + p->ws.ctl), p->param[NWM_PARAM_FILL_WAVES_PER_CU],
                        p->param[NWM_PARAM_DP_SPIN_LIMIT], p->param[NWM_PARAM_DP_TEST_HOLD],
                        p->param[NWM_PARAM_FILL_STAGING], st);
@@ -1085,7 +1085,7 @@ nwm_status nwm_align_batch_noalloc(nwm_plan *p, const float *S, float gap, float
   uint64_t *bnd = reinterpret_cast<uint64_t *>(base + 256);
   // the reset kernel clears the queue heads, the error flag and the published
   // rows' tags left by the previous call (no memset node, no allocation)
-  hipError_t e = launch_nw_fill(p->dev, S, gap, score, tbc, bnd, p->n_bnd, ctl, p->param[NWM_PARAM_FILL_WAVES_PER_CU],
+  hipError_t e = launch_nw_fill(p->dev, S, gap, score, tbc, bnd, ctl, p->param[NWM_PARAM_FILL_WAVES_PER_CU],
                                 p->param[NWM_PARAM_DP_SPIN_LIMIT], p->param[NWM_PARAM_DP_TEST_HOLD],
                                 p->param[NWM_PARAM_FILL_STAGING], st);
   if (e == hipSuccess) e = walk_parts(p, tbc, score, bnd, path, n_diag, 0, 3, st);
@@ -1285,7 +1285,7 @@ static nwm_status mine_path(nwm_plan *p, const nwm_batch *batch, const nwm_dict 
     if (otop > 0) {
       if (e == hipSuccess) e = hipStreamWaitEvent(lane, p->ev_top, 0);
       if (e == hipSuccess)
-        e = launch_nw_fill_items(D, S, gap, score, tbc, bnd, p->n_bnd, ctl + 2, ctl + 1, 0, itop, 0, ttop, wpc, spin,
+        e = launch_nw_fill_items(D, S, gap, score, tbc, bnd, ctl + 2, ctl + 1, 0, itop, 0, ttop, wpc, spin,
                                  hold, stg, lane);
       if (e == hipSuccess) e = walk_parts(p, tbc, score, bnd, path, n_diag, 0, 1, lane);
       if (e == hipSuccess) e = keep_parts(p, S, threshold, path, n_diag, kept, n_kept, 0, 1, lane);
@@ -1294,7 +1294,7 @@ static nwm_status mine_path(nwm_plan *p, const nwm_batch *batch, const nwm_dict 
     if (ol > otop) {
       if (e == hipSuccess) e = hipStreamWaitEvent(aux, p->ev_long, 0);
       if (e == hipSuccess)
-        e = launch_nw_fill_items(D, S, gap, score, tbc, bnd, p->n_bnd, ctl + 3, ctl + 1, itop, il - itop, ttop,
+        e = launch_nw_fill_items(D, S, gap, score, tbc, bnd, ctl + 3, ctl + 1, itop, il - itop, ttop,
                                  tl - ttop, wpc, spin, hold, stg, aux);
       if (e == hipSuccess) e = walk_parts(p, tbc, score, bnd, path, n_diag, 1, 2, aux);
       if (e == hipSuccess)
@@ -1310,7 +1310,7 @@ static nwm_status mine_path(nwm_plan *p, const nwm_batch *batch, const nwm_dict 
   if (e == hipSuccess) e = hipStreamWaitEvent(st, p->ev_b_rest, 0);
   if (e == hipSuccess && scored) e = score_tiles(p, batch, sc, S, S_raw, ws, 2, 3, st);
   if (e == hipSuccess)
-    e = launch_nw_fill_items(D, S, gap, score, tbc, bnd, p->n_bnd, ctl, ctl + 1, il, D.n_items - il, tl,
+    e = launch_nw_fill_items(D, S, gap, score, tbc, bnd, ctl, ctl + 1, il, D.n_items - il, tl,
                              D.n_tasks - tl, wpc, spin, hold, stg, st);
   if (e == hipSuccess) e = walk_parts(p, tbc, score, bnd, path, n_diag, 2, 3, st);
   if (e == hipSuccess) e = keep_parts(p, S, threshold, path, n_diag, kept, n_kept, 2, 3, st);

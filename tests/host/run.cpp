@@ -14,15 +14,15 @@ void host_gap(size_t from, size_t to) { gaps.push_back({from, to}); }
 namespace nwm {
 hipError_t fill_set_attrs(int) { return 0; }
 hipError_t launch_nw_reset(const PlanDev &, float, float *, uint64_t *, int32_t *, int, hipStream_t) { return 0; }
-hipError_t launch_nw_fill_items(const PlanDev &, const float *, float, float *, char *, uint64_t *, int64_t, int32_t *,
-                                int32_t *, int, int, int, int, int, int, int, int, hipStream_t) {
+hipError_t launch_nw_fill_items(const PlanDev &, const float *, float, float *, char *, uint64_t *, int32_t *, int32_t *,
+                                int, int, int, int, int, int, int, int, hipStream_t) {
   return 0;
 }
 
 // The fill in plain code: scores and the traceback's bit planes (what lies
 // outside the lattice is noise).
-hipError_t launch_nw_fill(const PlanDev &P, const float *S, float g, float *score, char *tb, uint64_t *, int64_t, int32_t *,
-                          int, int, int, int, hipStream_t) {
+hipError_t launch_nw_fill(const PlanDev &P, const float *S, float g, float *score, char *tb, uint64_t *, int32_t *, int, int, int, int,
+                          hipStream_t) {
   uint64_t noise = 88172645463325252ull;
   for (int b = 0; b < P.B; ++b) {
     const int n = P.n[b], m = P.m[b], nG = (m + 126) >> 6;
