@@ -38,7 +38,8 @@ hipError_t launch_score_s(const PlanDev &, bool, int, int, const int64_t *, cons
 hipError_t sparse_set_attrs();
 hipError_t launch_score(const PlanDev &, bool, const int64_t *, const int64_t *, const uint2 *, const int32_t *,
                         const uint32_t *, const int32_t *, nwm_scorer, float *, float *, int, int, int, const uint2 *,
-                        const int32_t *, const int2 *, const int64_t *, const int64_t *, int, int, hipStream_t);
+                        const int32_t *, const int2 *, const int64_t *, const int64_t *, const GtMeta *, int, int,
+                        hipStream_t);
 size_t score_lds_bytes(int nch, bool bf16);
 hipError_t score_set_attrs(int nch_max);
 hipError_t launch_nw_fill(const PlanDev &, const float *, float, float *, char *, uint64_t *, int32_t *, int, int, int,
@@ -184,6 +185,7 @@ struct nwm_plan {
   struct Part {
     int rt, ct, gt, gs;
     int64_t sent, tiles, rows, cells;
+    int64_t rec;   // its first tile's record of the dense contraction (-1: no records)
   } part[4] = {};
   hipStream_t lane_stream = nullptr;   // the top pairs' DP
   hipEvent_t ev_top = nullptr, ev_top_done = nullptr;
@@ -392,7 +394,7 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
   std::vector<int64_t> sfirst(B + 1, 0), tfirst(B + 1, 0), s_off(B + 1, 0), p_off(B + 1, 0), tb_off(B + 1, 0);
   std::vector<int32_t> rt_pair, rt_row0, rt_rows, ct_pair, ct_col0, ct_cols;
   std::vector<int32_t> lane_gt(B + 1, 0), lane_rt(B + 1, 0), lane_ct(B + 1, 0);
-  std::vector<GtMeta> gs_meta;
+  std::vector<GtMeta> gs_meta, gt_meta;
   for (int b = 0; b < B; ++b) {
     const int64_t nb = p->n[b], mb = p->m[b];
     sfirst[b + 1] = sfirst[b] + nb;
@@ -438,6 +440,10 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
     wave_tiles += r * c;
   }
   const int run = (int)std::min<int64_t>(SCOLS, std::max<int64_t>(8, wave_tiles / 1024));
+  // records of the dense contraction's tiles, for the parts that take it
+  p->n_src = sfirst[B];
+  bool dense[3];
+  for (int k = 0; k < 3; ++k) dense[k] = p->part[k].tiles > 0 && !sparse(p, k);
   int64_t n_gt = 0;
   std::vector<int64_t> sent_ids;
   sent_ids.reserve((size_t)sfirst[B]);
@@ -447,7 +453,9 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
     p->part[k].gt = (int)n_gt;
     p->part[k].gs = (int)gs_meta.size();
     p->part[k].sent = (int64_t)sent_ids.size();
+    p->part[k].rec = k < 3 && dense[k] ? (int64_t)gt_meta.size() : -1;
   };
+  p->part[0].rec = dense[0] ? 0 : -1;
   mark(1);   // (moved on while there are top pairs)
   for (int pass = 0; pass < 2; ++pass) {
     const size_t q0 = pass == 0 ? 0 : n_long_pairs, q1 = pass == 0 ? n_long_pairs : lane_pairs.size();
@@ -471,6 +479,11 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
       lane_rt[q] = rt0;
       lane_ct[q] = ct0;
       n_gt += (int64_t)nrt * nct;
+      if (dense[is_top[b] ? 0 : is_long[b] ? 1 : 2])
+        for (int rt = rt0; rt < rt0 + nrt; ++rt)
+          for (int ct = ct0; ct < ct0 + nct; ++ct)
+            gt_meta.push_back(GtMeta{rt, ct, b, (int32_t)mb, rt_row0[rt], rt_rows[rt], ct_col0[ct], ct_cols[ct],
+                                     sfirst[b] + rt_row0[rt], tfirst[b] + ct_col0[ct], s_off[b], 0});
       if (nct > 0) {
         const int chunks = (nct + run - 1) / run, tiles = (nct + chunks - 1) / chunks;
         for (int r = 0; r < nb; r += SROWS)
@@ -650,6 +663,7 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
   size_t i_cn = add(ct_cols.data(), 4 * ct_cols.size());
   size_t i_lp = add(lane_pairs.data(), 4 * lane_pairs.size()), i_lg = add(lane_gt.data(), 4 * lane_gt.size());
   size_t i_lr = add(lane_rt.data(), 4 * lane_rt.size()), i_lc = add(lane_ct.data(), 4 * lane_ct.size());
+  size_t i_gt = add(gt_meta.data(), sizeof(GtMeta) * gt_meta.size());
   size_t i_gs = add(gs_meta.data(), sizeof(GtMeta) * gs_meta.size());
   size_t i_rm = add(rt_meta.data(), sizeof(TileMeta) * rt_meta.size());
   size_t i_cm = add(ct_meta.data(), sizeof(TileMeta) * ct_meta.size());
@@ -704,6 +718,7 @@ nwm_status nwm_plan_create(nwm_ctx *ctx, const nwm_batch *batch, int32_t max_deg
   D.lane_rt = (const int32_t *)at(i_lr);
   D.lane_ct = (const int32_t *)at(i_lc);
   D.n_gs = (int)gs_meta.size();
+  D.gt_meta = (const GtMeta *)at(i_gt);
   D.gs_meta = (const GtMeta *)at(i_gs);
   D.rt_meta = (const TileMeta *)at(i_rm);
   D.ct_meta = (const TileMeta *)at(i_cm);
@@ -955,12 +970,15 @@ static hipError_t score_tiles(nwm_plan *p, const nwm_batch *batch, nwm_scorer sc
                             (int32_t *)(w + p->ws.a_cnt), (uint16_t *)(w + p->ws.t_list), (uint2 *)(w + p->ws.t_rec),
                             (float *)(w + p->ws.t_len), sc, S, S_raw, p->part[i].gs, p->part[j].gs - p->part[i].gs, st);
     }
+    // (a kind chosen by parameter covers parts that have none)
+    const bool records = p->part[i].rec >= 0 && !p->param[NWM_PARAM_SCORE_KIND];
     return launch_score(p->dev, p->prec == NWM_BF16, batch->src_off, batch->tgt_off, (uint2 *)(w + p->ws.a_list),
                         (int32_t *)(w + p->ws.a_choff), (uint32_t *)(w + p->ws.b_list),
                         (int32_t *)(w + p->ws.b_choff), sc, S, S_raw, p->param[NWM_PARAM_SCORE_XCD_MAP],
                         p->param[NWM_PARAM_SCORE_COMPACT], p->param[NWM_PARAM_SCORE_KGROUP], (uint2 *)(w + p->ws.b_mt),
                         (int32_t *)(w + p->ws.b_kcn), (int2 *)(w + p->ws.b_rng), (int64_t *)(w + p->ws.a_base),
-                        (int64_t *)(w + p->ws.b_base), p->part[i].gt, p->part[j].gt - p->part[i].gt, st);
+                        (int64_t *)(w + p->ws.b_base),
+                        records ? p->dev.gt_meta + p->part[i].rec : nullptr, p->part[i].gt, p->part[j].gt - p->part[i].gt, st);
   });
   mk.done();
   return e;

@@ -128,6 +128,7 @@ struct PlanDev {
   // lane_pair[q]'s row tiles from lane_rt[q], column tiles from lane_ct[q] and
   // (row tile, column tile) products, row-major, from lane_gt[q]
   int n_gt;
+  const GtMeta *gt_meta;   // their records, in parts that take the dense contraction by default
   const int32_t *lane_pair, *lane_gt, *lane_rt, *lane_ct;   // [B + 1]
   // tiles of the sparse contraction: SROWS source sentences x column tiles
   int n_gs;

@@ -55,6 +55,16 @@ def test_parts_by_different_contractions_in_bounds(program):
     np.testing.assert_array_equal(_bits(mined["S"]), _bits(one["S"]))
 
 
+def test_tiles_with_and_without_records(program):
+    # a tall narrow pair (dense by the plan's rule, so its tiles have records)
+    # before wide ones (summed), then all of them dense by parameter
+    b = _batch([1300, 20, 30], [60, 330, 290], 2048, [5, 12], [5, 22, 9], seed=9)
+    S = oracle.score(b)["S64"]
+    for params in ({}, {"score_kind": 1}, {"score_kind": 2}):
+        got = M.run(program, b, prec=1, params=params, split=64)["S"]
+        assert np.abs(got.astype(np.float64) - S).max() <= 2e-2
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_drawn_plans_in_bounds(program, seed):
     rng = np.random.default_rng([41, seed])
