@@ -162,20 +162,24 @@ def rooflines(model, kernel_ms, prec_name):
     return out
 
 
-def summed_cells(batch, prec_name):
-    """Share of the cells whose contraction sums each target sentence's words
-    (k_score_s) instead of multiplying dense tiles (k_score_c): by the plan's
-    bound on a merged row's entries and, in BF16, for pairs of two and more
-    column tiles (the plan decides this for a part of the batch at a time)."""
-    T_src, n_src = int(batch.src_tok.size), int(batch.n.astype(np.int64).sum())
+def summed_model(batch):
+    """Algorithmic work of the classes whose kernels differ where the contraction
+    sums each target sentence's words (no dense tiles, no row-tile lists)."""
+    n, m = batch.n.astype(np.int64), batch.m.astype(np.int64)
+    cells, n_src, n_tgt = int(np.dot(n, m)), int(n.sum()), int(m.sum())
+    T_src, T_tgt = int(batch.src_tok.size), int(batch.tgt_tok.size)
     deg = np.diff(batch.d_row_off.astype(np.int64))
-    entries = T_src * int(deg.max()) if deg.size else 0
-    if entries > (128 if prec_name == "bf16" else 256) * n_src:
-        return 0.0
-    if prec_name != "bf16":
-        return 1.0
-    cells = batch.n.astype(np.int64) * batch.m
-    return float(cells[batch.m > 64].sum()) / max(int(cells.sum()), 1)
+    E = int(deg[batch.src_tok].sum()) if T_src else 0
+    return {
+        "expand_a": ("hbm", 4 * T_src + 8 * T_src + 8 * E + 16 * n_src + 8 * E + 4 * n_src,
+                     "merge: read 4 B token + 8 B dictionary row offsets per source token, 8 B per dictionary entry, "
+                     "16 B per sentence; write 8 B per merged entry (at most one per dictionary entry) + 4 B count per "
+                     "sentence"),
+        "build_b": ("hbm", 4 * T_tgt + 8 * n_tgt + 2 * T_tgt + 12 * n_tgt,
+                    "read: 4 B token + 8 B offset per target token / sentence; write: 2 B per distinct word of a "
+                    "sentence (at most one per token), 12 B record and length per sentence"),
+        "score": ("hbm", 4.0 * cells, "4 B/cell (S written; the words of each target sentence are summed in LDS)"),
+    }
 
 
 KERNEL_NAMES = {"merge": "k_merge_src", "build_a": "k_build_a", "expand_a": "k_expand_a", "build_b": "k_build_b",
@@ -212,12 +216,14 @@ def batched(nw, torch, ctx, batch, prec_name, prec, args, db=None, dd=None):
     kernel = {k: v[0] / args.steps for k, v in km.items() if v[1]}
     launches = {k: v[1] / args.steps for k, v in km.items() if v[1]}
     ms = eager_ms
+    score_cells = mn.plan.score_cells()
     if not args.no_graph:
         gstep = lambda: mn.mine(w, gap, thr, graph=True)
         ms = _time_steps(gstep, args.steps, max(args.warmup, 1), torch)
     _log("%s: eager %.4f ms/step, %s %.4f ms/step" % (prec_name, eager_ms, "eager" if args.no_graph else "graph",
                                                       ms))
-    return dict(ms=ms, eager_ms=eager_ms, kernel=kernel, launches=launches, params=params, miner=mn)
+    return dict(ms=ms, eager_ms=eager_ms, kernel=kernel, launches=launches, params=params, miner=mn,
+                score_cells=score_cells)
 
 
 def plain(nw, torch, ctx, batch, idx, dd):
@@ -243,21 +249,20 @@ def summarize(batch, res, prec_name, counted):
     """`counted`: the committed counter traffic was taken on this workload
     (the full 4096-pair one); elsewhere traffic is null."""
     model, cells, n_kc = work_model(batch)
-    summed = summed_cells(batch, prec_name)
-    if summed > 0.99:
-        # no dense tile is multiplied: what the scores cannot do without is
-        # their own write (the sums themselves are bound by LDS reads)
-        model["score"] = ("hbm", 4.0 * cells, "4 B/cell (S written; the words of each target sentence are summed in "
-                          "LDS, no dense tile is multiplied)")
+    dense, summed = res["score_cells"]   # cells by the contraction that scored them
+    if summed:
+        # (with dense tiles beside: a bound that leaves their lists out)
+        model.update(summed_model(batch))
     rl = rooflines(model, res["kernel"], prec_name)
     for k, r in rl.items():
-        name = KERNEL_NAMES[k] % prec_name if "%" in KERNEL_NAMES[k] else KERNEL_NAMES[k]
-        if summed > 0.99:
-            name = {"score": "k_score_s", "build_b": "k_tgt_lists"}.get(k, name)
-        elif summed > 0.0 and k == "score":
-            r["algorithmic"] += "; where sentences are summed word by word (k_score_s) the rate is an equivalent one"
+        key = name = KERNEL_NAMES[k] % prec_name if "%" in KERNEL_NAMES[k] else KERNEL_NAMES[k]
+        if summed:
+            own = {"score": "k_score_s", "build_b": "k_tgt_lists", "expand_a": "k_expand_a<false>"}
+            name = own.get(k, name) if not dense or k not in own else "%s + %s" % (own[k], name)
+            if dense and k in own:
+                r["algorithmic"] += "; dense tiles take %.1f %% of the cells" % (100.0 * dense / (dense + summed))
         r["kernel"] = name
-        r["traffic"] = profiled_traffic(name) if counted else None
+        r["traffic"] = profiled_traffic(key) if counted else None
     dom = max(rl, key=lambda k: rl[k]["kernel_ms"])
     fill = res["kernel"].get("nw_fill")
     return dict(pairs_per_s=round(batch.B / (res["ms"] / 1000.0), 2), ms_per_step=round(res["ms"], 4),
@@ -465,7 +470,7 @@ def main():
         dt = time.perf_counter() - t0
         search = {"trials_per_s": round(trials / dt, 2), "pairs": tb_.B, "trials": trials,
                   "best": {"threshold": res["threshold"], "gap": res["gap"], "similarity": round(res["similarity"], 3)},
-                  "note": "per trial: NW fill + traceback + keep on the GPU, similarity on the host"}
+                  "note": "per trial: NW fill + traceback + keep on the GPU, similarity counted there; trials queue up"}
         del smn
 
     plain_ms = None

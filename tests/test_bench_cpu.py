@@ -42,3 +42,22 @@ def test_rooflines_and_dominant():
     assert abs(rl["nw_fill"]["frac"] - round(ach / 8000.0, 4)) < 1e-9
     assert max(rl, key=lambda k: rl[k]["kernel_ms"]) == "nw_fill"
     assert isinstance(bench.cpu_model(), str)
+
+
+def test_kernels_named_by_what_the_plan_chose():
+    b = corpus.make_batch(2, pairs=16)
+    km = {"score": 0.2, "build_b": 0.1, "expand_a": 0.3, "nw_fill": 0.1}
+    cells = b.cells()
+
+    def names(dense, summed):
+        res = dict(kernel=km, launches={}, params={}, ms=1.0, eager_ms=1.0, score_cells=(dense, summed))
+        rl = bench.summarize(b, res, "bf16", counted=False)["rooflines"]
+        return {k: (r["kernel"], r["bound"]) for k, r in rl.items()}
+    assert names(cells, 0)["score"] == ("k_score_c<bf16>", "mfma")
+    only = names(0, cells)
+    assert only["score"] == ("k_score_s", "hbm") and only["build_b"][0] == "k_tgt_lists"
+    assert only["expand_a"][0] == "k_expand_a<false>" and only["nw_fill"][0] == "k_nw_fill"
+    assert names(cells // 2, cells - cells // 2)["score"] == ("k_score_s + k_score_c<bf16>", "hbm")
+    model = bench.summed_model(b)
+    assert model["score"][1] == 4.0 * cells
+    assert model["build_b"][1] == 6 * len(b.tgt_tok) + 20 * int(b.m.sum())
