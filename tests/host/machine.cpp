@@ -64,11 +64,23 @@ void sync_block() { yield(BLOCK); }
   std::abort();
 }
 
+// With HOST_ORDER set the waves of a workgroup, and the lanes of a wave, run in
+// another order at every turn: a result that depends on it is a race.
+static uint64_t turn = 0;
+static int place(int k, int n) {   // k-th of n
+  if (!turn) return k;
+  const uint64_t a = (turn >> 20) % (uint64_t)n;
+  return (turn >> 40) & 1 ? (int)((a + n - (uint64_t)k) % n) : (int)((a + (uint64_t)k) % n);
+}
+static void next_turn() { turn = turn * 6364136223846793005ull + 1442695040888963407ull; }
+
 void launch(const char *name, dim3 g, dim3 b, size_t lds, const std::function<void()> &f) {
   grid_dim = g;
   block_dim = b;
   body = &f;
   const int T = (int)b.x, W = (T + 63) / 64;
+  const char *seed = std::getenv("HOST_ORDER");
+  turn = seed ? std::strtoull(seed, nullptr, 10) * 0x9E3779B97F4A7C15ull + 1 : 0;
   while ((int)stacks.size() < T) stacks.push_back((char *)aligned_alloc(64, STACK));
   took_part.assign(W, 0);
   buffers.assign(W, std::vector<char>(2 * 64 * 64));
@@ -89,15 +101,23 @@ void launch(const char *name, dim3 g, dim3 b, size_t lds, const std::function<vo
     }
     for (bool more = true; more;) {
       more = false;
-      for (int w = 0; w < W; ++w) {
-        const int a = 64 * w, e = std::min(T, a + 64);
+      if (turn) next_turn();
+      const uint64_t of_waves = turn;
+      for (int v = 0; v < W; ++v) {
+        const uint64_t of_lanes = turn;
+        turn = of_waves;
+        const int w = place(v, W), a = 64 * w, e = std::min(T, a + 64);
+        turn = of_lanes;
         for (;;) {
-          for (int t = a; t < e; ++t)
+          if (turn) next_turn();
+          for (int k = 0; k < e - a; ++k) {
+            const int t = a + place(k, e - a);
             if (lanes[t].st == READY) {
               cur = t;
               thread_idx.x = (unsigned)t;
               wave_switch(&scheduler, lanes[t].sp);
             }
+          }
           int first = -1, waits = 0;
           for (int t = a; t < e; ++t) {
             const Lane &l = lanes[t];

@@ -109,10 +109,11 @@ def build(folder) -> str:
 
 
 def run(program, batch, op="score", prec=0, params=None, raw=True, bound=None, passes=1, E=None, S=None, S_raw=None,
-        apart=False, split=None, gap=-0.2, threshold=0.5):
+        apart=False, split=None, order=None, gap=-0.2, threshold=0.5):
     """One job ("score", "mine", the dense "backward" or "align" over S); a sanitizer report
     ends the program and raises.  apart: no two lists share space; split: tiles
-    from which a batch's parts choose their contraction each.  Returns S, S_raw, the launches per kernel
+    from which a batch's parts choose their contraction each; order: a seed for the
+    order in which waves and lanes run.  Returns S, S_raw, the launches per kernel
     class and the backward's weight gradient."""
     n, m = np.asarray(batch.n, np.int64), np.asarray(batch.m, np.int64)
     bound = int(np.diff(batch.src_off).max(initial=0)) if bound is None else bound
@@ -135,6 +136,8 @@ def run(program, batch, op="score", prec=0, params=None, raw=True, bound=None, p
                UBSAN_OPTIONS="print_stacktrace=1:halt_on_error=1")
     if apart:
         env["HOST_APART"] = "1"
+    if order is not None:
+        env["HOST_ORDER"] = str(order)
     if split is not None:
         env["HOST_SPLIT"] = str(split)
     r = subprocess.run([program, job, res], capture_output=True, text=True, env=env)

@@ -33,6 +33,9 @@ def test_contractions_in_bounds(program, case, prec):
     np.testing.assert_array_equal(_bits(one["S_raw"]), _bits(two["S_raw"]))
     quiet = M.run(program, b, prec=prec, raw=False)
     np.testing.assert_array_equal(_bits(quiet["S"]), _bits(one["S"]))
+    for order in (1, 2):   # waves and lanes in other orders: no race
+        other = M.run(program, b, prec=prec, order=order)
+        np.testing.assert_array_equal(_bits(other["S"]), _bits(one["S"]))
     ora = oracle.score(b)
     if prec == 0:
         assert H.s_rel_err(one["S"], ora["S64"]).max() <= 1e-5
@@ -183,7 +186,7 @@ def test_traceback_in_bounds(program, pairs):
     S = np.concatenate([_path_case(*PATHS[k], rng) for k in names] + [rng.random(70 * 50).astype(np.float32)])
     b = _batch(ns, ms, 10, [0], [0])
     for threshold in (0.5, -1e30):
-        got = M.run(program, b, op="align", S=S, gap=-0.125, threshold=threshold, passes=2)
+        got = M.run(program, b, op="align", S=S, gap=-0.125, threshold=threshold, passes=2, order=3 if threshold < 0 else None)
         ora = oracle.align(ns, ms, S, -0.125, threshold)
         H.assert_align_equal(got, ora, ns, ms, check_path_as_kept=threshold < 0)
 
