@@ -143,7 +143,8 @@ void nwm_plan_destroy(nwm_plan *plan);
  * Y exact) and accumulates in FP32: on MFMA over dense tiles, or, where the
  * target sentences' words are few against the tiles' vocabulary, as sums over
  * each target sentence's words (BF16: on MFMA; FP32: the same additions in the
- * same order, identical results).
+ * same order).  A value of D that is infinite or NaN (BF16: once rounded) reaches
+ * cells of the source sentences that bring it only.
  * Outputs (device, FP32, row-major n_b x m_b blocks, pair b at element
  * offset sum_{c<b} n_c m_c): S [S_elems]; S_raw [S_elems] or NULL.
  * ws: device workspace of ws_bytes, contents need not persist. */
@@ -292,8 +293,10 @@ nwm_status nwm_union_kept(const nwm_plan *plan, const int32_t *kept_fwd, const i
  *                                 0 = over the whole vocabulary.  Default 1.
  *                                 The FP32 sums are taken in another order, so
  *                                 S may differ in the last bits.
- *   NWM_PARAM_DP_SPIN_LIMIT       polls of the row above before a DP wave gives
- *                                 up (0 = the default, 2^22; at most 2^30)
+ *   NWM_PARAM_DP_SPIN_LIMIT       polls of the row above in memory before a DP
+ *                                 wave gives up (0 = the default, 2^22; at most
+ *                                 2^30); where the row comes through LDS, four
+ *                                 polls count as one
  *   NWM_PARAM_DP_TEST_HOLD        testing only: 1 = the first strip of every
  *                                 pair taller than one strip publishes nothing,
  *                                 so the strips below it give up (exercises the
