@@ -40,6 +40,18 @@ def test_dense_variants_give_the_same_bits(batch, prec):
             np.testing.assert_array_equal(other[k].view(np.uint32), one[k].view(np.uint32))
 
 
+@pytest.mark.parametrize("batch", ["ragged", "fused edges"])
+def test_fp32_kinds_add_in_one_order(batch):
+    # each target sentence's own words, a tile's, the whole vocabulary: the same
+    # FP32 additions, the others add zeros between them
+    b = BATCHES[batch]()
+    summed = H.run_gpu(b, prec=0)
+    assert summed["miner"].plan.score_cells() == (0, b.cells())
+    for other in (_dense(b, 0), H.run_gpu(b, prec=0, params={"score_compact": 0})):
+        for k in ("S", "S_raw"):
+            np.testing.assert_array_equal(other[k].view(np.uint32), summed[k].view(np.uint32))
+
+
 def test_kinds_are_counted():
     import paper_1512_01641_amd as nw
     b = corpus.make_batch(2, pairs=40)
